@@ -712,7 +712,7 @@ int make_paged_plan(const hk_shape *s, int64_t B, const hk_paged_cache *c, Paged
     p->off_prep = end;
     if (p->M > 0 && hk::kv_gemm_uses_prepared(p->M, s->d, s->gemm_tile, s->dtype)) end += prepared_layout(s->d).total;
     p->off_partial = end;
-    p->n_waves = hk::attn_wavefronts(s->n_heads, c->total_tokens, 0, hk::kPagedResidentWaves);
+    p->n_waves = hk::attn_wavefronts(s->n_heads, c->total_tokens, 0);
     end += align_up(((size_t)p->n_waves + (size_t)B * s->n_heads) * (s->head_dim + 2) * sizeof(float));
     p->total = end;
     return HK_OK;
@@ -817,7 +817,7 @@ int make_paged_absorbed_plan(const hk_shape *s, int64_t B, const hk_paged_cache 
     p->off_proj = take(act ? absorbed_proj_floats(s, B) * sizeof(float) : 0);
     p->off_partial = end;
     // the attention over the KV blocks alone: sized for every token being cached (the device knows the true number)
-    p->n_waves = hk::attn_wavefronts(s->n_heads, c->total_tokens, 0, hk::kPagedResidentWaves);
+    p->n_waves = hk::attn_wavefronts(s->n_heads, c->total_tokens, 0);
     take(((size_t)p->n_waves + bh) * (s->head_dim + 2) * sizeof(float));
     p->total = end;
     return HK_OK;

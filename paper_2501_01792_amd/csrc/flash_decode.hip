@@ -14,46 +14,32 @@
 //     is unique, and makes the partials of one pair a contiguous run.  A second small kernel
 //     merges the run of every pair by log-sum-exp.  Wavefronts never talk to each other: no LDS,
 //     no barrier.
-//   * A wavefront consumes 64 tokens at a time.  dh/8 lanes cover one row with 16-byte loads, so
-//     every load instruction of a wavefront reads whole, consecutive rows (1 KiB contiguous), and
-//     all K and V loads of the 64 tokens are issued before the first use.
-//   * q.k: each lane forms the partial dot product of its 8 elements (v_dot2_f32_f16, fp32
-//     accumulation); the dh/8 partials of the dh/8 rows a lane group holds are combined with a
-//     reduce-scatter butterfly, after which every lane owns the complete score of exactly one
-//     token: the softmax work (exp2, running max/sum) is done once per token, not per element.
-//   * Online softmax state is kept per lane group (the lanes sharing a row) in the log2 domain
-//     with a finite "-infinity" so that fully masked tiles need no special case.
+//   * A wavefront consumes 64 tokens at a time (attn_tile.h).  dh/8 lanes cover one row with 16-byte loads, so
+//     every load instruction of a wavefront reads whole, consecutive rows (1 KiB contiguous), and all K and V
+//     loads of the 64 tokens are issued before the first use: 128 registers of rows, 3 wavefronts per SIMD.  Left to
+//     the compiler (4 per SIMD) the V rows were asked for behind the K rows' use, a second memory latency per step,
+//     and in bf16 they were widened on arrival (246 registers, 2 per SIMD).
+//   * Small problems are cut into ranges of one step each, aligned to the pairs, so that they too fill the chip and pay
+//     one latency (with at least 128 tokens per range, 64,000 positions ran on 125 of 256 compute units).
+// Measured (kernel alone): 4.8 GB in 718 us (6.73 TB/s; 731 before all rows were asked for at once), 2.1 GB bf16 in
+// 312 us (6.7 TB/s; 327), 33 MB of one request in 7.8 us (26).
 #include "hk_internal.h"
 #include "elem.h"
+#include "attn_merge.h"
 #include "attn_ranges.h"
+#include "attn_tile.h"
 
 namespace hk {
 namespace {
 
-
 constexpr int kThreads = 256;
 constexpr int kWavesPerBlock = 4;
-constexpr int kTile = 64;               // tokens per wavefront step
-constexpr float kNegBig = -1.0e30f;     // finite stand-in for -inf in running maxima
-
-template <int DT>
-__device__ __forceinline__ float dot8(typename Elem<DT>::V8 a, typename Elem<DT>::V8 b)
-{
-    typedef typename Elem<DT>::V2 half2_t;
-    float s = 0.f;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        half2_t x = {a[2 * j], a[2 * j + 1]};
-        half2_t y = {b[2 * j], b[2 * j + 1]};
-        s = Elem<DT>::dot2(x, y, s);
-    }
-    return s;
-}
+using attn::kTile;
 
 using ranges::range_begin;
 
 template <int DH, int DT>
-__global__ __launch_bounds__(kThreads) void flash_decode_kernel(
+__global__ __launch_bounds__(kThreads, 3) void flash_decode_kernel(
     const typename Elem<DT>::T *__restrict__ q,
     const typename Elem<DT>::T *__restrict__ K0, const typename Elem<DT>::T *__restrict__ V0,
     const typename Elem<DT>::T *__restrict__ K1, const typename Elem<DT>::T *__restrict__ V1,
@@ -62,9 +48,8 @@ __global__ __launch_bounds__(kThreads) void flash_decode_kernel(
 {
     typedef typename Elem<DT>::T elem_t;
     typedef typename Elem<DT>::V8 half8_t;
-    constexpr int LPR = DH / 8;          // lanes per row
-    constexpr int RPL = 64 / LPR;        // rows per load instruction == lane groups per wavefront
-    constexpr int NL = LPR;              // loads per lane per 64-token tile
+    typedef attn::Tile<DH, DT> tile_t;
+    constexpr int LPR = tile_t::LPR, RPL = tile_t::RPL, NL = tile_t::NL;
 
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6));   // wavefront-uniform
@@ -75,16 +60,14 @@ __global__ __launch_bounds__(kThreads) void flash_decode_kernel(
     int64_t p = range_begin(w, total, W);
     const int64_t p_end = range_begin(w + 1, total, W);
     while (p < p_end) {
-        const int bh = (int)(p / L);
+        const int bh = (int)ranges::quot(p, L);
         const int t_first = (int)(p - (int64_t)bh * L);
         const int64_t pair_end = (int64_t)(bh + 1) * L;
         const int t_last = (int)((p_end < pair_end ? p_end : pair_end) - (int64_t)bh * L);   // tokens [t_first, t_last) of pair bh
 
         const half8_t qv = *reinterpret_cast<const half8_t *>(q + (int64_t)bh * DH + c * 8);
-        float m_run = kNegBig, l_run = 0.f;
-        float acc[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) acc[j] = 0.f;
+        tile_t tile;
+        tile.clear();
 
         // the part of [t_first, t_last) inside the first segment, then the part inside the second
 #pragma unroll 1
@@ -99,102 +82,54 @@ __global__ __launch_bounds__(kThreads) void flash_decode_kernel(
 
             for (int tb = t_begin; tb < t_end; tb += kTile) {
                 half8_t kr[NL], vr[NL];
+                // row of load i: the step's first row (scalar) plus a 32-bit lane offset; rows past the end re-read the
+                // last one and are masked
+                const elem_t *Kt = Kp + (int64_t)tb * DH, *Vt = Vp + (int64_t)tb * DH;
+                const int rows = t_end - tb;
+                auto lane_off = [&](int i) {
+                    const int r = i * RPL + g;
+                    return (uint32_t)((r < rows ? r : rows - 1) * DH + c * 8);
+                };
 #pragma unroll
-                for (int i = 0; i < NL; ++i) {
-                    int t = tb + i * RPL + g;
-                    if (t >= t_end) t = t_end - 1;                 // clamp; the score is masked below
-                    kr[i] = __builtin_nontemporal_load(reinterpret_cast<const half8_t *>(Kp + (int64_t)t * DH + c * 8));
-                }
+                for (int i = 0; i < NL; ++i) kr[i] = __builtin_nontemporal_load(reinterpret_cast<const half8_t *>(Kt + lane_off(i)));
 #pragma unroll
-                for (int i = 0; i < NL; ++i) {
-                    int t = tb + i * RPL + g;
-                    if (t >= t_end) t = t_end - 1;
-                    vr[i] = __builtin_nontemporal_load(reinterpret_cast<const half8_t *>(Vp + (int64_t)t * DH + c * 8));
-                }
-
-                // partial dot products, then reduce-scatter over the LPR lanes of a group
-                float pd[NL];
-#pragma unroll
-                for (int i = 0; i < NL; ++i) pd[i] = dot8<DT>(qv, kr[i]);
-#pragma unroll
-                for (int h = NL / 2; h >= 1; h >>= 1) {
-                    const bool up = (c & h) != 0;
-#pragma unroll
-                    for (int i = 0; i < h; ++i) {
-                        const float send = up ? pd[i] : pd[i + h];
-                        const float keep = up ? pd[i + h] : pd[i];
-                        pd[i] = keep + __shfl_xor(send, h, 64);
-                    }
-                }
-                // lane (g, c) now owns the score of token tb + c*RPL + g
-                const int my_t = tb + c * RPL + g;
-                const float s = (my_t < t_end) ? pd[0] * scale_log2e : -INFINITY;
-
-                float m_tile = s;
-#pragma unroll
-                for (int h = LPR / 2; h >= 1; h >>= 1) m_tile = fmaxf(m_tile, __shfl_xor(m_tile, h, 64));
-                const float m_new = fmaxf(m_run, m_tile);
-                const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
-                const float pe = __builtin_amdgcn_exp2f(s - m_new);
-                m_run = m_new;
-                l_run = l_run * alpha + pe;
-#pragma unroll
-                for (int j = 0; j < 8; ++j) acc[j] *= alpha;
-
-#pragma unroll
-                for (int i = 0; i < NL; ++i) {
-                    const float wgt = __shfl(pe, g * LPR + i, 64);   // weight of token tb + i*RPL + g
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) acc[j] = __builtin_fmaf(wgt, (float)vr[i][j], acc[j]);
-                }
+                for (int i = 0; i < NL; ++i) vr[i] = __builtin_nontemporal_load(reinterpret_cast<const half8_t *>(Vt + lane_off(i)));
+                __builtin_amdgcn_sched_barrier(0);                 // every load of the step is on its way before the first use
+                tile.consume(qv, kr, vr, lane, tb + c * RPL + g < t_end, scale_log2e);
             }
         }
-
-        // ---- combine the lane groups of the wavefront: l over the lanes of a group, then (m, l, o) over groups
-#pragma unroll
-        for (int h = LPR / 2; h >= 1; h >>= 1) l_run += __shfl_xor(l_run, h, 64);
-#pragma unroll
-        for (int off = LPR; off < 64; off <<= 1) {
-            const float m_o = __shfl_xor(m_run, off, 64);
-            const float l_o = __shfl_xor(l_run, off, 64);
-            const float m_new = fmaxf(m_run, m_o);
-            const float sa = __builtin_amdgcn_exp2f(m_run - m_new), sb = __builtin_amdgcn_exp2f(m_o - m_new);
-            l_run = l_run * sa + l_o * sb;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) acc[j] = acc[j] * sa + __shfl_xor(acc[j], off, 64) * sb;
-            m_run = m_new;
-        }
-        if (g == 0) {
-            float *dst = partial + ((int64_t)w + bh) * (DH + 2);
-#pragma unroll
-            for (int j = 0; j < 8; ++j) dst[2 + c * 8 + j] = acc[j];
-            if (c == 0) { dst[0] = m_run; dst[1] = l_run; }
-        }
+        tile.store(partial + ((int64_t)w + bh) * (DH + 2), lane);
         p = (int64_t)bh * L + t_last;
     }
 }
 
-// Log-sum-exp merge of the partials of one (sequence, head): those of the wavefronts whose range
+// Log-sum-exp merge of the partials of every (sequence, head), P wavefronts each: those of the wavefronts whose range
 // meets the pair's positions [bh L, (bh+1) L), at indices (wavefront + bh).
-template <int DH, int DT>
-__global__ __launch_bounds__(DH) void merge_partials_kernel(const float *__restrict__ partial, int L, int64_t total,
-                                                            int W, typename Elem<DT>::T *__restrict__ out, float2 *__restrict__ lse)
+template <int DH, int DT, int P>
+__global__ __launch_bounds__(merge::kThreads) void merge_partials_kernel(const float *__restrict__ partial, int L, int64_t total,
+                                                                         int W, int BH, typename Elem<DT>::T *__restrict__ out,
+                                                                         float2 *__restrict__ lse)
 {
-    const int bh = blockIdx.x, e = threadIdx.x;
+    __shared__ merge::Shared<DH, P> sh;
+    const int wave = threadIdx.x >> 6;
+    int bh = blockIdx.x * (kWavesPerBlock / P) + wave / P;
+    const bool live = bh < BH;
+    if (!live) bh = BH - 1;                                    // works on the last pair (the workgroup shares a barrier), stores nothing
     const int64_t lo = (int64_t)bh * L, hi = lo + L - 1;       // first and last position of the pair
     const int w_first = ranges::owner(lo, total, W), w_last = ranges::owner(hi, total, W);
-    const float *src = partial + ((int64_t)w_first + bh) * (DH + 2);
-    const int n = w_last - w_first + 1;
-    float mx = kNegBig;
-    for (int i = 0; i < n; ++i) mx = fmaxf(mx, src[i * (DH + 2)]);
-    float o = 0.f, l = 0.f;
-    for (int i = 0; i < n; ++i) {
-        const float wgt = __builtin_amdgcn_exp2f(src[i * (DH + 2)] - mx);
-        o = __builtin_fmaf(wgt, src[i * (DH + 2) + 2 + e], o);
-        l = __builtin_fmaf(wgt, src[i * (DH + 2) + 1], l);
-    }
-    out[(int64_t)bh * DH + e] = (typename Elem<DT>::T)(o / l);
-    if (lse && e == 0) lse[bh] = make_float2(mx, l);
+    float m, l, o[DH / 64];
+    merge::merge_run<DH, P>(partial + ((int64_t)w_first + bh) * (DH + 2), w_last - w_first + 1, sh, m, l, o);
+    if (!live || wave % P != 0) return;
+    merge::store_row<DH>(out + (int64_t)bh * DH, o, l);
+    if (lse && (threadIdx.x & 63) == 0) lse[bh] = make_float2(m, l);
+}
+
+template <int DH, int DT, int P>
+void launch_merge(const AttnArgs &a, int L, int64_t total, hipStream_t s)
+{
+    constexpr int pairs = kWavesPerBlock / P;                  // of a workgroup
+    hipLaunchKernelGGL((merge_partials_kernel<DH, DT, P>), dim3((unsigned)((a.BH + pairs - 1) / pairs)), dim3(merge::kThreads), 0, s,
+                       a.partial, L, total, a.n_waves, a.BH, static_cast<typename Elem<DT>::T *>(a.out), a.lse);
 }
 
 template <int DH, int DT>
@@ -213,8 +148,8 @@ hipError_t launch_dh(const AttnArgs &a, hipStream_t s)
     hipError_t e = hipGetLastError();
     if (e == hipSuccess && a.after_main) e = hipEventRecord(a.after_main, s);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((merge_partials_kernel<DH, DT>), dim3((unsigned)a.BH), dim3(DH), 0, s,
-                       a.partial, L, total, a.n_waves, static_cast<elem_t *>(a.out), a.lse);
+    if (merge::waves_per_pair(a.n_waves, a.BH) == 1) launch_merge<DH, DT, 1>(a, L, total, s);
+    else launch_merge<DH, DT, 4>(a, L, total, s);
     return hipGetLastError();
 }
 
@@ -259,7 +194,7 @@ hipError_t launch_segment_join(const void *out_a, const float2 *lse_a, const voi
     return hipGetLastError();
 }
 
-int attn_wavefronts(int64_t BH, int64_t L, int splits, int resident)
+int attn_wavefronts(int64_t BH, int64_t L, int splits)
 {
     const int64_t total = BH * L;
     if (total <= 0) return 0;
@@ -267,8 +202,10 @@ int attn_wavefronts(int64_t BH, int64_t L, int splits, int resident)
     if (splits > 0) {
         W = BH * splits;                                       // `splits` equal token ranges per pair
     } else {
-        W = resident;                                          // every wavefront resident: one round
-        const int64_t by_work = (total + 2 * kTile - 1) / (2 * kTile);   // at least ~128 tokens each
+        W = kAttnResidentWaves;                                // every wavefront resident: one round
+        // Small problems: every pair cut into ranges of at most one step of 64 tokens, none across two pairs, so that
+        // a wavefront asks for all of its bytes at once and pays one memory latency.
+        const int64_t by_work = BH * ((L + kTile - 1) / kTile);
         if (W > by_work) W = by_work;
     }
     if (W > total) W = total;                                  // no empty range

@@ -69,16 +69,16 @@ struct AttnArgs {
     hipEvent_t after_main; // optional: recorded after the streaming kernel, before the merge
     int dtype;             // 0: fp16, 1: bf16
 };
-// Wavefronts of the attention kernel that stay resident together on an MI355X: 256 compute units x
-// 4 SIMDs x 4 wavefronts (the kernel's register footprint, <= 128 VGPRs, allows 4 per SIMD).
-constexpr int kAttnResidentWaves = 256 * 4 * 4;
-// The paged kernel carries block addressing on top and fits 3 wavefronts per SIMD.
-constexpr int kPagedResidentWaves = 256 * 4 * 3;
+// Wavefronts of the attention kernels (contiguous and paged) that stay resident together on an MI355X: 256 compute
+// units x 4 SIMDs x 3 wavefronts (a wavefront holds the K and V rows of a whole step, 128 registers of <= 168).
+// 2048, 4096 and 6144 wavefronts were level with 3072 or up to 5 % slower (2.1 GB cached: 329, 331, 331 against 328 us;
+// 67 MB: 26.9, 27.6, 27.7 against 26.1 us).
+constexpr int kAttnResidentWaves = 256 * 4 * 3;
 constexpr int kAttnMaxWaves = 1 << 20;
 // Number of wavefronts the attention kernel uses for BH pairs of L tokens; splits > 0 asks for
 // that many token ranges per pair.  A function of the shape only, so that workspace sizes can be
 // computed without a device.
-int attn_wavefronts(int64_t BH, int64_t L, int splits, int resident = kAttnResidentWaves);
+int attn_wavefronts(int64_t BH, int64_t L, int splits);
 // Single-query attention over the two token segments taken as one context.
 hipError_t launch_flash_decode(const AttnArgs &a, hipStream_t s);
 // Joins the attention results of two disjoint token segments of the same (sequence, head) pairs: out_x [BH, dh]
