@@ -115,11 +115,11 @@ size_t hk_regen_workspace_bytes(const hk_shape *shape, int32_t B, int32_t L_act)
  * statistics are applied to the accumulators.  hk_prepare_layer computes W'
  * (fp16), c and b' (fp32) into `prepared` (device, 256-byte aligned, at least
  * hk_prepared_bytes(shape) bytes, owned by the caller, valid as long as it is
- * referenced from hk_layer_params.prepared).  Large regenerations run on this
- * form.  A call that is not given a prepared layer prepares one itself, in its
- * workspace, every time (one extra pass over the weights); a caller that keeps
- * the layer prepared saves that pass.  Small regenerations apply the LayerNorm
- * on the fly instead and ignore `prepared`.
+ * referenced from hk_layer_params.prepared).  With gemm_tile = 0, regenerations
+ * of every size run on this form when the caller brings it.  Without it, a large
+ * regeneration prepares the layer itself, in its workspace, every time (one extra
+ * pass over the weights), and a small one applies the LayerNorm on the fly, which
+ * is two to four times slower than the prepared form.
  */
 size_t hk_prepared_bytes(const hk_shape *shape);
 int hk_prepare_layer(const hk_shape *shape, const hk_layer_params *params,

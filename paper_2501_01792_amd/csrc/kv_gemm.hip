@@ -8,7 +8,8 @@
 //   * One workgroup = 4 wavefronts (one per SIMD) computes a BM x BN output tile; the
 //     wavefronts form a 2 x 2 grid, each owning a (BM/2) x (BN/2) sub-tile held in
 //     accumulator registers.
-//   (This is the kernel for small problems; large ones take the streaming kernel of kv_gemm_fold.hip.)
+//   (This is the kernel for small problems on a layer that is not prepared; a prepared one takes the folded product of
+//   kv_gemm_tile.hip or kv_gemm_fold.hip, which needs no vector arithmetic in its main loop.)
 //   * The k loop advances 64 at a time through a double-buffered LDS stage.  Global loads
 //     of step k+1 are in flight while the MFMAs of step k run; one barrier per step.
 //   * LayerNorm is the prologue of the A operand: raw fp16 activations are normalised in
@@ -188,8 +189,9 @@ hipError_t launch_tile(const KvGemmArgs &a, hipStream_t s)
 bool kv_gemm_uses_prepared(int64_t M, int d, int tile, int dtype)
 {
     if (dtype == 1) return true;                           // bf16: one kernel for every problem size
-    // Large problems: 256x256 tiles (highest reuse per LDS byte).  Problems with too few such
-    // tiles to occupy the 256 compute units take 128x128 tiles.
+    // Large problems: 256x256 tiles (highest reuse per LDS byte).  Problems with too few such tiles to occupy the 256
+    // compute units take 128x128 tiles, unless the caller brings a prepared layer (preparing one is a pass over the
+    // weights).
     const int64_t big_tiles = ((M + 255) / 256) * ((2 * (int64_t)d + 255) / 256);
     return (tile ? tile : (big_tiles >= 512 ? 256 : 128)) == 256;
 }
@@ -197,7 +199,12 @@ bool kv_gemm_uses_prepared(int64_t M, int d, int tile, int dtype)
 hipError_t launch_kv_gemm(const KvGemmArgs &a, hipStream_t s)
 {
     if (a.M <= 0) return hipSuccess;
-    if (kv_gemm_uses_prepared(a.M, a.d, a.tile, a.dtype)) {
+    const bool fold = kv_gemm_uses_prepared(a.M, a.d, a.tile, a.dtype);
+    // A prepared layer, and the tile left to the library: the folded product on the tile that suits the problem.  (A
+    // large problem of a caller that keeps compute units free stays with the persistent kernel, and d = 64 has fewer k
+    // blocks than that kernel's pipeline.)
+    if (a.Wp && a.cvec && a.bvec && a.tile == 0 && a.d >= 128 && !(fold && a.cu_limit > 0)) return launch_kv_gemm_prepared(a, s);
+    if (fold) {
         if (!a.Wp || !a.cvec || !a.bvec) return hipErrorInvalidValue;
         return launch_kv_gemm_fold(a, s);                  // LayerNorm folded around the product
     }

@@ -1,0 +1,48 @@
+"""The projection on a prepared layer takes a tile from 32 x 32 to 256 x 256 by the size of the problem; every tile adds
+the same products in the same order as the 256 x 256 kernel (which the parity tests compare with the oracle), so the
+regenerated rows must be the same bits, at tile edges, with rows left over, with one and several output tiles per compute
+unit, with as many k blocks as the load ring has stages and fewer, and every other byte of the caches stays as it was."""
+import pytest
+import torch
+
+from test_gpu_parity import hk  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+# (heads, head_dim, sequences, checkpoint rows of each): comments name the tile that a 256-unit device takes
+SIZES = [
+    (1, 128, 1, 1), (1, 128, 3, 11), (2, 64, 1, 512),             # 32 x 32; 2 k blocks: fewer than the ring's stages
+    (3, 64, 2, 351), (5, 64, 1, 512),                             # 64 x 32
+    (1, 128, 1, 2100), (12, 64, 1, 449), (12, 64, 2, 256),        # 64 x 64
+    (5, 64, 3, 697), (12, 64, 1, 1023),                           # 128 x 64
+    (3, 64, 1, 6001), (12, 128, 1, 701),                          # 128 x 128
+    (12, 128, 1, 1537), (5, 64, 1, 8000), (12, 64, 4, 3001),      # 192 x 128
+    (12, 64, 1, 4100), (32, 128, 5, 193),                         # 256 x 128
+    (72, 128, 1, 5),                                              # 32 x 64
+    (72, 128, 3, 17),                                             # 64 x 128
+    (56, 128, 1, 500),                                            # 256 x 128 or 128 x 256: 224 tiles
+    (12, 64, 1, 6000),                                            # 256 x 256
+]
+
+
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16], ids=["f16", "bf16"])
+@pytest.mark.parametrize("H,dh,B,L", SIZES)
+def test_every_tile_gives_the_same_rows(hk, H, dh, B, L, dtype):
+    d = H * dh
+    gen = torch.Generator(device="cuda").manual_seed(L * 131 + d)
+
+    def draw(*shape, std, mean=0.0):
+        return torch.empty(shape, dtype=dtype, device="cuda").normal_(mean, std, generator=gen)
+
+    layer = (draw(d, std=0.02, mean=1.0), draw(d, std=0.02), draw(2 * d, d, std=0.02), draw(2 * d, std=0.01))
+    prepared = hk.prepare_layer(*layer, H)
+    act = draw(B, L, d, std=1.0, mean=0.25)
+    got = {}
+    for tile in (0, 256):
+        K, V = (torch.full((B, H, L + 5, dh), -7.0, dtype=dtype, device="cuda") for _ in range(2))
+        hk.regen_kv(act, *layer, H, K_out=K, V_out=V, tok_off=3, prepared=prepared, gemm_tile=tile)
+        got[tile] = (K, V)
+    for a, ref in zip(got[0], got[256]):
+        assert torch.equal(a, ref)
+        assert bool((a[:, :, :3] == -7.0).all()) and bool((a[:, :, L + 3:] == -7.0).all())
+        assert bool((a[:, :, 3:L + 3] != -7.0).any())
