@@ -580,7 +580,10 @@ int hk_hybrid_decode_attn_absorbed(const hk_shape *shape, const void *q,
 size_t hk_qkv_workspace_bytes(const hk_shape *shape, int32_t B)
 {
     if (check_shape(shape) != HK_OK || B < 0 || B > (1 << 24)) return 0;
-    return kAlign;                                             // the call is one kernel that needs no scratch; the argument stays
+    // rows go kQkvMaxRows at a time; the same for both dtypes (bf16 takes the three launches wherever fp16 does)
+    const int rows = B < hk::kQkvMaxRows ? B : hk::kQkvMaxRows;
+    if (hk::qkv_stream_takes(rows, shape->d, 1)) return hk::qkv_stream_scratch_bytes(rows, shape->d);
+    return kAlign;                                             // fewer rows than that in a last launch need no more
 }
 
 namespace {
@@ -629,7 +632,7 @@ int qkv_impl(const hk_shape *shape, const void *x_cur, int32_t B,
         return HK_ERR_ALIGN;
     if (K_dst && (!aligned(K_dst, 16) || !aligned(V_dst, 16))) return HK_ERR_ALIGN;
     if (act_dst && !aligned(act_dst, 16)) return HK_ERR_ALIGN;
-    if (workspace_bytes < hk_qkv_workspace_bytes(shape, B)) return HK_ERR_WORKSPACE;
+    if (workspace_bytes < kAlign) return HK_ERR_WORKSPACE;    // less than hk_qkv_workspace_bytes: the one-launch kernel
 
     const int d = shape->d;
     hipStream_t hs = static_cast<hipStream_t>(stream);
@@ -652,6 +655,7 @@ int qkv_impl(const hk_shape *shape, const void *x_cur, int32_t B,
             a.store_mask = store_mask ? store_mask + b0 : nullptr;
             a.max_blocks = paged->max_blocks; a.blk_log2 = blk_log2; a.P_kv = paged->P_kv; a.P_act = paged->P_act;
         }
+        a.scratch = workspace; a.scratch_bytes = workspace_bytes;
         if (hk::launch_qkv_current(a, hs) != hipSuccess) return HK_ERR_LAUNCH;
     }
     return HK_OK;

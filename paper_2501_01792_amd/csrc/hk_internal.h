@@ -107,10 +107,17 @@ struct QkvArgs {
     const int32_t *block_table, *seq_len;
     const int32_t *store_mask;     // paged only, optional [B]: zero = the request's row is not stored (q is still produced)
     int max_blocks, blk_log2, P_kv, P_act;
+    void *scratch;                 // for launch_qkv_stream; with less than that needs, the one-launch kernel runs
+    size_t scratch_bytes;
 };
 constexpr int kQkvMaxRows = 128;       // rows one launch of the skinny kernel takes
 // LayerNorm + Q (and K/V) projection of B <= kQkvMaxRows current-token rows, with write-back.
 hipError_t launch_qkv_current(const QkvArgs &a, hipStream_t s);
+// The form of it in three launches (qkv_stream.hip): whether it is the better one, its scratch, the call.
+constexpr int kQkvStreamCus = 256;     // compute units that its scratch is sized for
+bool qkv_stream_takes(int B, int d, int dtype);
+size_t qkv_stream_scratch_bytes(int B, int d);
+hipError_t launch_qkv_stream(const QkvArgs &a, hipStream_t s);
 
 struct PagedAttnArgs {
     const void *q;                     // [B, H, dh] fp16

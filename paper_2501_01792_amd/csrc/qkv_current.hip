@@ -8,9 +8,11 @@
 //   k, v = xhat [Wk; Wv]^T + [bk; bv]            -> K_dst, V_dst [B, H, L_cap, dh] at token tok_pos
 //
 // With B rows only, this is a skinny GEMM whose cost is one pass over the weights (2 d^2 or 6 d^2
-// bytes): an HBM streaming kernel, one launch (qkv_fused_kernel below).
+// bytes): an HBM streaming kernel, one launch (qkv_fused_kernel below).  Many rows and wide layers take the three launches
+// of qkv_stream.hip instead, if the workspace holds their scratch.
 #include "hk_internal.h"
 #include "elem.h"
+#include "qkv_dst.h"
 #include "skinny_mma.h"
 
 namespace hk {
@@ -20,27 +22,6 @@ using skinny::float16_t;
 
 typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
 typedef float float16_t __attribute__((ext_vector_type(16)));
-
-// Where the current token of a request goes in a paged cache (QkvArgs): its table entry and its row in the block,
-// or row < 0 when the request has no token, the table has no entry for it, or the caller's mask says that the
-// token is not to be stored.
-struct PagedDst {
-    const int32_t *block_table, *seq_len;      // block_table == nullptr: contiguous stores
-    const int32_t *store_mask;                 // optional: zero = the request's token is not stored
-    int max_blocks, blk_log2, P_kv, P_act;
-};
-__device__ __forceinline__ void paged_slot(const PagedDst &p, int b, int32_t &entry, int &row)
-{
-    row = -1;
-    entry = 0;
-    if (p.store_mask && p.store_mask[b] == 0) return;
-    const int t = p.seq_len[b] - 1;
-    if (t < 0) return;
-    const int bi = t >> p.blk_log2;
-    if (bi >= p.max_blocks) return;
-    entry = p.block_table[(int64_t)b * p.max_blocks + bi];
-    row = t & ((1 << p.blk_log2) - 1);
-}
 
 // Everything in one launch.  A workgroup owns 32 NW output features (rows of Wq, or of [Wk; Wv]); its wavefronts form
 // KS groups of NW, every group takes a contiguous part of the reduction axis (the problem has too few output
@@ -389,11 +370,6 @@ __global__ __launch_bounds__(64 * NW * KS) void qkv_fused_kernel(FusedArgs p)
         }
 }
 
-PagedDst paged_dst(const QkvArgs &a)
-{
-    return PagedDst{a.block_table, a.seq_len, a.store_mask, a.max_blocks, a.blk_log2, a.P_kv, a.P_act};
-}
-
 template <int RB, int NW, int KS, int kDepth, int DT>
 hipError_t launch_fused(const QkvArgs &a, hipStream_t s)
 {
@@ -447,6 +423,7 @@ hipError_t launch_qkv_current(const QkvArgs &a, hipStream_t s)
     if (a.B > kQkvMaxRows || a.d % 64 != 0 || a.d < 64) return hipErrorInvalidValue;
     if (a.block_table && (!a.seq_len || a.max_blocks <= 0 || a.blk_log2 < 4 || a.blk_log2 > 10 || a.P_kv < 0 || a.P_act < 0))
         return hipErrorInvalidValue;
+    if (qkv_stream_takes(a.B, a.d, a.dtype) && a.scratch_bytes >= qkv_stream_scratch_bytes(a.B, a.d)) return launch_qkv_stream(a, s);
     return a.dtype == 1 ? launch_dt<1>(a, s) : launch_dt<0>(a, s);
 }
 

@@ -1,0 +1,463 @@
+// QKV generation for the current input tokens (qkv_current.hip), form for more than one block of 32 rows, in three
+// launches:
+//   norm   xhat = LayerNorm(x) [B, d] in the storage type (fp32 statistics, one rounding), and the checkpoint copy
+//   stream parts of xhat [Wq; Wkv]^T, fp32, from a fixed number of persistent workgroups
+//   finish sum of the parts, bias, rounding, store of q and of the K / V rows
+//
+// What bounds it: one pass over the weights (6 d^2 bytes).  The one-launch kernel builds the normalised tile, the two
+// correction sums and the operand layout on the vector ALU and in LDS beside the products, in every workgroup: with 64 to
+// 128 rows that, and not the weights, set its time, and its workgroups (128 features each) left a third of the compute
+// units idle at d = 7168.  Here:
+//   * 128 features x 64 reduction elements of the weights are a unit of work (64 features where d is no multiple of 128).
+//     The units of all feature tiles, in order, are cut into equal runs, one per workgroup, so that every compute unit has
+//     the same work whatever the number of tiles; a run leaves one fp32 part per tile that it meets, and the order in
+//     which parts are added is fixed by the sizes.  The cut is that of Q, K and V also where only Q is asked for: q must
+//     not depend on whether K / V rows are produced.
+//   * Both operands of a unit are one stage of an LDS ring filled by direct loads (16 bytes per lane, 8 lanes per
+//     128-byte line, XOR swizzle on the global side); the ring runs on across tiles, so the loads never drain.
+//   * The weights are asked for non-temporally: xhat (up to 2.4 MB), which every workgroup reads once per tile, stays in
+//     L2 (d = 7168, B = 32: 70 -> 61 us).  64-feature units read xhat twice as often (B = 128: 95 us against 87).
+//   * 4 wavefronts, 2 x 2; fragments double-buffered in registers, one barrier per unit, as in kv_gemm_tile.hip.  One
+//     workgroup with a ring as deep as the LDS allows beat two with half of it each (B = 64: 69 us against 71).
+//   * Non-temporal stores of the parts were slower (B = 64, d = 7168: 74 us): the finishing kernel finds them in cache.
+// Measured, fp16, Q + K + V, new weights in every call, against the one-launch kernel: d = 7168, B = 32 / 64 / 128: 60 / 69 /
+// 87 us (79 / 105 / 110; 308 MB of weights); d = 4096, B = 128: 38 (68); d = 9216, B = 128: 134 (152).  Error against 64
+// bits 2.9e-4 (3.6e-4: two roundings on the way into the product); bf16 2.35e-3 (2.8e-3).
+#include "hk_internal.h"
+#include "elem.h"
+#include "qkv_dst.h"
+
+#include <type_traits>
+
+namespace hk {
+namespace {
+
+typedef __attribute__((address_space(3))) void *lds_ptr_t;
+
+constexpr int kUnitK = 64;                                  // reduction elements of a unit: 128-byte LDS rows
+constexpr int kRowBytes = kUnitK * 2;
+constexpr int kStreamed = 2;                                // cache policy of the weight loads: non-temporal, the rows stay in L2
+constexpr int kMinRun = 4;                                  // fewest units of a run worth a part of its own
+
+// Runs: workgroup w of n takes units [w u / n, (w + 1) u / n).  A tile's parts come from consecutive workgroups; the part
+// of (workgroup w, tile t) is number t + w, so that there are fewer than tiles + n.
+__host__ __device__ inline int run_begin(int w, int units, int n) { return (int)((int64_t)w * units / n); }
+__host__ __device__ inline int run_of(int unit, int units, int n) { return (int)((((int64_t)unit + 1) * n - 1) / units); }
+
+__device__ __forceinline__ float wave_sum(float v)
+{
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
+    return v;
+}
+// Sum over the 256 threads; `buf` holds 4 floats and is used once per call.
+__device__ __forceinline__ float block_sum(float v, float *buf)
+{
+    v = wave_sum(v);
+    if ((threadIdx.x & 63) == 0) buf[threadIdx.x >> 6] = v;
+    __syncthreads();
+    return (buf[0] + buf[1]) + (buf[2] + buf[3]);
+}
+
+// norm: a workgroup per row.  Mean, then centred sum of squares, in fp32; the first kKeep chunks of a thread stay in
+// registers (rows of up to 16384 elements are read once), later ones are read again in each pass.
+constexpr int kKeep = 8;
+template <int DT>
+__global__ __launch_bounds__(256) void qkv_norm_kernel(const typename Elem<DT>::T *__restrict__ x,
+                                                       const typename Elem<DT>::T *__restrict__ gamma,
+                                                       const typename Elem<DT>::T *__restrict__ beta,
+                                                       typename Elem<DT>::T *__restrict__ xhat,
+                                                       typename Elem<DT>::T *__restrict__ act_dst, int64_t act_row_stride,
+                                                       int d, float eps, PagedDst pd)
+{
+    typedef typename Elem<DT>::T elem_t;
+    typedef typename Elem<DT>::V8 vec8_t;
+    __shared__ float buf[2][4];
+    const int m = blockIdx.x, tid = threadIdx.x, nvec = d >> 3;
+    const vec8_t *row = reinterpret_cast<const vec8_t *>(x + (int64_t)m * d);
+    vec8_t *ckpt = nullptr;
+    if (act_dst) {
+        if (pd.block_table) {
+            int32_t entry;
+            int r;
+            paged_slot(pd, m, entry, r);
+            if (r >= 0 && entry < 0 && ~entry < pd.P_act)
+                ckpt = reinterpret_cast<vec8_t *>(act_dst + ((((int64_t)~entry) << pd.blk_log2) + r) * d);
+        } else {
+            ckpt = reinterpret_cast<vec8_t *>(act_dst + (int64_t)m * act_row_stride);
+        }
+    }
+    vec8_t v[kKeep];
+#pragma unroll
+    for (int i = 0; i < kKeep; ++i) {
+        const int c = tid + 256 * i;
+        v[i] = row[c < nvec ? c : nvec - 1];
+    }
+    float s = 0.f;
+    auto add = [&](const vec8_t &e8) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) s += (float)e8[e];
+    };
+#pragma unroll
+    for (int i = 0; i < kKeep; ++i)
+        if (tid + 256 * i < nvec) add(v[i]);
+    for (int c = tid + 256 * kKeep; c < nvec; c += 256) add(row[c]);
+    const float mean = block_sum(s, buf[0]) / (float)d;
+    s = 0.f;
+    auto add_sq = [&](const vec8_t &e8) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) { const float df = (float)e8[e] - mean; s = __builtin_fmaf(df, df, s); }
+    };
+#pragma unroll
+    for (int i = 0; i < kKeep; ++i)
+        if (tid + 256 * i < nvec) add_sq(v[i]);
+    for (int c = tid + 256 * kKeep; c < nvec; c += 256) add_sq(row[c]);
+    const float rstd = 1.0f / __builtin_sqrtf(block_sum(s, buf[1]) / (float)d + eps);
+    vec8_t *out = reinterpret_cast<vec8_t *>(xhat + (int64_t)m * d);
+    auto put = [&](const vec8_t &e8, int c) {
+        const vec8_t g = reinterpret_cast<const vec8_t *>(gamma)[c], b = reinterpret_cast<const vec8_t *>(beta)[c];
+        vec8_t o;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) o[e] = (elem_t)__builtin_fmaf(((float)e8[e] - mean) * rstd, (float)g[e], (float)b[e]);
+        out[c] = o;
+        if (ckpt) ckpt[c] = e8;
+    };
+#pragma unroll
+    for (int i = 0; i < kKeep; ++i)
+        if (tid + 256 * i < nvec) put(v[i], tid + 256 * i);
+    for (int c = tid + 256 * kKeep; c < nvec; c += 256) put(row[c], c);
+}
+
+// Waits until at most r (<= R) of the youngest units this wavefront has asked for, LPS loads each, are in flight (stores
+// of parts count too: the wait is then for more than it needs).
+template <int R, int LPS>
+__device__ __forceinline__ void wait_units(int r)
+{
+    if constexpr (R > 0) {
+        if (r < R) return wait_units<R - 1, LPS>(r);
+    }
+    static_assert(R * LPS <= 63, "vmcnt counts to 63");
+    __builtin_amdgcn_s_waitcnt((R * LPS & 15) | ((R * LPS >> 4) << 14) | 0x0F70);   // vmcnt(R * LPS)
+}
+
+struct StreamArgs {
+    const void *xhat, *Wq, *Wkv;
+    float *part;
+    int B, d, q_tiles, nks, units, runs, live;                 // live: units that are asked for (the first ones)
+};
+
+template <int BM, int BN, int NS>
+constexpr int stream_lds_bytes() { return NS * (BM + BN) * kRowBytes; }
+// Workgroups of a compute unit: two where the LDS of one allows it.
+template <int BM, int BN, int NS>
+constexpr int stream_per_cu() { return stream_lds_bytes<BM, BN, NS>() <= 80 * 1024 ? 2 : 1; }
+
+template <int BM, int BN, int NS, int DT>
+__global__ __launch_bounds__(256, (stream_per_cu<BM, BN, NS>())) void qkv_stream_kernel(StreamArgs p)
+{
+#if defined(__HIP_DEVICE_COMPILE__)                            // (the host pass drops the kernel's stub over a direct load in this body)
+    typedef typename Elem<DT>::T elem_t;
+    typedef typename Elem<DT>::V8 vec8_t;
+    extern __shared__ __align__(16) unsigned char smem[];
+    constexpr int LA = BM / 32, LB = BN / 32, LPS = LA + LB;   // direct loads of a lane per unit
+    constexpr int TM = BM / 32, TN = BN / 32;                  // 16 x 16 MFMA blocks of a wavefront (2 x 2 wavefronts)
+    constexpr int kStage = (BM + BN) * kRowBytes;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave >> 1, wn = wave & 1;
+    const int d = p.d, nks = p.nks;
+    const int u_begin = run_begin((int)blockIdx.x, p.units, p.runs);
+    const int u_end = run_begin((int)blockIdx.x + 1, p.units, p.runs);
+    const int n = (u_end < p.live ? u_end : p.live) - u_begin; // >= 1: no more runs than units, none past the live ones
+
+    // ---- direct loads: load i of wavefront w fills LDS rows 8 (w + 4 i) .. + 7 of an operand; lane l writes row l / 8,
+    // physical chunk l % 8, and fetches logical chunk (l % 8) ^ ((row / 2) % 8), so 8 lanes fetch one 128-byte line
+    const int l_row = 8 * wave + (lane >> 3);
+    const int l_chunk = (lane & 7) ^ ((4 * (wave & 1) + (lane >> 4)) & 7);
+    const __amdgpu_buffer_rsrc_t a_rsrc =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<elem_t *>(static_cast<const elem_t *>(p.xhat)), 0, p.B * d * 2, 0x00020000);
+    int a_voff[LA], b_voff[LB];
+#pragma unroll
+    for (int i = 0; i < LA; ++i) {
+        const int r = l_row + 32 * i;
+        a_voff[i] = ((r < p.B ? r : p.B - 1) * d + l_chunk * 8) * 2;   // rows past the end: the last row, never stored
+    }
+#pragma unroll
+    for (int i = 0; i < LB; ++i) {
+        // LDS row rho: wavefront column rho / (BN/2), MFMA block j, block column c; it holds weight row
+        // (BN/2) (rho / (BN/2)) + TN c + j, so that a lane ends up with TN consecutive features
+        const int rho = l_row + 32 * i, w = rho / (BN / 2), in = rho % (BN / 2);
+        b_voff[i] = ((w * (BN / 2) + TN * (in & 15) + (in >> 4)) * d + l_chunk * 8) * 2;
+    }
+    // the unit to ask for next: its tile's rows and its place on the reduction axis
+    int ask_tile = u_begin / nks, ask_k = u_begin % nks;
+    auto tile_rsrc = [&](int tile) {
+        const elem_t *W = tile < p.q_tiles ? static_cast<const elem_t *>(p.Wq) + (int64_t)tile * BN * d
+                                           : static_cast<const elem_t *>(p.Wkv) + (int64_t)(tile - p.q_tiles) * BN * d;
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<elem_t *>(W), 0, BN * d * 2, 0x00020000);
+    };
+    __amdgpu_buffer_rsrc_t b_rsrc = tile_rsrc(ask_tile);
+    auto issue = [&](int slot, int i) {
+        unsigned char *dst = smem + slot * kStage + wave * 1024;
+        // weights first: they come from HBM, the rows from L2
+        if (i < LB)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(b_rsrc, (lds_ptr_t)(dst + BM * kRowBytes + i * 4096), 16, b_voff[i], ask_k * kRowBytes, 0, kStreamed);
+        else
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, (lds_ptr_t)(dst + (i - LB) * 4096), 16, a_voff[i - LB], ask_k * kRowBytes, 0, 0);
+    };
+    auto asked = [&](bool more) {                              // more: another unit of this run will be asked for
+        if (++ask_k == nks) {
+            ask_k = 0;
+            ++ask_tile;
+            if (more) b_rsrc = tile_rsrc(ask_tile);
+        }
+    };
+
+    // ---- fragment reads: row lane % 16 (+ 16 i) of the wavefront's part, logical chunk 4 ks + lane / 16
+    const int fr = lane & 15, fc = lane >> 4;
+    int frag_off[2];
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) frag_off[ks] = fr * kRowBytes + (((4 * ks + fc) ^ ((fr >> 1) & 7)) << 4);
+    const int a_rd = wm * (BM / 2) * kRowBytes, b_rd = BM * kRowBytes + wn * (BN / 2) * kRowBytes;
+    vec8_t fa[2][TM], fb[2][TN];
+    auto read_frag = [&](int ks, int slot, int which) {        // in the order the MFMAs need them: a[0], b[..], a[1..]
+        const unsigned char *src = smem + slot * kStage + frag_off[ks];
+        if (which == 0 || which > TN) {
+            const int i = which == 0 ? 0 : which - TN;
+            fa[ks][i] = *reinterpret_cast<const vec8_t *>(src + a_rd + i * (16 * kRowBytes));
+        } else {
+            fb[ks][which - 1] = *reinterpret_cast<const vec8_t *>(src + b_rd + (which - 1) * (16 * kRowBytes));
+        }
+    };
+    float4_t acc[TM][TN];
+    auto clear = [&]() {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) acc[i][j] = float4_t{0.f, 0.f, 0.f, 0.f};
+    };
+    clear();
+
+    for (int s = 0; s < NS; ++s) {
+        if (s < n) {
+#pragma unroll
+            for (int i = 0; i < LPS; ++i) issue(s, i);
+            asked(s + 1 < n);
+        }
+    }
+    wait_units<NS - 1, LPS>(n < NS ? n - 1 : NS - 1);
+    asm volatile("s_barrier" ::: "memory");
+#pragma unroll
+    for (int q = 0; q < TM + TN; ++q) read_frag(0, 0, q);
+
+    constexpr int kMma = TM * TN, kFrags = TM + TN;
+    constexpr int kSlotsA = kMma > kFrags ? kMma : kFrags;
+    constexpr int kSlotsB = kSlotsA > LPS ? kSlotsA : LPS;
+    int cur = 0, tile = u_begin / nks, k = u_begin % nks;
+    // One unit (kind 0: the run's last; 1: a next one exists; 2: and unit i + NS exists).  Its first half multiplies
+    // fragments that are in registers already and reads those of the second half; then this wavefront waits for its loads
+    // of unit i + 1 and meets the others, after which that unit is complete in LDS and the slot of unit i (every read of
+    // it has come back) takes unit i + NS; the second half reads the first fragments of unit i + 1.
+    auto unit = [&](auto kind, int i) {
+        constexpr int KIND = decltype(kind)::value;
+        const int nxt = cur + 1 == NS ? 0 : cur + 1;
+#pragma unroll
+        for (int q = 0; q < kSlotsA; ++q) {
+            if (q < kMma) acc[q / TN][q % TN] = Elem<DT>::mfma_16x16x32(fa[0][q / TN], fb[0][q % TN], acc[q / TN][q % TN]);
+            if (q < kFrags) read_frag(1, cur, q);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if constexpr (KIND == 2) wait_units<NS - 2, LPS>(NS - 2);
+        if constexpr (KIND == 1) wait_units<NS - 2, LPS>(n - 2 - i);
+        if constexpr (KIND > 0) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < kSlotsB; ++q) {
+            if (q < kMma) acc[q / TN][q % TN] = Elem<DT>::mfma_16x16x32(fa[1][q / TN], fb[1][q % TN], acc[q / TN][q % TN]);
+            if (KIND > 0 && q < kFrags) read_frag(0, nxt, q);
+            if (KIND == 2 && q < LPS) issue(cur, q);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if constexpr (KIND == 2) asked(i + NS + 1 < n);
+        cur = nxt;
+        if (++k == nks || KIND == 0) {                         // the tile ends here for this run: its part leaves
+            float4_t *dst = reinterpret_cast<float4_t *>(p.part + (int64_t)(tile + (int)blockIdx.x) * (BM * BN));
+#pragma unroll
+            for (int ii = 0; ii < TM; ++ii)
+#pragma unroll
+                for (int j = 0; j < TN; ++j) dst[(ii * TN + j) * 256 + tid] = acc[ii][j];
+            clear();
+            k = 0;
+            ++tile;
+        }
+    };
+    int i = 0;
+    for (; i + NS < n; ++i) unit(std::integral_constant<int, 2>{}, i);
+    for (; i + 1 < n; ++i) unit(std::integral_constant<int, 1>{}, i);
+    unit(std::integral_constant<int, 0>{}, i);
+#endif
+}
+
+// finish: a workgroup per (tile, 16-row blocks i of the wavefront rows); thread for thread the layout of the parts.
+struct FinishArgs {
+    const float *part;
+    const void *bq, *bkv;
+    void *q_out, *K_dst, *V_dst;
+    int B, d, n_heads, head_dim, L_cap, tok_pos, q_tiles, nks, units, runs;
+    PagedDst pd;
+};
+
+template <int BM, int BN, int DT>
+__global__ __launch_bounds__(256) void qkv_finish_kernel(FinishArgs p)
+{
+    typedef typename Elem<DT>::T elem_t;
+    typedef elem_t out_t __attribute__((ext_vector_type(BN / 32)));
+    constexpr int TN = BN / 32;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tile = blockIdx.x, i = blockIdx.y;
+    const int m0 = (wave >> 1) * (BM / 2) + 16 * i + 4 * (lane >> 4);       // first of this thread's 4 rows
+    if (m0 >= p.B) return;                                                  // no barrier in this kernel
+    const int w0 = run_of(tile * p.nks, p.units, p.runs), w1 = run_of(tile * p.nks + p.nks - 1, p.units, p.runs);
+    const float4_t *src = reinterpret_cast<const float4_t *>(p.part + (int64_t)(tile + w0) * (BM * BN)) + i * TN * 256 + tid;
+    float4_t sum[TN];
+#pragma unroll
+    for (int j = 0; j < TN; ++j) sum[j] = src[256 * j];
+    for (int w = w0 + 1; w <= w1; ++w) {
+        src += BM * BN / 4;
+#pragma unroll
+        for (int j = 0; j < TN; ++j) sum[j] += src[256 * j];
+    }
+    const bool is_q = tile < p.q_tiles;
+    const int n = (is_q ? tile : tile - p.q_tiles) * BN + (BN / 2) * (wave & 1) + TN * (lane & 15);   // first of TN features
+    const out_t bias = *reinterpret_cast<const out_t *>(static_cast<const elem_t *>(is_q ? p.bq : p.bkv) + n);
+    const int f = n < p.d ? n : n - p.d;
+    const int h = f / p.head_dim, e = f % p.head_dim;
+    const int head_stride = p.pd.block_table ? (p.head_dim << p.pd.blk_log2) : p.L_cap * p.head_dim;
+    elem_t *dst = is_q ? static_cast<elem_t *>(p.q_out) + n
+                       : static_cast<elem_t *>(n < p.d ? p.K_dst : p.V_dst) + (int64_t)h * head_stride + e;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int m = m0 + r;
+        if (m >= p.B) break;
+        int64_t base = -1;                                                  // or the row is not stored
+        if (is_q) {
+            base = (int64_t)m * p.d;
+        } else if (p.pd.block_table) {
+            int32_t entry;
+            int row;
+            paged_slot(p.pd, m, entry, row);
+            if (row >= 0 && entry >= 0 && entry < p.pd.P_kv) base = ((((int64_t)entry * p.n_heads) << p.pd.blk_log2) + row) * p.head_dim;
+        } else {
+            base = ((int64_t)m * p.n_heads * p.L_cap + p.tok_pos) * p.head_dim;
+        }
+        if (base >= 0) {
+            out_t o;
+#pragma unroll
+            for (int j = 0; j < TN; ++j) o[j] = (elem_t)(sum[j][r] + (float)bias[j]);
+            *reinterpret_cast<out_t *>(dst + base) = o;
+        }
+    }
+}
+
+size_t align256(size_t n) { return (n + 255) / 256 * 256; }
+
+int stream_runs(int units, int workgroups)
+{
+    const int most = units / kMinRun > 0 ? units / kMinRun : 1;
+    return workgroups < most ? workgroups : most;
+}
+
+template <int BM, int BN, int NS, int DT>
+hipError_t launch_dt(const QkvArgs &a, int cus, hipStream_t s)
+{
+    typedef typename Elem<DT>::T elem_t;
+    const PagedDst pd = paged_dst(a);
+    elem_t *xhat = static_cast<elem_t *>(a.scratch);
+    float *part = reinterpret_cast<float *>(static_cast<char *>(a.scratch) + align256((size_t)a.B * a.d * 2));
+    hipLaunchKernelGGL(qkv_norm_kernel<DT>, dim3((unsigned)a.B), dim3(256), 0, s, static_cast<const elem_t *>(a.x),
+                       static_cast<const elem_t *>(a.ln_w), static_cast<const elem_t *>(a.ln_b), xhat,
+                       static_cast<elem_t *>(a.act_dst), a.act_row_stride, a.d, a.eps, pd);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    StreamArgs t;
+    t.xhat = xhat; t.Wq = a.Wq; t.Wkv = a.Wkv; t.part = part;
+    t.B = a.B; t.d = a.d; t.q_tiles = a.d / BN; t.nks = a.d / kUnitK;
+    const int tiles = a.K_dst ? 3 * t.q_tiles : t.q_tiles;
+    t.units = 3 * t.q_tiles * t.nks;
+    t.live = tiles * t.nks;
+    t.runs = stream_runs(t.units, stream_per_cu<BM, BN, NS>() * cus);
+    auto kern = qkv_stream_kernel<BM, BN, NS, DT>;
+    constexpr int lds = stream_lds_bytes<BM, BN, NS>();
+    static_assert(lds <= 160 * 1024, "the workgroup must fit the LDS of a compute unit");
+    static LdsOnce lds_once;
+    e = allow_dynamic_lds(reinterpret_cast<const void *>(kern), lds, lds_once);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(run_of(t.live - 1, t.units, t.runs) + 1)), dim3(256), lds, s, t);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    FinishArgs f;
+    f.part = part; f.bq = a.bq; f.bkv = a.bkv; f.q_out = a.q_out; f.K_dst = a.K_dst; f.V_dst = a.V_dst;
+    f.B = a.B; f.d = a.d; f.n_heads = a.n_heads; f.head_dim = a.head_dim; f.L_cap = a.L_cap; f.tok_pos = a.tok_pos;
+    f.q_tiles = t.q_tiles; f.nks = t.nks; f.units = t.units; f.runs = t.runs; f.pd = pd;
+    hipLaunchKernelGGL((qkv_finish_kernel<BM, BN, DT>), dim3((unsigned)tiles, BM / 32), dim3(256), 0, s, f);
+    return hipGetLastError();
+}
+
+template <int BM, int BN, int NS>
+hipError_t launch_any(const QkvArgs &a, int cus, hipStream_t s)
+{
+    return a.dtype == 1 ? launch_dt<BM, BN, NS, 1>(a, cus, s) : launch_dt<BM, BN, NS, 0>(a, cus, s);
+}
+
+}  // namespace
+
+// Where the lines lie (measured, fp16 / bf16, one-launch kernel against this one, us): three launches cost 17 us however
+// small the layer, so wide layers and many rows come here.
+//   more than 64 rows: d = 768: 19.3 / 22.4 against 18.5 (B = 80 / 96); every wider layer gains, 4096: 55 / 68 against 35
+//   33 to 64 rows: d = 1280, B = 40: 17.3 against 19; 2048: 20.7 against 18.6.  fp16 up to 8192 (B = 64: 95 against 93): beyond it the
+//     one-launch kernel with its workgroups of 128 features keeps up; 9216, B = 64: 103 against 108 (bf16: 119
+//     against 110)
+//   up to 32 rows: while the one-launch kernel's workgroups (64 features) fit 256 units at once it is the faster one: d =
+//     5120, B = 32: 36 against 36, B = 8: 32 against 34; 6144: 62 to 70 against 47 to 49; 9216, B = 32: 103 against 92
+// Wider layers than 9216 were not measured and stay with one launch.
+bool qkv_stream_takes(int B, int d, int dtype)
+{
+    if (B <= 0 || B > kQkvMaxRows || d % kUnitK != 0 || d > 9216) return false;
+    if (B > 64) return d >= 768;
+    if (B > 32) return d >= 2048 && (dtype == 1 || d <= 8192);
+    return 3 * (d / 64) > 256;
+}
+
+// Scratch of one launch of B rows: xhat and the parts (fewer than tiles + runs of them).  The number of runs follows the
+// device; the bound is for kQkvStreamCus compute units, and a device with more gets as many runs as for that number.
+size_t qkv_stream_scratch_bytes(int B, int d)
+{
+    const size_t rows = (B + 31) / 32 * 32;
+    const size_t parts = d % 128 == 0 ? (size_t)(3 * (d / 128) + kQkvStreamCus) * 128 : (size_t)(3 * (d / 64) + 2 * kQkvStreamCus) * 64;
+    return align256((size_t)B * d * 2) + rows * parts * 4;
+}
+
+hipError_t launch_qkv_stream(const QkvArgs &a, hipStream_t s)
+{
+    if (a.B <= 0 || a.B > kQkvMaxRows || a.d % kUnitK != 0 || a.d > 9216 ||
+        a.scratch_bytes < qkv_stream_scratch_bytes(a.B, a.d)) return hipErrorInvalidValue;
+    int dev = 0, cus = 0;
+    const hipError_t e = current_device_cus(&dev, &cus);
+    if (e != hipSuccess) return e;
+    if (cus > kQkvStreamCus) cus = kQkvStreamCus;
+    if (a.d % 128 != 0) {
+        switch ((a.B + 31) / 32) {
+        case 1: return launch_any<32, 64, 6>(a, cus, s);
+        case 2: return launch_any<64, 64, 5>(a, cus, s);
+        case 3: return launch_any<96, 64, 4>(a, cus, s);
+        default: return launch_any<128, 64, 3>(a, cus, s);
+        }
+    }
+    switch ((a.B + 31) / 32) {
+    case 1: return launch_any<32, 128, 7>(a, cus, s);
+    case 2: return launch_any<64, 128, 6>(a, cus, s);
+    case 3: return launch_any<96, 128, 5>(a, cus, s);
+    default: return launch_any<128, 128, 4>(a, cus, s);
+    }
+}
+
+}  // namespace hk
