@@ -413,9 +413,9 @@ hipError_t launch_any(const QkvArgs &a, int cus, hipStream_t s)
 // Where the lines lie (measured, fp16 / bf16, one-launch kernel against this one, us): three launches cost 17 us however
 // small the layer, so wide layers and many rows come here.
 //   more than 64 rows: d = 768: 19.3 / 22.4 against 18.5 (B = 80 / 96); every wider layer gains, 4096: 55 / 68 against 35
-//   33 to 64 rows: d = 1280, B = 40: 17.3 against 19; 2048: 20.7 against 18.6.  fp16 up to 8192 (B = 64: 95 against 93): beyond it the
-//     one-launch kernel with its workgroups of 128 features keeps up; 9216, B = 64: 103 against 108 (bf16: 119
-//     against 110)
+//   33 to 64 rows: d = 1280, B = 40: 17.3 against 19; 2048: 20.7 against 18.6; 4096, B = 64: 36 / 43 against 32.  fp16 up
+//     to 8192 (B = 64: 95 against 93), beyond which the one-launch kernel's workgroups of 128 features keep up (9216, B =
+//     64: 103 against 108; bf16: 119 against 110)
 //   up to 32 rows: while the one-launch kernel's workgroups (64 features) fit 256 units at once it is the faster one: d =
 //     5120, B = 32: 36 against 36, B = 8: 32 against 34; 6144: 62 to 70 against 47 to 49; 9216, B = 32: 103 against 92
 // Wider layers than 9216 were not measured and stay with one launch.
