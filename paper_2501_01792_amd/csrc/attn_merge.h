@@ -59,7 +59,13 @@ __device__ __forceinline__ void merge_run(const float *__restrict__ src, int n, 
         float mx = m;
 #pragma unroll
         for (int j = 0; j < kBatch; ++j) {
-            if (i0 + j >= i_end) mm[j] = -INFINITY;                             // weight 2^-inf = 0
+            if (i0 + j >= i_end) {
+                // neutral: weight 2^-inf = 0, and nothing for it to meet (the slot read in its place may hold an infinity)
+                mm[j] = -INFINITY;
+                ll[j] = 0.f;
+#pragma unroll
+                for (int e = 0; e < E; ++e) oo[j][e] = 0.f;
+            }
             mx = fmaxf(mx, mm[j]);
         }
         const float a = __builtin_amdgcn_exp2f(m - mx);

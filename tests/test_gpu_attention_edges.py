@@ -69,3 +69,53 @@ def test_paged_attention_at_step_edges(hk, lens, bt, dtype):
     ref = pgo.paged_decode_attn(qh, Kh, Vh, paged["act_pool"], paged["block_table"], paged["seq_len"], bt, z, z,
                                 np.zeros((2 * cfg.d, cfg.d), np.float16), np.zeros(2 * cfg.d, np.float16), H)
     _check("out", out, ref, dtype)
+
+
+def _with_and_without_an_infinity(call, V, at):
+    """call() with V as it is and with V[at] = inf (one element of one token of every pair)."""
+    out = call().clone()
+    V[at] = float("inf")
+    return out, call()
+
+
+def _only_infinite_at(out, ref, e):
+    """The weight of every token is positive here, so the element is infinite; the others do not know of it."""
+    assert bool((out[..., e] == float("inf")).all()), "%d NaN" % int(out[..., e].isnan().sum())
+    keep = [i for i in range(out.shape[-1]) if i != e]
+    assert torch.equal(out[..., keep], ref[..., keep])
+
+
+# one partial per pair (which no batch of the merge is), several, many; whole steps of 64 tokens
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("dh,H,L,t", [(128, 3, 64, 0), (64, 2, 64, 63), (128, 2, 128, 100), (128, 4, 640, 600), (128, 1, 1280, 1279)])
+def test_an_infinite_value_stays_infinite_in_the_merge(hk, dh, H, L, t, dtype):
+    rng = np.random.default_rng(L + t)
+    q, K, V = (_to_gpu(rng.standard_normal(s), dtype)[0] for s in ((2, H, dh), (2, H, L, dh), (2, H, L, dh)))
+    z = torch.zeros(16, dtype=q.dtype, device="cuda")                   # layer parameters: nothing is regenerated
+    ref, out = _with_and_without_an_infinity(lambda: hk.hybrid_decode_attn(q, K, V, None, (z, z, z, z), 1.0), V, (..., t, 5))
+    _only_infinite_at(out, ref, 5)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("lens,block,row", [([64, 128], 3, 15), ([640, 64], 5, 0), ([64], 0, 7)], ids=str)
+def test_an_infinite_value_stays_infinite_in_the_paged_merge(hk, lens, block, row, dtype):
+    _paged_infinity(hk, lens, block, row, dtype)
+
+
+def _paged_infinity(hk, lens, block, row, dtype, H=3, dh=128, bt=16):
+    """V infinite in one row of one block of request 0; blocks lie in the pool in reverse order."""
+    rng = np.random.default_rng(sum(lens))
+    counts = [(n + bt - 1) // bt for n in lens]
+    pool, table, at = sum(counts), np.zeros((len(lens), max(counts)), np.int32), 0
+    for r, c in enumerate(counts):
+        table[r, :c] = pool - 1 - np.arange(at, at + c)
+        at += c
+    q, K, V = (_to_gpu(rng.standard_normal(s), dtype)[0] for s in ((len(lens), H, dh), (pool, H, bt, dh), (pool, H, bt, dh)))
+    tab, sl = _gpu(table), _gpu(np.asarray(lens, np.int32))
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    cud = _gpu(cu)
+    ref, out = _with_and_without_an_infinity(
+        lambda: hk.paged_decode_attn(q, K, V, None, tab, sl, bt, None, n_act_used=0, cu_tokens=cud, total_tokens=int(cu[-1])),
+        V, (int(table[0, block]), slice(None), row, 5))
+    _only_infinite_at(out[:1], ref[:1], 5)
+    assert torch.equal(out[1:], ref[1:])
