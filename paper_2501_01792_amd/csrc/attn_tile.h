@@ -13,8 +13,11 @@
 //     ownership is the same; a weight is spread over its group by a row broadcast.  Through the LDS permute network
 //     (35 per step) they were a chain of LDS latencies.
 //   * Online softmax per lane group in the log2 domain with a finite "-infinity".
+//   * A step of fewer than 64 tokens reads zeros in the place of the missing rows (the bound of the buffer descriptor): a
+//     repeated real row, masked by a weight of zero, would make 0 * inf = NaN of an infinite V element.
 #pragma once
 #include <hip/hip_runtime.h>
+#include <stdint.h>
 
 #include "attn_merge.h"
 #include "elem.h"
@@ -55,6 +58,24 @@ __device__ __forceinline__ float dot8(typename Elem<DT>::V8 a, typename Elem<DT>
         s = Elem<DT>::dot2(x, y, s);
     }
     return s;
+}
+
+// Rows of one operand that lie in a row: `base` is the first, `rows` (0 .. 64) of them exist.  Both are wavefront-uniform;
+// where the compiler cannot prove it, it would loop over the lanes' descriptors, so it is said.
+template <typename elem_t>
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t step_rows(const elem_t *base, int rows, int row_elems)
+{
+    const uint64_t at = reinterpret_cast<uintptr_t>(base);
+    const uint64_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)at);
+    const uint64_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(at >> 32));
+    return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<elem_t *>(hi << 32 | lo), 0,
+                                             __builtin_amdgcn_readfirstlane(rows) * row_elems * (int)sizeof(elem_t), 0x00020000);
+}
+// Load i of them: 64 lanes x 16 bytes, whole rows, non-temporal.
+template <typename vec8_t>
+__device__ __forceinline__ vec8_t step_load(__amdgpu_buffer_rsrc_t rows, int i, int lane)
+{
+    return __builtin_bit_cast(vec8_t, __builtin_amdgcn_raw_buffer_load_b128(rows, lane * 16 + i * 1024, 0, 2));
 }
 
 template <int DH, int DT>

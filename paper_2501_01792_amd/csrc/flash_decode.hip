@@ -82,18 +82,13 @@ __global__ __launch_bounds__(kThreads, 3) void flash_decode_kernel(
 
             for (int tb = t_begin; tb < t_end; tb += kTile) {
                 half8_t kr[NL], vr[NL];
-                // row of load i: the step's first row (scalar) plus a 32-bit lane offset; rows past the end re-read the
-                // last one and are masked
-                const elem_t *Kt = Kp + (int64_t)tb * DH, *Vt = Vp + (int64_t)tb * DH;
-                const int rows = t_end - tb;
-                auto lane_off = [&](int i) {
-                    const int r = i * RPL + g;
-                    return (uint32_t)((r < rows ? r : rows - 1) * DH + c * 8);
-                };
+                const int rows = t_end - tb < kTile ? t_end - tb : kTile;
+                const __amdgpu_buffer_rsrc_t Kt = attn::step_rows(Kp + (int64_t)tb * DH, rows, DH);
+                const __amdgpu_buffer_rsrc_t Vt = attn::step_rows(Vp + (int64_t)tb * DH, rows, DH);
 #pragma unroll
-                for (int i = 0; i < NL; ++i) kr[i] = __builtin_nontemporal_load(reinterpret_cast<const half8_t *>(Kt + lane_off(i)));
+                for (int i = 0; i < NL; ++i) kr[i] = attn::step_load<half8_t>(Kt, i, lane);
 #pragma unroll
-                for (int i = 0; i < NL; ++i) vr[i] = __builtin_nontemporal_load(reinterpret_cast<const half8_t *>(Vt + lane_off(i)));
+                for (int i = 0; i < NL; ++i) vr[i] = attn::step_load<half8_t>(Vt, i, lane);
                 __builtin_amdgcn_sched_barrier(0);                 // every load of the step is on its way before the first use
                 tile.consume(qv, kr, vr, lane, tb + c * RPL + g < t_end, scale_log2e);
             }

@@ -9,9 +9,8 @@
 // (request, head) pairs form one line, pair-major, of H * sum(len) positions; it is cut into W equal
 // ranges, one per resident wavefront; a wavefront emits one partial per pair it touches at index
 // (wavefront + pair); a second kernel merges each pair's run of partials.  What differs is the address
-// of a token: the block table is read with scalar loads (one entry per load instruction's group of
-// rows, which never straddles a block), and steps are aligned to 64 tokens inside a pair so that the
-// rows of one load instruction share a block.  The table entries of a step are fetched during the step before.
+// of a token: the block table is read with scalar loads, one entry for every 16 tokens of a step (steps are
+// aligned to 64 tokens inside a pair, so that 16 tokens never straddle a block), during the step before.
 // Measured (kernel alone, 16-token blocks in random order): 403 MB of 32 ragged requests in 69 us (92 before ranges
 // were moved to whole steps and the entries fetched ahead), 3.6 GB in 564 us (592).
 #include "hk_internal.h"
@@ -95,58 +94,43 @@ __global__ __launch_bounds__(kThreads, 3) void paged_decode_kernel(
         tile_t tile;
         tile.clear();
 
-        // table entries of a step: a 64-token step meets at most four blocks (block_tokens >= 16)
+        // table entries of a step: one for every 16 of its tokens, which never straddle a block (block_tokens >= 16)
         auto entries_of = [&](int tb, int32_t (&e)[4]) {
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                int bi = (tb >> blk_log2) + j;
-                bi = bi < last_block ? bi : last_block;
-                e[j] = tab[bi];
+                const int bi = (tb + 16 * j) >> blk_log2;
+                e[j] = tab[bi < last_block ? bi : last_block];
             }
         };
         int32_t ent[4] = {0, 0, 0, 0};
         if (t_first < t_last) entries_of(t_first, ent);
         for (int tb = t_first; tb < t_last; tb += kTile) {
             half8_t kr[NL], vr[NL];
-            // Address of the rows of load group i: a wavefront-uniform block base (scalar registers) plus a
-            // 32-bit lane offset.  Rows tb + i RPL .. + RPL - 1 lie in one block (block_tokens is a multiple of
-            // RPL).  Groups past the last token are redirected to the last token's block and row, and masked.
-            const elem_t *kb[4], *vb[4];
+            const int rows = t_last - tb < kTile ? t_last - tb : kTile;
+            __amdgpu_buffer_rsrc_t kb[4], vb[4];                   // 16 tokens each
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                int bi = (tb >> blk_log2) + j;
-                bi = bi < last_block ? bi : last_block;
                 const int32_t e = __builtin_amdgcn_readfirstlane(ent[j]);
                 bool is_act = e < 0;
                 int pb = is_act ? ~e : e;
                 if ((is_act ? P_act : P_kv) <= 0) { is_act = !is_act; pb = 0; }   // a corrupt table cannot leave
                 const int P = is_act ? P_act : P_kv;                              // the pools (one is not empty)
                 pb = pb < P ? pb : P - 1;
-                const int64_t at = (int64_t)pb * blk_elems + (int64_t)h * (blk * DH) - (int64_t)(bi << blk_log2) * DH;   // + t * DH
-                kb[j] = (is_act ? K_regen : K_pool) + at;
-                vb[j] = (is_act ? V_regen : V_pool) + at;
+                const int64_t at = (int64_t)pb * blk_elems + (int64_t)(h * blk + ((tb + 16 * j) & (blk - 1))) * DH;
+                const int here = rows - 16 * j;
+                const int n = here < 0 ? 0 : here < 16 ? here : 16;
+                kb[j] = attn::step_rows((is_act ? K_regen : K_pool) + at, n, DH);
+                vb[j] = attn::step_rows((is_act ? V_regen : V_pool) + at, n, DH);
             }
-            auto lane_off = [&](int i) {
-                int t = tb + i * RPL + g;
-                t = t < t_last ? t : t_last - 1;
-                return (uint32_t)(t * DH + c * 8);
-            };
+            constexpr int kPer = 16 / RPL;                         // loads of 16 tokens
 #pragma unroll
-            for (int i = 0; i < NL; ++i) {
-                const int j = (i * RPL) >> blk_log2;               // 0..3, wavefront-uniform
-                const elem_t *b = j == 0 ? kb[0] : j == 1 ? kb[1] : j == 2 ? kb[2] : kb[3];
-                kr[i] = __builtin_nontemporal_load(reinterpret_cast<const half8_t *>(b + lane_off(i)));
-            }
+            for (int i = 0; i < NL; ++i) kr[i] = attn::step_load<half8_t>(kb[i / kPer], i % kPer, lane);
 #pragma unroll
-            for (int i = 0; i < NL; ++i) {
-                const int j = (i * RPL) >> blk_log2;
-                const elem_t *b = j == 0 ? vb[0] : j == 1 ? vb[1] : j == 2 ? vb[2] : vb[3];
-                vr[i] = __builtin_nontemporal_load(reinterpret_cast<const half8_t *>(b + lane_off(i)));
-            }
+            for (int i = 0; i < NL; ++i) vr[i] = attn::step_load<half8_t>(vb[i / kPer], i % kPer, lane);
             // the next step's entries (scalar loads) are on their way while this step's rows arrive
             if (tb + kTile < t_last) entries_of(tb + kTile, ent);
             __builtin_amdgcn_sched_barrier(0);                     // every load of the step is on its way before the first use
-            tile.consume(qv, kr, vr, lane, tb + c * RPL + g < t_last, scale_log2e);
+            tile.consume(qv, kr, vr, lane, c * RPL + g < rows, scale_log2e);
         }
         tile.store(partial + ((int64_t)w + pair) * (DH + 2), lane);
         p = base + (int64_t)h * len + t_end;

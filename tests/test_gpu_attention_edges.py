@@ -119,3 +119,21 @@ def _paged_infinity(hk, lens, block, row, dtype, H=3, dh=128, bt=16):
         V, (int(table[0, block]), slice(None), row, 5))
     _only_infinite_at(out[:1], ref[:1], 5)
     assert torch.equal(out[1:], ref[1:])
+
+
+# steps of fewer than 64 tokens, whose missing rows are read from the last one of the range
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("dh,H,L,t", [(128, 3, 1, 0), (64, 2, 65, 64), (128, 32, 1999, 1998), (128, 32, 1999, 61), (64, 5, 700, 63),
+                                      (128, 3, 127, 63)])
+def test_an_infinite_value_stays_infinite_beside_masked_rows(hk, dh, H, L, t, dtype):
+    rng = np.random.default_rng(L + t)
+    q, K, V = (_to_gpu(rng.standard_normal(s), dtype)[0] for s in ((1, H, dh), (1, H, L, dh), (1, H, L, dh)))
+    z = torch.zeros(16, dtype=q.dtype, device="cuda")
+    ref, out = _with_and_without_an_infinity(lambda: hk.hybrid_decode_attn(q, K, V, None, (z, z, z, z), 1.0), V, (..., t, 5))
+    _only_infinite_at(out, ref, 5)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("lens,block,row", [([65, 64], 4, 0), ([1], 0, 0), ([700, 3], 43, 11)], ids=str)
+def test_an_infinite_value_stays_infinite_beside_masked_rows_paged(hk, lens, block, row, dtype):
+    _paged_infinity(hk, lens, block, row, dtype)
