@@ -113,7 +113,8 @@ size_t hk_regen_workspace_bytes(const hk_shape *shape, int32_t B, int32_t L_act)
  *     W'[n, k] = ln_w[k] * Wkv[n, k],  c[n] = sum_k W'[n, k],  b'[n] = bkv[n] + sum_k ln_b[k] * Wkv[n, k],
  * which lets the raw checkpoint rows feed the matrix cores while the row
  * statistics are applied to the accumulators.  hk_prepare_layer computes W'
- * (fp16), c and b' (fp32) into `prepared` (device, 256-byte aligned, at least
+ * (fp16; times a power of two when every |ln_w| is below 0.5, so that a small
+ * ln_w costs no precision), c and b' (fp32) into `prepared` (device, 256-byte aligned, at least
  * hk_prepared_bytes(shape) bytes, owned by the caller, valid as long as it is
  * referenced from hk_layer_params.prepared).  With gemm_tile = 0, regenerations
  * of every size run on this form when the caller brings it.  Without it, a large

@@ -375,7 +375,8 @@ __global__ __launch_bounds__(256) void absorbed_scores_block_kernel(const _Float
 }
 
 // softmax over the checkpoint rows of one (sequence, head), one wavefront each.  In the log2 domain:
-//   s_t = sl (rstd_t raw_t + k_t c1 + c2),  k_t = -(mean_t - x_t[0]) rstd_t,  c1 = q . c_K,h,  c2 = q . b'_K,h,
+//   s_t = sl (rstd_t f raw_t + k_t c1 + c2),  k_t = -(mean_t - x_t[0]) rstd_t,  c1 = q . c_K,h,  c2 = q . b'_K,h,
+//   f the factor of the prepared layer's scaled weights,
 //   sl = scale log2(e);   w_t = fp16(2^(s_t - m) rstd_t / l), zero from L_act to the next multiple of 64;
 //   sums = (m, l, sum_t w_t mean_t with the stored w_t, -)
 template <int DT>
@@ -406,7 +407,8 @@ __global__ __launch_bounds__(256) void absorbed_softmax_kernel(const _Float16 *_
     // is issued, and the kernel then pays one memory latency per row and lane.
     const int t_last = L_act > 0 ? L_act - 1 : 0;          // row 0 of the scratch rows is readable even without rows
     constexpr int kBatch = 8;
-    auto score_of = [&](const float4 &s4, float rv) { return sl * (__builtin_fmaf(s4.x, rv, __builtin_fmaf(s4.z, c1, c2))); };
+    const float wscale = bvec[2 * H * head_dim];           // of the scaled weights that U was formed with
+    auto score_of = [&](const float4 &s4, float rv) { return sl * (__builtin_fmaf(s4.x, rv * wscale, __builtin_fmaf(s4.z, c1, c2))); };
     // The first 64 kKeep rows stay in registers (score, rstd, mean), so that up to that many rows are read once
     // (the statistics of a row are shared by all heads: re-reading them per pass made this kernel L2-bound);
     // rows beyond are read again in each of the three passes.  (Keeping 64 scores per lane and re-reading the
@@ -515,7 +517,7 @@ __global__ __launch_bounds__(256) void absorbed_project_kernel(const _Float16 *_
         const int64_t bh = (int64_t)b * H + h;
         const float4 sa = sums[bh];
         float o = (red[0][b][c] + red[1][b][c]) + (red[2][b][c] + red[3][b][c]);
-        o += bv[n];
+        o = __builtin_fmaf(o, bv[d], bv[n]);               // bv[d]: the factor of the scaled weights
         // join of the two segments; a segment without tokens has denominator 0 and drops out, both empty: zero
         float m = sa.x, wc = 0.f, oc = 0.f;
         if (lse_c) {
@@ -596,7 +598,7 @@ __global__ __launch_bounds__(256) void absorbed_join_kernel(const float *__restr
     half4_t res;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        const float oa = o[j] + bv[n + j];
+        const float oa = __builtin_fmaf(o[j], bv[d], bv[n + j]);
         const float ocj = skinny::stored_to_float<DT>(reinterpret_cast<const _Float16 *>(&oc) + j);
         skinny::float_to_stored<DT>(reinterpret_cast<_Float16 *>(&res) + j, wc + wa > 0.f ? (wc * ocj + wa * oa) / (wc + wa) : 0.f);
     }

@@ -86,14 +86,15 @@ int check_params(const hk_layer_params *lp)
     return HK_OK;
 }
 
-// Layout of a prepared layer: W' [2d, d] fp16, then c [2d] fp32, then b' [2d] fp32, each 256-byte aligned.
+// Layout of a prepared layer: W' [2d, d] fp16 (times a power of two), then c [2d] fp32, then b' [2d] fp32, each 256-byte
+// aligned, then the factor fp32 that takes the power of two back (right behind b': 2d floats are a multiple of 256 bytes).
 PreparedLayout prepared_layout(int d)
 {
     PreparedLayout L;
     L.off_w = 0;
     L.off_c = align_up((size_t)2 * d * d * 2);
     L.off_b = L.off_c + align_up((size_t)2 * d * sizeof(float));
-    L.total = L.off_b + align_up((size_t)2 * d * sizeof(float));
+    L.total = L.off_b + align_up((size_t)2 * d * sizeof(float) + sizeof(float));
     return L;
 }
 
@@ -120,8 +121,6 @@ int regen_impl(const hk_shape *s, const void *act, int64_t L_act, const hk_layer
             return HK_ERR_LAUNCH;
         prepared = prep_scratch;
     }
-    if (hk::launch_ln_stats(act, stats, M, s->d, s->ln_eps, stream, s->dtype) != hipSuccess) return HK_ERR_LAUNCH;
-    if (!mk.put(1)) return HK_ERR_LAUNCH;
     hk::KvGemmArgs g;
     g.act = act; g.stats = stats; g.ln_w = lp->ln_w; g.ln_b = lp->ln_b; g.Wkv = lp->Wkv; g.bkv = lp->bkv;
     g.Wp = nullptr; g.cvec = nullptr; g.bvec = nullptr;
@@ -132,6 +131,9 @@ int regen_impl(const hk_shape *s, const void *act, int64_t L_act, const hk_layer
         g.cvec = reinterpret_cast<const float *>(pp + L.off_c);
         g.bvec = reinterpret_cast<const float *>(pp + L.off_b);
     }
+    const float *wscale = prepared && hk::kv_gemm_takes_prepared(M, s->d, s->gemm_tile, s->dtype) ? g.bvec + 2 * s->d : nullptr;
+    if (hk::launch_ln_stats(act, stats, M, s->d, s->ln_eps, wscale, stream, s->dtype) != hipSuccess) return HK_ERR_LAUNCH;
+    if (!mk.put(1)) return HK_ERR_LAUNCH;
     g.K_out = K_out; g.V_out = V_out; g.M = M; g.d = s->d; g.n_heads = s->n_heads; g.head_dim = s->head_dim;
     g.L_act = (int)L_act; g.L_cap = L_cap; g.tok_off = tok_off; g.tile = s->gemm_tile; g.dtype = s->dtype;
     g.cu_limit = cu_limit;

@@ -21,7 +21,8 @@ hipError_t allow_dynamic_lds(const void *kernel, int bytes, LdsOnce &once);
 
 // Per-row LayerNorm statistics of act[M, d] (fp16, or bf16 with dtype 1) in fp32.
 // stats[r] = (rstd_r, -mean_r * rstd_r), so that (x - mean) * rstd == fma(x, stats.x, stats.y).
-hipError_t launch_ln_stats(const void *act, float2 *stats, int64_t M, int d, float eps, hipStream_t s, int dtype = 0);
+// wscale (optional, device): stats.x is rstd * *wscale, for a product with the scaled weights of a prepared layer.
+hipError_t launch_ln_stats(const void *act, float2 *stats, int64_t M, int d, float eps, const float *wscale, hipStream_t s, int dtype = 0);
 
 struct KvGemmArgs {
     const void *act;       // [M, d] fp16
@@ -31,8 +32,8 @@ struct KvGemmArgs {
     const void *Wkv;       // [2d, d] fp16
     const void *bkv;       // [2d] fp16
     const void *Wp;        // prepared layer (null when not given): [2d, d] fp16 gamma-scaled weights,
-    const float *cvec;     //   [2d] row sums of Wp,
-    const float *bvec;     //   [2d] bias with the LayerNorm bias folded in
+    const float *cvec;     //   [2d] row sums of the gamma-scaled weights,
+    const float *bvec;     //   [2d] bias with the LayerNorm bias folded in; behind it the factor that Wp has to be taken times
     void *K_out;           // [B, H, L_cap, dh] fp16
     void *V_out;
     int64_t M;             // B * L_act
@@ -48,6 +49,9 @@ hipError_t launch_kv_gemm(const KvGemmArgs &a, hipStream_t s);
 // Whether launch_kv_gemm takes the 256 x 256 streaming kernel for this problem (tile: 0 = choose, 128, 256).
 // That kernel works on a prepared layer (Wp, cvec, bvec), so the caller must supply one.
 bool kv_gemm_uses_prepared(int64_t M, int d, int tile, int dtype = 0);
+// Whether it takes a form that works on the prepared layer when one is given (and its row statistics then carry the
+// layer's factor).
+bool kv_gemm_takes_prepared(int64_t M, int d, int tile, int dtype = 0);
 // The 256 x 256 kernel for prepared layers (LayerNorm folded around the product; needs Wp, cvec, bvec).
 hipError_t launch_kv_gemm_fold(const KvGemmArgs &a, hipStream_t s);
 // The folded product on the tile size that suits the problem, 32 x 32 to 256 x 256 (the same bits with any of them).
@@ -146,7 +150,7 @@ struct AbsorbedArgs {
     const void *act;           // [B, L_act, d]
     float4 *stats;             // [B * L_act] scratch: (rstd, mean, -(mean - first element) rstd, -) of every checkpoint row
     const void *Wp;            // prepared layer: [2d, d] gamma-scaled weights,
-    const float *cvec, *bvec;  //   [2d] row sums of Wp, [2d] bias with the LayerNorm bias folded in
+    const float *cvec, *bvec;  //   [2d] and [2d + 1] as in KvGemmArgs
     void *U;                   // [H, B, d] fp16 scratch: the query carried through the key weights
     float *w_raw;              // [B, H, Lp] fp32 scratch: x_t . U  (Lp = absorbed_row_pitch(L_act))
     void *w;                   // [B, H, Lp] fp16 scratch: softmax weight times rstd, normalised; zero past L_act

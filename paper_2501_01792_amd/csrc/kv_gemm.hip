@@ -196,6 +196,11 @@ bool kv_gemm_uses_prepared(int64_t M, int d, int tile, int dtype)
     return (tile ? tile : (big_tiles >= 512 ? 256 : 128)) == 256;
 }
 
+bool kv_gemm_takes_prepared(int64_t M, int d, int tile, int dtype)
+{
+    return kv_gemm_uses_prepared(M, d, tile, dtype) || (tile == 0 && d >= 128);
+}
+
 hipError_t launch_kv_gemm(const KvGemmArgs &a, hipStream_t s)
 {
     if (a.M <= 0) return hipSuccess;

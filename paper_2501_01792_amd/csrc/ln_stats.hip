@@ -3,7 +3,8 @@
 // The checkpoint is the decoder layer's input (Sec. 3.3), so the layer's pre-attention
 // LayerNorm has to be applied before Eq. 7.  This kernel only produces the two fp32
 // numbers per row that the projection kernel needs to normalise the row on the fly:
-//     stats[r] = (rstd, -mean * rstd),   rstd = 1 / sqrt(var + eps), var biased.
+//     stats[r] = (rstd, -mean * rstd),   rstd = 1 / sqrt(var + eps), var biased
+// (rstd times the factor of a prepared layer's scaled weights, where the projection works on one).
 // Mean and variance are taken in two passes over the row (over a register copy of the row when it
 // fits, else over memory, where the second pass hits L2), both summed in fp32 with wavefront shuffles.
 #include "hk_internal.h"
@@ -27,7 +28,7 @@ constexpr int kMaxVec = 20;        // rows of up to 64 * 8 * 20 = 10240 elements
 template <int DT, int NV>
 __global__ __launch_bounds__(256) void ln_stats_reg_kernel(const typename Elem<DT>::T *__restrict__ act,
                                                            float2 *__restrict__ stats,
-                                                           int64_t M, int d, float eps)
+                                                           int64_t M, int d, float eps, const float *__restrict__ wscale)
 {
     const int lane = threadIdx.x & 63;
     const int64_t row = (int64_t)blockIdx.x * kRowsPerBlock + (threadIdx.x >> 6);
@@ -63,14 +64,14 @@ __global__ __launch_bounds__(256) void ln_stats_reg_kernel(const typename Elem<D
     }
     const float var = wave_sum(ss) / (float)d;
     const float rstd = 1.0f / sqrtf(var + eps);
-    if (lane == 0) stats[row] = make_float2(rstd, -mean * rstd);
+    if (lane == 0) stats[row] = make_float2(wscale ? rstd * *wscale : rstd, -mean * rstd);
 }
 
 // Any row length: two passes over memory (the second one hits L2).
 template <int DT>
 __global__ __launch_bounds__(256) void ln_stats_kernel(const typename Elem<DT>::T *__restrict__ act,
                                                        float2 *__restrict__ stats,
-                                                       int64_t M, int d, float eps)
+                                                       int64_t M, int d, float eps, const float *__restrict__ wscale)
 {
     const int lane = threadIdx.x & 63;
     const int64_t row = (int64_t)blockIdx.x * kRowsPerBlock + (threadIdx.x >> 6);
@@ -98,30 +99,30 @@ __global__ __launch_bounds__(256) void ln_stats_kernel(const typename Elem<DT>::
     }
     const float var = wave_sum(ss) / (float)d;
     const float rstd = 1.0f / sqrtf(var + eps);
-    if (lane == 0) stats[row] = make_float2(rstd, -mean * rstd);
+    if (lane == 0) stats[row] = make_float2(wscale ? rstd * *wscale : rstd, -mean * rstd);
 }
 
 template <int DT>
-hipError_t launch_dt(const void *act, float2 *stats, int64_t M, int d, float eps, hipStream_t s)
+hipError_t launch_dt(const void *act, float2 *stats, int64_t M, int d, float eps, const float *wscale, hipStream_t s)
 {
     const int64_t blocks = (M + kRowsPerBlock - 1) / kRowsPerBlock;
     const typename Elem<DT>::T *a = static_cast<const typename Elem<DT>::T *>(act);
     const int nv = (d / 8 + 63) / 64;          // 16-byte chunks per lane
     const dim3 grid((unsigned)blocks), block(256);
-    if (nv <= 4) hipLaunchKernelGGL((ln_stats_reg_kernel<DT, 4>), grid, block, 0, s, a, stats, M, d, eps);
-    else if (nv <= 8) hipLaunchKernelGGL((ln_stats_reg_kernel<DT, 8>), grid, block, 0, s, a, stats, M, d, eps);
-    else if (nv <= 12) hipLaunchKernelGGL((ln_stats_reg_kernel<DT, 12>), grid, block, 0, s, a, stats, M, d, eps);
-    else if (nv <= kMaxVec) hipLaunchKernelGGL((ln_stats_reg_kernel<DT, kMaxVec>), grid, block, 0, s, a, stats, M, d, eps);
-    else hipLaunchKernelGGL(ln_stats_kernel<DT>, grid, block, 0, s, a, stats, M, d, eps);
+    if (nv <= 4) hipLaunchKernelGGL((ln_stats_reg_kernel<DT, 4>), grid, block, 0, s, a, stats, M, d, eps, wscale);
+    else if (nv <= 8) hipLaunchKernelGGL((ln_stats_reg_kernel<DT, 8>), grid, block, 0, s, a, stats, M, d, eps, wscale);
+    else if (nv <= 12) hipLaunchKernelGGL((ln_stats_reg_kernel<DT, 12>), grid, block, 0, s, a, stats, M, d, eps, wscale);
+    else if (nv <= kMaxVec) hipLaunchKernelGGL((ln_stats_reg_kernel<DT, kMaxVec>), grid, block, 0, s, a, stats, M, d, eps, wscale);
+    else hipLaunchKernelGGL(ln_stats_kernel<DT>, grid, block, 0, s, a, stats, M, d, eps, wscale);
     return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_ln_stats(const void *act, float2 *stats, int64_t M, int d, float eps, hipStream_t s, int dtype)
+hipError_t launch_ln_stats(const void *act, float2 *stats, int64_t M, int d, float eps, const float *wscale, hipStream_t s, int dtype)
 {
     if (M <= 0) return hipSuccess;
-    return dtype == 1 ? launch_dt<1>(act, stats, M, d, eps, s) : launch_dt<0>(act, stats, M, d, eps, s);
+    return dtype == 1 ? launch_dt<1>(act, stats, M, d, eps, wscale, s) : launch_dt<0>(act, stats, M, d, eps, wscale, s);
 }
 
 }  // namespace hk

@@ -26,6 +26,39 @@ SIZES = [
 
 
 @pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16], ids=["f16", "bf16"])
+@pytest.mark.parametrize("ln_scale", [1.0, 1e-2, 1e-3, 1e-4])
+@pytest.mark.parametrize("H,dh,B,L", [(6, 128, 4, 17), (6, 128, 4, 6000)])        # a small tile; 256 x 256
+def test_small_layernorm_weights_keep_the_precision_of_a_prepared_layer(hk, H, dh, B, L, ln_scale, dtype):
+    """A small ln_w must not push the prepared weights out of the normal range of their type.  Rows: one rounding of the
+    weights and one of the result, each u / sqrt(3) at most in the 2-norm (u = 2^-11; 2^-8, bf16).  Attention without
+    regenerated rows: the tolerance of the step, 5e-3."""
+    d = H * dh
+    gen = torch.Generator(device="cuda").manual_seed(L)
+
+    def draw(*shape, std, mean=0.0):
+        return torch.empty(shape, device="cuda").normal_(mean, std, generator=gen)
+
+    layer = tuple(t.to(dtype) for t in (draw(d, std=0.02, mean=1.0) * ln_scale, draw(d, std=0.02) * ln_scale,
+                                        draw(2 * d, d, std=0.2), draw(2 * d, std=0.1) * ln_scale))
+    prepared = hk.prepare_layer(*layer, H)
+    # scores of spread 1.6 whatever ln_w is; weights of 0.2 keep the results themselves in the normal range
+    act, q = draw(B, L, d, std=1.0, mean=0.25).to(dtype), draw(B, H, dh, std=0.3 / ln_scale).to(dtype)
+    K, V = hk.regen_kv(act, *layer, H, prepared=prepared)
+    out = hk.hybrid_decode_attn_absorbed(q, None, None, act, layer + (prepared,), 0.0)
+
+    ln_w, ln_b, W, b = (t.double() for t in layer)
+    x = act.double().view(B * L, d)
+    xhat = (x - x.mean(1, keepdim=True)) / torch.sqrt(x.var(1, unbiased=False, keepdim=True) + 1e-5) * ln_w + ln_b
+    rk, rv = ((xhat @ W.T + b).view(B, L, 2, H, dh).permute(2, 0, 3, 1, 4))
+    u = {torch.float16: 2.0 ** -11, torch.bfloat16: 2.0 ** -8}[dtype]
+    for name, got, ref, tol in (("K", K, rk, 2 * u / 3 ** 0.5), ("V", V, rv, 2 * u / 3 ** 0.5),
+                                ("out", out, (torch.softmax((q.double()[:, :, None] * rk).sum(-1) * dh ** -0.5, 2)[..., None] * rv).sum(2), 5e-3)):
+        err = float((got.double() - ref).norm() / ref.norm())
+        print("%s: rel_l2 = %.3e" % (name, err), flush=True)
+        assert err <= tol, name
+
+
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16], ids=["f16", "bf16"])
 @pytest.mark.parametrize("H,dh,B,L", SIZES)
 def test_every_tile_gives_the_same_rows(hk, H, dh, B, L, dtype):
     d = H * dh
