@@ -43,6 +43,27 @@ struct PreparedLayout {
 };
 PreparedLayout prepared_layout(int d);
 
+// Wavefronts (token ranges) of the attention of a step whose other scratch ends at `base` bytes, or at `base_prepared`
+// for a caller that brings a prepared layer.  As many as the library wants, unless that is what makes the step outgrow
+// the static scratch array (hk_hybrid_decode_attn_static): then as many as fit, down to one per 128 positions (less one:
+// the partial's place is that of the factor in a prepared layer).  Small problems are cut up to twice as fine, and no
+// step is refused for the sake of that.  The number is the same for every entry point and caller, because the order of
+// the sums, and with it the result's bits, hang on it.
+int step_wavefronts(const hk_shape *s, int64_t BH, int64_t L, size_t base, size_t base_prepared)
+{
+    const int want = hk::attn_wavefronts(BH, L, s->attn_splits);
+    if (s->attn_splits > 0) return want;
+    const int64_t coarse = (BH * L + 127) / 128 - 1;
+    const int least = want < coarse ? want : coarse > 1 ? (int)coarse : 1;
+    const size_t slot = (s->head_dim + 2) * sizeof(float);
+    for (size_t b : {base, base_prepared}) {
+        if (b > HK_STATIC_SCRATCH_BYTES) continue;
+        const int64_t room = (int64_t)((HK_STATIC_SCRATCH_BYTES - b) / slot) - BH;    // b and the array are multiples of kAlign
+        if (room >= least) return room < want ? (int)room : want;
+    }
+    return want;
+}
+
 // Fills the plan; returns HK_OK or a status.  regen_only: plan of hk_regen_kv (no K/V scratch, no partials).
 // prep_room = false: the caller brings a prepared layer, no room for one is planned.
 int make_plan(const hk_shape *s, int64_t B, int64_t L_kv, int64_t L_act, bool regen_only, Plan *p, bool prep_room = true)
@@ -69,7 +90,8 @@ int make_plan(const hk_shape *s, int64_t B, int64_t L_kv, int64_t L_act, bool re
     p->off_partial = end;
     p->n_waves = 0;
     if (!regen_only && L_kv + L_act > 0 && p->BH > 0) {
-        p->n_waves = hk::attn_wavefronts(p->BH, L_kv + L_act, s->attn_splits);
+        const size_t prep = p->M > 0 && hk::kv_gemm_uses_prepared(p->M, s->d, s->gemm_tile, s->dtype) ? prepared_layout(s->d).total : 0;
+        p->n_waves = step_wavefronts(s, p->BH, L_kv + L_act, p->off_prep + prep, p->off_prep);
         end += align_up(((size_t)p->n_waves + (size_t)p->BH) * (s->head_dim + 2) * sizeof(float));
     }
     p->total = end;
