@@ -604,10 +604,9 @@ int hk_hybrid_decode_attn_absorbed(const hk_shape *shape, const void *q,
 size_t hk_qkv_workspace_bytes(const hk_shape *shape, int32_t B)
 {
     if (check_shape(shape) != HK_OK || B < 0 || B > (1 << 24)) return 0;
-    // rows go kQkvMaxRows at a time; the same for both dtypes (bf16 takes the three launches wherever fp16 does)
+    // rows go kQkvMaxRows at a time, and a last launch of fewer rows needs no more
     const int rows = B < hk::kQkvMaxRows ? B : hk::kQkvMaxRows;
-    if (hk::qkv_stream_takes(rows, shape->d, 1)) return hk::qkv_stream_scratch_bytes(rows, shape->d);
-    return kAlign;                                             // fewer rows than that in a last launch need no more
+    return hk::qkv_stream_takes(rows, shape->d, shape->dtype) ? hk::qkv_stream_scratch_bytes(rows, shape->d) : kAlign;
 }
 
 namespace {

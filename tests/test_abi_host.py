@@ -183,7 +183,7 @@ def test_qkv_current_rejects_bad_arguments():
     """Every check of hk_qkv_current runs on the host before a launch: no GPU is touched here."""
     ok = hk.make_shape(768, 12)
     need = hk.hk_qkv_workspace_bytes(ok, 4)
-    assert need > 0                                              # a token amount: the call keeps its intermediates on chip
+    assert need > 0                                              # 4 rows of a narrow layer: a single kernel
     assert hk.hk_qkv_workspace_bytes(hk.make_shape(768, 11), 4) == 0
     assert hk.hk_qkv_workspace_bytes(ok, 1000) == hk.hk_qkv_workspace_bytes(ok, 128)      # rows go 128 at a time
     lp = hk.hk_layer_params(FAKE, FAKE, FAKE, FAKE, None)
@@ -204,6 +204,21 @@ def test_qkv_current_rejects_bad_arguments():
     assert call(x=FAKE + 8) == hk.HK_ERR_ALIGN and call(K=FAKE + 8) == hk.HK_ERR_ALIGN
     assert call(A=FAKE + 2) == hk.HK_ERR_ALIGN and call(ws=FAKE + 16) == hk.HK_ERR_ALIGN
     assert call(n=need - 1) == hk.HK_ERR_WORKSPACE
+
+
+def test_qkv_workspace_is_what_the_call_uses():
+    """256 bytes exactly where the call is a single kernel: by rows, width and dtype (head_dim 64 or 128 alike)."""
+    def three_launches(B, d, bf16):
+        shape = hk.make_shape(d, d // 64, dtype=hk.HK_DTYPE_BF16 if bf16 else hk.HK_DTYPE_F16)
+        need = hk.hk_qkv_workspace_bytes(shape, B)
+        assert need == 256 or need > 2 * B * d                   # the normalised rows at least
+        return need > 256
+
+    assert not three_launches(64, 9216, False)
+    assert all(three_launches(B, d, bf16) for bf16 in (False, True) for B, d in
+               ((128, 768), (65, 768), (33, 2048), (64, 7168), (1, 5504), (32, 9216), (128, 9216)))
+    assert not any(three_launches(B, d, bf16) for bf16 in (False, True) for B, d in
+                   ((128, 704), (64, 1984), (32, 5440), (1, 4096), (128, 9280), (1, 9280)))
 
 
 def test_binding_refuses_cpu_tensors():
