@@ -410,20 +410,28 @@ hipError_t launch_any(const QkvArgs &a, int cus, hipStream_t s)
 
 }  // namespace
 
-// Where the lines lie (measured, fp16 / bf16, one-launch kernel against this one, us): three launches cost 17 us however
-// small the layer, so wide layers and many rows come here.
-//   more than 64 rows: d = 768: 19.3 / 22.4 against 18.5 (B = 80 / 96); every wider layer gains, 4096: 55 / 68 against 35
-//   33 to 64 rows: d = 1280, B = 40: 17.3 against 19; 2048: 20.7 against 18.6; 4096, B = 64: 36 / 43 against 32.  fp16 up
-//     to 8192 (B = 64: 95 against 93), beyond which the one-launch kernel's workgroups of 128 features keep up (9216, B =
-//     64: 103 against 108; bf16: 119 against 110)
-//   up to 32 rows: while the one-launch kernel's workgroups (64 features) fit 256 units at once it is the faster one: d =
-//     5120, B = 32: 36 against 36, B = 8: 32 against 34; 6144: 62 to 70 against 47 to 49; 9216, B = 32: 103 against 92
+// Where the lines lie (measured, new weights in every call, replayed from a graph, us a call, one-launch kernel against
+// this one, fp16 / bf16 where they differ).  Three launches cost 12 to 14 us however small the layer, so many rows and wide
+// layers come here.
+//   97 rows and more: every layer from d = 768 on: 25.0 / 28.1 against 15.1 (B = 128); 4096: 69 / 84 against 39; 7168:
+//     116 / 141 against 91; 9216: 148 / 179 against 136; 9152 (units of 64 features): 148 against 149 / 181 against 150
+//   65 to 96 rows: from d = 768 on: 18.8 / 20.9 against 13.5 (B = 65).  fp16 below 8448: 8192, B = 96: 118 against 108;
+//     8256, B = 65: 114 against 107; 8448, B = 96: 111.7 against 116.6; 9216, B = 96: 118 against 127; 9152: 118 against
+//     137.  bf16 everywhere: 9216, B = 96: 145 against 128
+//   33 to 64 rows: from d = 2048 on: 20.6 / 23.7 against 18.0 (B = 33).  fp16 below 8192, where the one-launch kernel
+//     changes to workgroups of 128 features: 8128, B = 64: 132 against 97; 8192, B = 33: 91 against 95 and 101 against 98
+//     (two sessions); 8704: level.  bf16 below 8448: 8256, B = 64: 111 against 104; 8448: 101 against 103; 9152: 109
+//     against 123; 9216: level
+//   up to 32 rows: while the one-launch kernel's workgroups (64 features) fit 256 units at once it is level within 8 % or
+//     faster: 4096, B = 32: 29.7 against 27.4; from 5504 on 60 against 39 (B = 1); 9216: 98 against 93 (B = 1), 105
+//     against 94 (B = 32)
 // Wider layers than 9216 were not measured and stay with one launch.
 bool qkv_stream_takes(int B, int d, int dtype)
 {
     if (B <= 0 || B > kQkvMaxRows || d % kUnitK != 0 || d > 9216) return false;
-    if (B > 64) return d >= 768;
-    if (B > 32) return d >= 2048 && (dtype == 1 || d <= 8192);
+    if (B > 96) return d >= 768;
+    if (B > 64) return d >= 768 && (dtype == 1 || d < 8448);
+    if (B > 32) return d >= 2048 && d < (dtype == 1 ? 8448 : 8192);
     return 3 * (d / 64) > 256;
 }
 

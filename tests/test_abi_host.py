@@ -214,7 +214,11 @@ def test_qkv_workspace_is_what_the_call_uses():
         assert need == 256 or need > 2 * B * d                   # the normalised rows at least
         return need > 256
 
-    assert not three_launches(64, 9216, False)
+    # wide layers on which the single kernel is as fast or faster
+    assert not any(three_launches(B, d, False) for B, d in ((65, 8448), (96, 9216), (80, 9152), (33, 8192), (64, 9216)))
+    assert not any(three_launches(B, d, True) for B, d in ((33, 8448), (64, 9152)))
+    assert all(three_launches(B, d, True) for B, d in ((65, 8448), (96, 9216), (33, 8384)))
+    assert three_launches(96, 8384, False) and three_launches(64, 8128, False) and three_launches(97, 9152, False)
     assert all(three_launches(B, d, bf16) for bf16 in (False, True) for B, d in
                ((128, 768), (65, 768), (33, 2048), (64, 7168), (1, 5504), (32, 9216), (128, 9216)))
     assert not any(three_launches(B, d, bf16) for bf16 in (False, True) for B, d in
