@@ -144,6 +144,7 @@ struct StreamArgs {
     const void *xhat, *Wq, *Wkv;
     float *part;
     int B, d, q_tiles, nks, units, runs, live;                 // live: units that are asked for (the first ones)
+    int split;                                                 // workgroups that share a run: each takes BN features of its tiles
 };
 
 template <int BM, int BN, int NS>
@@ -166,8 +167,9 @@ __global__ __launch_bounds__(256, (stream_per_cu<BM, BN, NS>())) void qkv_stream
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 1, wn = wave & 1;
     const int d = p.d, nks = p.nks;
-    const int u_begin = run_begin((int)blockIdx.x, p.units, p.runs);
-    const int u_end = run_begin((int)blockIdx.x + 1, p.units, p.runs);
+    const int run = (int)blockIdx.x / p.split, part = (int)blockIdx.x % p.split;
+    const int u_begin = run_begin(run, p.units, p.runs);
+    const int u_end = run_begin(run + 1, p.units, p.runs);
     const int n = (u_end < p.live ? u_end : p.live) - u_begin; // >= 1: no more runs than units, none past the live ones
 
     // ---- direct loads: load i of wavefront w fills LDS rows 8 (w + 4 i) .. + 7 of an operand; lane l writes row l / 8,
@@ -192,8 +194,8 @@ __global__ __launch_bounds__(256, (stream_per_cu<BM, BN, NS>())) void qkv_stream
     // the unit to ask for next: its tile's rows and its place on the reduction axis
     int ask_tile = u_begin / nks, ask_k = u_begin % nks;
     auto tile_rsrc = [&](int tile) {
-        const elem_t *W = tile < p.q_tiles ? static_cast<const elem_t *>(p.Wq) + (int64_t)tile * BN * d
-                                           : static_cast<const elem_t *>(p.Wkv) + (int64_t)(tile - p.q_tiles) * BN * d;
+        const elem_t *W = tile < p.q_tiles ? static_cast<const elem_t *>(p.Wq) + (int64_t)(tile * p.split + part) * BN * d
+                                           : static_cast<const elem_t *>(p.Wkv) + (int64_t)((tile - p.q_tiles) * p.split + part) * BN * d;
         return __builtin_amdgcn_make_buffer_rsrc(const_cast<elem_t *>(W), 0, BN * d * 2, 0x00020000);
     };
     __amdgpu_buffer_rsrc_t b_rsrc = tile_rsrc(ask_tile);
@@ -281,7 +283,7 @@ __global__ __launch_bounds__(256, (stream_per_cu<BM, BN, NS>())) void qkv_stream
         if constexpr (KIND == 2) asked(i + NS + 1 < n);
         cur = nxt;
         if (++k == nks || KIND == 0) {                         // the tile ends here for this run: its part leaves
-            float4_t *dst = reinterpret_cast<float4_t *>(p.part + (int64_t)(tile + (int)blockIdx.x) * (BM * BN));
+            float4_t *dst = reinterpret_cast<float4_t *>(p.part + (int64_t)((tile + run) * p.split + part) * (BM * BN));
 #pragma unroll
             for (int ii = 0; ii < TM; ++ii)
 #pragma unroll
@@ -298,12 +300,12 @@ __global__ __launch_bounds__(256, (stream_per_cu<BM, BN, NS>())) void qkv_stream
 #endif
 }
 
-// finish: a workgroup per (tile, 16-row blocks i of the wavefront rows); thread for thread the layout of the parts.
+// finish: a workgroup per (tile or part of it, 16-row blocks i of the wavefront rows); thread for thread the layout of the parts.
 struct FinishArgs {
     const float *part;
     const void *bq, *bkv;
     void *q_out, *K_dst, *V_dst;
-    int B, d, n_heads, head_dim, L_cap, tok_pos, q_tiles, nks, units, runs;
+    int B, d, n_heads, head_dim, L_cap, tok_pos, q_tiles, nks, units, runs, split;
     PagedDst pd;
 };
 
@@ -314,21 +316,21 @@ __global__ __launch_bounds__(256) void qkv_finish_kernel(FinishArgs p)
     typedef elem_t out_t __attribute__((ext_vector_type(BN / 32)));
     constexpr int TN = BN / 32;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int tile = blockIdx.x, i = blockIdx.y;
+    const int tile = (int)blockIdx.x / p.split, part = (int)blockIdx.x % p.split, i = blockIdx.y;
     const int m0 = (wave >> 1) * (BM / 2) + 16 * i + 4 * (lane >> 4);       // first of this thread's 4 rows
     if (m0 >= p.B) return;                                                  // no barrier in this kernel
     const int w0 = run_of(tile * p.nks, p.units, p.runs), w1 = run_of(tile * p.nks + p.nks - 1, p.units, p.runs);
-    const float4_t *src = reinterpret_cast<const float4_t *>(p.part + (int64_t)(tile + w0) * (BM * BN)) + i * TN * 256 + tid;
+    const float4_t *src = reinterpret_cast<const float4_t *>(p.part + (int64_t)((tile + w0) * p.split + part) * (BM * BN)) + i * TN * 256 + tid;
     float4_t sum[TN];
 #pragma unroll
     for (int j = 0; j < TN; ++j) sum[j] = src[256 * j];
     for (int w = w0 + 1; w <= w1; ++w) {
-        src += BM * BN / 4;
+        src += p.split * (BM * BN / 4);
 #pragma unroll
         for (int j = 0; j < TN; ++j) sum[j] += src[256 * j];
     }
     const bool is_q = tile < p.q_tiles;
-    const int n = (is_q ? tile : tile - p.q_tiles) * BN + (BN / 2) * (wave & 1) + TN * (lane & 15);   // first of TN features
+    const int n = ((is_q ? tile : tile - p.q_tiles) * p.split + part) * BN + (BN / 2) * (wave & 1) + TN * (lane & 15);   // first of TN features
     const out_t bias = *reinterpret_cast<const out_t *>(static_cast<const elem_t *>(is_q ? p.bq : p.bkv) + n);
     const int f = n < p.d ? n : n - p.d;
     const int h = f / p.head_dim, e = f % p.head_dim;
@@ -367,7 +369,7 @@ int stream_runs(int units, int workgroups)
     return workgroups < most ? workgroups : most;
 }
 
-template <int BM, int BN, int NS, int DT>
+template <int BM, int BN, int NS, int SPLIT, int DT>
 hipError_t launch_dt(const QkvArgs &a, int cus, hipStream_t s)
 {
     typedef typename Elem<DT>::T elem_t;
@@ -381,7 +383,7 @@ hipError_t launch_dt(const QkvArgs &a, int cus, hipStream_t s)
     if (e != hipSuccess) return e;
     StreamArgs t;
     t.xhat = xhat; t.Wq = a.Wq; t.Wkv = a.Wkv; t.part = part;
-    t.B = a.B; t.d = a.d; t.q_tiles = a.d / BN; t.nks = a.d / kUnitK;
+    t.B = a.B; t.d = a.d; t.q_tiles = a.d / (BN * SPLIT); t.nks = a.d / kUnitK; t.split = SPLIT;
     const int tiles = a.K_dst ? 3 * t.q_tiles : t.q_tiles;
     t.units = 3 * t.q_tiles * t.nks;
     t.live = tiles * t.nks;
@@ -392,20 +394,20 @@ hipError_t launch_dt(const QkvArgs &a, int cus, hipStream_t s)
     static LdsOnce lds_once;
     e = allow_dynamic_lds(reinterpret_cast<const void *>(kern), lds, lds_once);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3((unsigned)(run_of(t.live - 1, t.units, t.runs) + 1)), dim3(256), lds, s, t);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(SPLIT * (run_of(t.live - 1, t.units, t.runs) + 1))), dim3(256), lds, s, t);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     FinishArgs f;
     f.part = part; f.bq = a.bq; f.bkv = a.bkv; f.q_out = a.q_out; f.K_dst = a.K_dst; f.V_dst = a.V_dst;
     f.B = a.B; f.d = a.d; f.n_heads = a.n_heads; f.head_dim = a.head_dim; f.L_cap = a.L_cap; f.tok_pos = a.tok_pos;
-    f.q_tiles = t.q_tiles; f.nks = t.nks; f.units = t.units; f.runs = t.runs; f.pd = pd;
-    hipLaunchKernelGGL((qkv_finish_kernel<BM, BN, DT>), dim3((unsigned)tiles, BM / 32), dim3(256), 0, s, f);
+    f.q_tiles = t.q_tiles; f.nks = t.nks; f.units = t.units; f.runs = t.runs; f.split = SPLIT; f.pd = pd;
+    hipLaunchKernelGGL((qkv_finish_kernel<BM, BN, DT>), dim3((unsigned)(SPLIT * tiles), BM / 32), dim3(256), 0, s, f);
     return hipGetLastError();
 }
 
-template <int BM, int BN, int NS>
+template <int BM, int BN, int NS, int SPLIT = 1>
 hipError_t launch_any(const QkvArgs &a, int cus, hipStream_t s)
 {
-    return a.dtype == 1 ? launch_dt<BM, BN, NS, 1>(a, cus, s) : launch_dt<BM, BN, NS, 0>(a, cus, s);
+    return a.dtype == 1 ? launch_dt<BM, BN, NS, SPLIT, 1>(a, cus, s) : launch_dt<BM, BN, NS, SPLIT, 0>(a, cus, s);
 }
 
 }  // namespace
@@ -461,7 +463,14 @@ hipError_t launch_qkv_stream(const QkvArgs &a, hipStream_t s)
         }
     }
     switch ((a.B + 31) / 32) {
-    case 1: return launch_any<32, 128, 7>(a, cus, s);
+    case 1: {
+        // Q alone occupies a third of the compute units, each of which waits for its own units: two workgroups a run then,
+        // 64 features each, with a ring of more units.  The cut along the reduction, and with it the bits, is the same.
+        // Q alone, B = 1 / 32, fp16: d = 7168: 40.8 / 44.3 -> 29.6 / 35.0 us (one-launch kernel: 36.6 / 41.0), 9216: 60.3 /
+        // 65.7 -> 40.5 / 48.9 (46.5 / 53.8).  With more rows one workgroup a run is faster than the one-launch kernel too.
+        static_assert(stream_per_cu<32, 128, 7>() == stream_per_cu<32, 64, 12>(), "the cut follows the workgroups of a compute unit");
+        return a.K_dst ? launch_any<32, 128, 7>(a, cus, s) : launch_any<32, 64, 12, 2>(a, cus, s);
+    }
     case 2: return launch_any<64, 128, 6>(a, cus, s);
     case 3: return launch_any<96, 128, 5>(a, cus, s);
     default: return launch_any<128, 128, 4>(a, cus, s);
