@@ -21,6 +21,7 @@
 #include "hk_internal.h"
 #include "elem.h"
 #include "kv_gemm_common.h"
+#include "kv_gemm_forms.h"
 
 #include <type_traits>
 
@@ -243,30 +244,21 @@ hipError_t launch_tile_any(const KvGemmArgs &a, hipStream_t s)
     return a.dtype == 1 ? launch_tile_dt<BM, BN, NS, 1>(a, s) : launch_tile_dt<BM, BN, NS, 0>(a, s);
 }
 
-// Which tile: the one with the least estimated time per k block for the compute unit with the most tiles,
-//     first + more (n - 1),   n = tiles of the busiest compute unit,
-// in microseconds as measured (first: a compute unit with one tile; more: each further one, sharing the unit or after
-// it).  Both grow with the tile's area, but `more` only from 64 x 64 on in proportion to it: small tiles move more
-// bytes per product, large ones leave units idle.  Measured at d = 768 to 9216 and M = 8 to 3072, the choice was the
-// fastest form or within 8 % of it.  256 x 256 is the kernel of kv_gemm_fold.hip.
-struct TileForm {
-    int bm, bn;
-    float first, more;
-    hipError_t (*launch)(const KvGemmArgs &, hipStream_t);
+// The kernels of forms::kForms, in its order.
+hipError_t (*const kLaunch[])(const KvGemmArgs &, hipStream_t) = {
+    launch_kv_gemm_fold,
+    launch_tile_any<256, 128, 3>,
+    launch_tile_any<128, 256, 3>,
+    launch_tile_any<192, 128, 3>,
+    launch_tile_any<128, 128, 4>,
+    launch_tile_any<128, 64, 3>,
+    launch_tile_any<64, 128, 3>,
+    launch_tile_any<64, 64, 4>,
+    launch_tile_any<64, 32, 6>,
+    launch_tile_any<32, 64, 6>,
+    launch_tile_any<32, 32, 9>,
 };
-const TileForm kForms[] = {
-    {256, 256, 1.30f, 1.50f, launch_kv_gemm_fold},
-    {256, 128, 0.90f, 0.95f, launch_tile_any<256, 128, 3>},
-    {128, 256, 0.90f, 0.95f, launch_tile_any<128, 256, 3>},
-    {192, 128, 0.69f, 0.75f, launch_tile_any<192, 128, 3>},
-    {128, 128, 0.61f, 0.60f, launch_tile_any<128, 128, 4>},
-    {128, 64, 0.46f, 0.34f, launch_tile_any<128, 64, 3>},
-    {64, 128, 0.49f, 0.35f, launch_tile_any<64, 128, 3>},
-    {64, 64, 0.37f, 0.21f, launch_tile_any<64, 64, 4>},
-    {64, 32, 0.29f, 0.165f, launch_tile_any<64, 32, 6>},
-    {32, 64, 0.30f, 0.16f, launch_tile_any<32, 64, 6>},
-    {32, 32, 0.20f, 0.13f, launch_tile_any<32, 32, 9>},
-};
+static_assert(sizeof(kLaunch) / sizeof(kLaunch[0]) == forms::kCount, "one kernel per form");
 
 }  // namespace
 
@@ -276,17 +268,7 @@ hipError_t launch_kv_gemm_prepared(const KvGemmArgs &a, hipStream_t s)
     int dev = 0, cus = 0;
     const hipError_t e = current_device_cus(&dev, &cus);
     if (e != hipSuccess) return e;
-    const TileForm *best = nullptr;
-    double least = 0.;
-    for (const TileForm &f : kForms) {
-        const int64_t tiles = ((a.M + f.bm - 1) / f.bm) * ((2 * (int64_t)a.d + f.bn - 1) / f.bn);
-        const double t = f.first + f.more * (double)((tiles + cus - 1) / cus - 1);
-        if (!best || t < least) {
-            best = &f;
-            least = t;
-        }
-    }
-    return best->launch(a, s);
+    return kLaunch[forms::pick(a.M, a.d, cus)](a, s);
 }
 
 }  // namespace hk

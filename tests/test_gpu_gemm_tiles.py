@@ -18,9 +18,11 @@ SIZES = [
     (3, 64, 1, 6001), (12, 128, 1, 701),                          # 128 x 128
     (12, 128, 1, 1537), (5, 64, 1, 8000), (12, 64, 4, 3001),      # 192 x 128
     (12, 64, 1, 4100), (32, 128, 5, 193),                         # 256 x 128
-    (72, 128, 1, 5),                                              # 32 x 64
+    (72, 128, 1, 5),                                              # 32 x 32, several tiles per compute unit
+    (17, 64, 1, 195), (51, 128, 2, 15),                           # 32 x 64
     (72, 128, 3, 17),                                             # 64 x 128
-    (56, 128, 1, 500),                                            # 256 x 128 or 128 x 256: 224 tiles
+    (56, 128, 1, 500),                                            # 256 x 128
+    (72, 128, 1, 300), (12, 128, 1, 2563),                        # 128 x 256
     (12, 64, 1, 6000),                                            # 256 x 256
 ]
 
