@@ -1,5 +1,5 @@
-// QKV generation for the current input tokens (qkv_current.hip), form for more than one block of 32 rows, in three
-// launches:
+// QKV generation for the current input tokens (qkv_current.hip), form for many rows and for wide layers (qkv_stream_takes
+// says which), in three launches:
 //   norm   xhat = LayerNorm(x) [B, d] in the storage type (fp32 statistics, one rounding), and the checkpoint copy
 //   stream parts of xhat [Wq; Wkv]^T, fp32, from a fixed number of persistent workgroups
 //   finish sum of the parts, bias, rounding, store of q and of the K / V rows
@@ -59,9 +59,9 @@ __device__ __forceinline__ float block_sum(float v, float *buf)
     return (buf[0] + buf[1]) + (buf[2] + buf[3]);
 }
 
-// norm: a workgroup per row.  Mean, then centred sum of squares, in fp32; the first kKeep chunks of a thread stay in
-// registers (rows of up to 16384 elements are read once), later ones are read again in each pass.
-constexpr int kKeep = 8;
+// norm: a workgroup per row, the row in registers.  Mean, then centred sum of squares, in fp32.
+constexpr int kMaxD = 9216;                                 // widest layer that comes here (qkv_stream_takes)
+constexpr int kKeep = (kMaxD / 8 + 255) / 256;              // 16-byte chunks of a thread
 template <int DT>
 __global__ __launch_bounds__(256) void qkv_norm_kernel(const typename Elem<DT>::T *__restrict__ x,
                                                        const typename Elem<DT>::T *__restrict__ gamma,
@@ -101,7 +101,6 @@ __global__ __launch_bounds__(256) void qkv_norm_kernel(const typename Elem<DT>::
 #pragma unroll
     for (int i = 0; i < kKeep; ++i)
         if (tid + 256 * i < nvec) add(v[i]);
-    for (int c = tid + 256 * kKeep; c < nvec; c += 256) add(row[c]);
     const float mean = block_sum(s, buf[0]) / (float)d;
     s = 0.f;
     auto add_sq = [&](const vec8_t &e8) {
@@ -111,7 +110,6 @@ __global__ __launch_bounds__(256) void qkv_norm_kernel(const typename Elem<DT>::
 #pragma unroll
     for (int i = 0; i < kKeep; ++i)
         if (tid + 256 * i < nvec) add_sq(v[i]);
-    for (int c = tid + 256 * kKeep; c < nvec; c += 256) add_sq(row[c]);
     const float rstd = 1.0f / __builtin_sqrtf(block_sum(s, buf[1]) / (float)d + eps);
     vec8_t *out = reinterpret_cast<vec8_t *>(xhat + (int64_t)m * d);
     auto put = [&](const vec8_t &e8, int c) {
@@ -125,7 +123,6 @@ __global__ __launch_bounds__(256) void qkv_norm_kernel(const typename Elem<DT>::
 #pragma unroll
     for (int i = 0; i < kKeep; ++i)
         if (tid + 256 * i < nvec) put(v[i], tid + 256 * i);
-    for (int c = tid + 256 * kKeep; c < nvec; c += 256) put(row[c], c);
 }
 
 // Waits until at most r (<= R) of the youngest units this wavefront has asked for, LPS loads each, are in flight (stores
@@ -430,7 +427,7 @@ hipError_t launch_any(const QkvArgs &a, int cus, hipStream_t s)
 // Wider layers than 9216 were not measured and stay with one launch.
 bool qkv_stream_takes(int B, int d, int dtype)
 {
-    if (B <= 0 || B > kQkvMaxRows || d % kUnitK != 0 || d > 9216) return false;
+    if (B <= 0 || B > kQkvMaxRows || d % kUnitK != 0 || d > kMaxD) return false;
     if (B > 96) return d >= 768;
     if (B > 64) return d >= 768 && (dtype == 1 || d < 8448);
     if (B > 32) return d >= 2048 && d < (dtype == 1 ? 8448 : 8192);
@@ -448,7 +445,7 @@ size_t qkv_stream_scratch_bytes(int B, int d)
 
 hipError_t launch_qkv_stream(const QkvArgs &a, hipStream_t s)
 {
-    if (a.B <= 0 || a.B > kQkvMaxRows || a.d % kUnitK != 0 || a.d > 9216 ||
+    if (a.B <= 0 || a.B > kQkvMaxRows || a.d % kUnitK != 0 || a.d > kMaxD ||
         a.scratch_bytes < qkv_stream_scratch_bytes(a.B, a.d)) return hipErrorInvalidValue;
     int dev = 0, cus = 0;
     const hipError_t e = current_device_cus(&dev, &cus);
