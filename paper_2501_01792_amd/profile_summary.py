@@ -28,7 +28,7 @@ SCRATCH = os.path.join("gpurun_out", "prof")      # raw profiler output, relativ
 
 KERNELS = ("column_product|paged_scores|paged_index|paged_prefix|paged_append|row_stats|absorbed_scores_block|"
            "absorbed_scores|absorbed_softmax|absorbed_project_block|absorbed_project|absorbed_join|absorbed_stream|"
-           "qkv_block|qkv_fused|ln_rows|qkv_finish|paged_decode|paged_merge|kv_gemm_fold|kv_gemm|prepare_layer|"
+           "qkv_fused|qkv_norm|qkv_stream|qkv_finish|paged_decode|paged_merge|kv_gemm_fold|kv_gemm_tile|kv_gemm|prepare_layer|"
            "flash_decode|merge_partials|segment_join|mfma_rate|ln_stats[a-z_]*")
 
 # counter groups, each within what one pass can hold (8 SQ, 4 TCC, 2 GRBM)
