@@ -14,7 +14,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libhybridkv.so")
 PROBE_SRC = [os.path.join(HERE, "probe", "mfma_rate.hip"),     # measurement aids: a library of their own
-             os.path.join(HERE, "probe", "read_rate.hip")]
+             os.path.join(HERE, "probe", "read_rate.hip"),
+             os.path.join(HERE, "probe", "tile_forms.hip")]    # launches the product library's kernels
 PROBE_LIB = os.path.join(HERE, "probe", "libhkprobe.so")
 PROBE_LT_SRC = os.path.join(HERE, "probe", "library_gemm.hip")  # the vendor GEMM's candidate kernels, timed (links hipBLASLt)
 PROBE_LT_LIB = os.path.join(HERE, "probe", "libhkprobe_lt.so")
@@ -49,7 +50,9 @@ def build(verbose: bool = False) -> str:
     subprocess.check_call([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", tmp])
     os.replace(tmp, LIB)
     tmp = PROBE_LIB + ".tmp%d" % os.getpid()
-    r = subprocess.run([HIPCC, *FLAGS, "-shared", *PROBE_SRC, "-o", tmp], capture_output=True, text=True)
+    r = subprocess.run([HIPCC, *FLAGS, "-shared", *PROBE_SRC, "-o", tmp, "-L" + HERE, "-l:" + os.path.basename(LIB),
+                        "-Wl,-rpath,$ORIGIN/.."],
+                       capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("hipcc failed for %s:\n%s\n%s" % (PROBE_SRC, r.stdout, r.stderr))
     os.replace(tmp, PROBE_LIB)

@@ -56,6 +56,8 @@ bool kv_gemm_takes_prepared(int64_t M, int d, int tile, int dtype = 0);
 hipError_t launch_kv_gemm_fold(const KvGemmArgs &a, hipStream_t s);
 // The folded product on the tile size that suits the problem, 32 x 32 to 256 x 256 (the same bits with any of them).
 hipError_t launch_kv_gemm_prepared(const KvGemmArgs &a, hipStream_t s);
+// The same on the form of that index in kv_gemm_forms.h.
+hipError_t launch_kv_gemm_form(const KvGemmArgs &a, int form, hipStream_t s);
 // Fills Wp, cvec, bvec from the layer's parameters.
 hipError_t launch_prepare_layer(const void *Wkv, const void *bkv, const void *ln_w, const void *ln_b,
                                 void *Wp, float *cvec, float *bvec, int d, hipStream_t s, int dtype = 0);

@@ -262,13 +262,18 @@ static_assert(sizeof(kLaunch) / sizeof(kLaunch[0]) == forms::kCount, "one kernel
 
 }  // namespace
 
+hipError_t launch_kv_gemm_form(const KvGemmArgs &a, int form, hipStream_t s)
+{
+    if (a.M <= 0 || a.d % kTileBK != 0 || form < 0 || form >= forms::kCount) return hipErrorInvalidValue;
+    return kLaunch[form](a, s);
+}
+
 hipError_t launch_kv_gemm_prepared(const KvGemmArgs &a, hipStream_t s)
 {
-    if (a.d % kTileBK != 0) return hipErrorInvalidValue;
     int dev = 0, cus = 0;
     const hipError_t e = current_device_cus(&dev, &cus);
     if (e != hipSuccess) return e;
-    return kLaunch[forms::pick(a.M, a.d, cus)](a, s);
+    return launch_kv_gemm_form(a, forms::pick(a.M, a.d, cus), s);
 }
 
 }  // namespace hk

@@ -7,8 +7,10 @@
     python -m paper_2501_01792_amd.measure overlap [--config opt6.7b] [--iters 20]
     python -m paper_2501_01792_amd.measure gemm    [--config opt66b] [--iters 6]
     python -m paper_2501_01792_amd.measure read    [--config opt66b] [--iters 5]
+    python -m paper_2501_01792_amd.measure tiles
+    python -m paper_2501_01792_amd.measure qkvlines
 
-Each prints one JSON line.  Inputs are drawn on the GPU with the scales of the benchmark recipe (timing only;
+Each prints one JSON line (``tiles`` and ``qkvlines`` a table in front of it).  Inputs are drawn on the GPU with the scales of the benchmark recipe (timing only;
 parity is the tests' business).  ``qkv`` measures hk_qkv_current (Sec. 4.2.2, QKV generation of the current
 token) COLD: the weights of one layer fit in the 256 MB last-level cache, which a real decoder of dozens of
 layers would have evicted by the time a layer comes round again, so a 512 MiB buffer is read between calls.
@@ -23,6 +25,10 @@ regeneration GEMM (all of its tokens as checkpoints) alternately with a plain li
 (torch.addmm, i.e. hipBLASLt: no LayerNorm, row-major output), as a comparator for what this GPU sustains on the shape.
 ``read`` measures how fast the workload's checkpoint rows stream from HBM with the load structure of the streaming
 kernels (32 rows per wavefront, 20 KiB in flight each) for four shapes of one load instruction, plain and non-temporal.
+``tiles`` measures the projection on a prepared layer (with its row statistics) on every tile form over widths and numbers
+of tokens, beside the form that the library takes.  ``qkvlines`` measures hk_qkv_current as a single kernel (a workspace of
+256 bytes) against the form that it takes with the workspace it asks for, over widths and rows, Q + K + V and Q alone, new
+weights in every call; only sizes where the two differ are printed.
 """
 import argparse
 import json
@@ -374,9 +380,88 @@ def measure_read(args):
     return 0
 
 
+def _replayed_us(calls, reps=5):
+    """Median microseconds of a call: all of ``calls`` captured in one graph, replayed ``reps`` times."""
+    import torch
+    for c in calls:
+        c()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        for c in calls:
+            c()
+    graph.replay()
+    torch.cuda.synchronize()
+    ts = []
+    for _ in range(reps):
+        e0, e1 = _events(torch)
+        e0.record(); graph.replay(); e1.record()
+        torch.cuda.synchronize()
+        ts.append(e0.elapsed_time(e1) * 1e3 / len(calls))
+    return float(np.median(ts))
+
+
+def measure_tiles(args):
+    import torch
+    from . import binding as hk, probe
+    forms = probe.tile_forms()
+    print("us a call (row statistics + projection), * = the form that the library takes, + = the fastest")
+    print("%-5s %5s %6s " % ("type", "d", "M") + " ".join("%9s" % ("%dx%d" % f) for f in forms) + "   taken / fastest")
+    worst, rows = 0.0, 0
+    for el, name in ((torch.float16, "f16"), (torch.bfloat16, "bf16")):
+        for d, H in ((768, 12), (1536, 12), (4096, 32), (5120, 40), (7168, 56), (9216, 72)):
+            n = lambda *s, std=1.0, mean=0.0: torch.empty(s, dtype=el, device="cuda").normal_(mean, std)
+            prep = hk.prepare_layer(n(d, std=0.02, mean=1.0), n(d, std=0.02), n(2 * d, d, std=0.02), n(2 * d, std=0.01), H)
+            for M in (8, 64, 128, 256, 512, 1024, 2048, 3072):
+                act, K, V = n(M, d), n(M, d), n(M, d)
+                stats = torch.empty(2 * M, dtype=torch.float32, device="cuda")
+                us = [_replayed_us([lambda: probe.tile_form_run(f, act, H, prep, stats, K, V)] * 10) for f in range(len(forms))]
+                taken, best = probe.tile_form_pick(M, d), int(np.argmin(us))
+                mark = lambda i: "*" if i == taken else "+" if i == best else " "
+                print("%-5s %5d %6d " % (name, d, M) + " ".join("%8.1f%s" % (t, mark(i)) for i, t in enumerate(us)) +
+                      "   %.2f" % (us[taken] / us[best]), flush=True)
+                worst, rows = max(worst, us[taken] / us[best]), rows + 1
+    print(json.dumps({"entry": "projection on a prepared layer, every tile form", "sizes": rows, "worst_taken_over_fastest": worst}))
+    return 0
+
+
+def measure_qkvlines(args):
+    import torch
+    from . import binding as hk
+    print("us a call: single kernel -> the form taken")
+    print("%-5s %5s %4s  %18s  %18s" % ("type", "d", "B", "Q + K + V", "Q alone"))
+    worst, rows = 0.0, 0
+    for el, name in ((torch.float16, "f16"), (torch.bfloat16, "bf16")):
+        for d, dh in ((768, 64), (1280, 64), (2048, 128), (2112, 64), (4096, 128), (5120, 128), (5504, 64), (5632, 128), (6144, 128),
+                      (7168, 128), (7232, 64), (8128, 64), (8192, 128), (8256, 64), (8448, 128), (8768, 64), (9152, 64), (9216, 128)):
+            H = d // dh
+            n = lambda *s, std=1.0, mean=0.0: torch.empty(s, dtype=el, device="cuda").normal_(mean, std)
+            sets = max(2, min(24, int(1.2e9 // (6 * d * d)) + 1))          # 1.2 GB of weights: none is in a cache twice
+            W = [(n(2 * d, d, std=0.02), n(d, d, std=0.02)) for _ in range(sets)]
+            ln_w, ln_b, bkv, bq = n(d, std=0.02, mean=1.0), n(d, std=0.02), n(2 * d, std=0.01), n(d, std=0.01)
+            for B in (1, 8, 32, 33, 48, 64, 65, 80, 96, 97, 128):
+                need = hk.hk_qkv_workspace_bytes(hk.make_shape(d, H, dtype=1 if el == torch.bfloat16 else 0), B)
+                if need <= 256:
+                    continue
+                x, q = n(B, d), torch.empty(B, H, dh, dtype=el, device="cuda")
+                K, V = (torch.empty(B, H, 4, dh, dtype=el, device="cuda") for _ in range(2))
+                us = []
+                for Kd, Vd in ((K, V), (None, None)):
+                    for nbytes in (256, need):
+                        ws = hk.new_workspace(nbytes)
+                        calls = [(lambda w=w: hk.qkv_current(x, ln_w, ln_b, w[0], bkv, w[1], bq, H, q_out=q, K_dst=Kd, V_dst=Vd,
+                                                             tok_pos=1, workspace=ws)) for w in W]
+                        us.append(_replayed_us(calls))
+                print("%-5s %5d %4d  %7.1f -> %7.1f  %7.1f -> %7.1f" % (name, d, B, *us), flush=True)
+                worst, rows = max(worst, us[1] / us[0], us[3] / us[2]), rows + 1
+    print(json.dumps({"entry": "hk_qkv_current, single kernel against three launches", "sizes": rows,
+                      "worst_taken_over_single_kernel": worst}))
+    return 0
+
+
 def main():
     ap = argparse.ArgumentParser(description=__doc__, formatter_class=argparse.RawDescriptionHelpFormatter)
-    ap.add_argument("what", choices=["qkv", "paged", "loop", "overlap", "gemm", "read"])
+    ap.add_argument("what", choices=["qkv", "paged", "loop", "overlap", "gemm", "read", "tiles", "qkvlines"])
     ap.add_argument("--config", default=None)
     ap.add_argument("--iters", type=int, default=20)
     ap.add_argument("--block-tokens", type=int, default=16)
@@ -405,6 +490,10 @@ def main():
         return measure_overlap(args)
     if args.what == "read":
         return measure_read(args)
+    if args.what == "tiles":
+        return measure_tiles(args)
+    if args.what == "qkvlines":
+        return measure_qkvlines(args)
     if args.what == "gemm":
         args.config = args.config or "opt66b"
         if args.iters == 20:

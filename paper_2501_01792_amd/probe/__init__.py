@@ -1,5 +1,6 @@
-"""Measurement aids: what a loop of nothing but fp16 MFMAs sustains on the GPU at hand (the benchmark prints it), and
-the rate at which row-major rows stream from HBM for different shapes of one load instruction (``measure read``).
+"""Measurement aids: what a loop of nothing but fp16 MFMAs sustains on the GPU at hand (the benchmark prints it), the
+rate at which row-major rows stream from HBM for different shapes of one load instruction (``measure read``), and the
+projection with its tile given instead of chosen (``measure tiles``).
 
 Its own small library (libhkprobe.so, built by ``paper_2501_01792_amd.build``), kept apart from the product
 library: it is no operation of the method and synchronises the stream.
@@ -27,7 +28,42 @@ def _load():
         _lib.hkprobe_read_rate.restype = ctypes.c_int
         _lib.hkprobe_read_rate.argtypes = [ctypes.c_int32, ctypes.c_int32, ctypes.c_void_p, ctypes.c_int32, ctypes.c_int32,
                                            ctypes.c_void_p, ctypes.c_int32, ctypes.POINTER(ctypes.c_float), ctypes.c_void_p]
+        _lib.hkprobe_tile_form_pick.argtypes = [ctypes.c_int64, ctypes.c_int32, ctypes.c_int32]
+        _lib.hkprobe_tile_form_tile.argtypes = [ctypes.c_int32, ctypes.POINTER(ctypes.c_int32), ctypes.POINTER(ctypes.c_int32)]
+        _lib.hkprobe_tile_form_run.argtypes = [ctypes.c_int32, ctypes.c_void_p, ctypes.c_int64, ctypes.c_int32, ctypes.c_int32, ctypes.c_int32,
+                                               ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p]
     return _lib
+
+
+def tile_forms():
+    """The (rows, features) of every tile form of the projection on a prepared layer, in the library's order."""
+    lib = _load()
+    out = []
+    for i in range(lib.hkprobe_tile_form_count()):
+        bm, bn = ctypes.c_int32(), ctypes.c_int32()
+        lib.hkprobe_tile_form_tile(i, ctypes.byref(bm), ctypes.byref(bn))
+        out.append((bm.value, bn.value))
+    return out
+
+
+def tile_form_pick(M: int, d: int) -> int:
+    """The form that the library takes on this GPU."""
+    import torch
+    return int(_load().hkprobe_tile_form_pick(M, d, torch.cuda.get_device_properties(0).multi_processor_count))
+
+
+def tile_form_run(form: int, act, n_heads: int, prepared, stats, K, V):
+    """Row statistics and projection of ``act[M, d]`` on tile form ``form``, enqueued on the current stream.  ``stats``: scratch
+    of 8 M bytes; ``K``, ``V``: M d elements each."""
+    import torch
+    M, d = act.shape
+    if not all(t.is_cuda and t.is_contiguous() for t in (act, prepared, stats, K, V)) or K.numel() < M * d or V.numel() < M * d \
+            or stats.numel() * stats.element_size() < 8 * M or act.dtype != K.dtype or act.dtype != V.dtype:
+        raise ValueError("contiguous GPU tensors of the documented sizes")
+    st = _load().hkprobe_tile_form_run(form, act.data_ptr(), M, d, n_heads, 1 if act.dtype == torch.bfloat16 else 0, prepared.data_ptr(),
+                                       stats.data_ptr(), K.data_ptr(), V.data_ptr(), torch.cuda.current_stream().cuda_stream)
+    if st != 0:
+        raise RuntimeError("hkprobe_tile_form_run failed: %d" % st)
 
 
 def read_rate(buf, rows: int, row_bytes: int, rows_per_load: int, nontemporal: bool, iters: int = 5) -> float:
