@@ -7,13 +7,8 @@
 // d = 4096, but a 256 x 256 tile has only 2 k blocks in flight per compute unit and takes 1.2 us for each of them
 // however many of its rows are real, and 32 to 128 of such tiles leave most of the chip idle.  So: smaller tiles until
 // every compute unit has one, and a ring of k blocks as deep as the LDS allows.
-//   * 4 wavefronts, 2 x 2, (BM/2) x (BN/2) accumulators each in 16 x 16 x 32 MFMA blocks; one workgroup per tile.
-//   * A k block (64 reduction elements) of both operands is one stage of an LDS ring of NS stages, filled by direct
-//     loads (16 bytes per lane, 8 lanes per 128-byte line, XOR swizzle of the chunk index applied on the global side).
-//     All NS stages are asked for before the first is used.
-//   * Fragments are double-buffered in registers: the reads of a half k block run under the MFMAs of the half before.
-//     One barrier per k block, in its middle, where the next block must have landed and the slot of the current one,
-//     whose last fragments are in registers, is free for block kb + NS.
+//   * The main loop is that of mma_ring.h: a k block (64 reduction elements) of both operands is one stage of an LDS ring
+//     of NS stages filled by direct loads, all NS asked for before the first is used.
 //   * Tiles are walked column panel by column panel over up to 8 row tiles inside an XCD: a weight panel leaves HBM once.
 // Measured with its row statistics (ln_stats, 4 to 6 us of it), fp16, against the 128 x 128 kernel with the LayerNorm
 // prologue / the 256 x 256 kernel: d = 4096, M = 64: 24.6 us (93.6 / 75.3); M = 512: 45.6 (93.9 / 79.1); M = 1024: 67.5
@@ -22,32 +17,15 @@
 #include "elem.h"
 #include "kv_gemm_common.h"
 #include "kv_gemm_forms.h"
-
-#include <type_traits>
+#include "mma_ring.h"
 
 namespace hk {
 namespace {
 
 using namespace gemm;
 
-constexpr int kTileBK = 64;                                 // reduction elements of a k block: 128-byte LDS rows
-constexpr int kTileRow = kTileBK * 2;
-
-typedef __attribute__((address_space(3))) void *lds_ptr_t;
-
 template <int BM, int BN, int NS>
-constexpr int tile_lds_bytes() { return NS * (BM + BN) * kTileRow + BM * (int)sizeof(RowDst); }
-
-// Waits until at most r (<= R) of the youngest k blocks this wavefront has asked for, LPS loads each, are in flight.
-template <int R, int LPS>
-__device__ __forceinline__ void wait_blocks(int r)
-{
-    if constexpr (R > 0) {
-        if (r < R) return wait_blocks<R - 1, LPS>(r);
-    }
-    static_assert(R * LPS <= 63, "vmcnt counts to 63");
-    __builtin_amdgcn_s_waitcnt((R * LPS & 15) | ((R * LPS >> 4) << 14) | 0x0F70);   // vmcnt(R * LPS)
-}
+constexpr int tile_lds_bytes() { return ring::lds_bytes<BM, BN, NS>() + BM * (int)sizeof(RowDst); }
 
 template <int BM, int BN, int NS, int DT>
 __global__ __launch_bounds__(256, BM * BN <= 128 * 128 ? 2 : 1) void kv_gemm_tile_kernel(
@@ -58,16 +36,14 @@ __global__ __launch_bounds__(256, BM * BN <= 128 * 128 ? 2 : 1) void kv_gemm_til
 {
 #if defined(__HIP_DEVICE_COMPILE__)                            // (the host pass drops the kernel's stub over a direct load in this body)
     typedef typename Elem<DT>::T elem_t;
-    typedef typename Elem<DT>::V8 vec8_t;
+    typedef ring::Ring<BM, BN, NS, DT> ring_t;
     extern __shared__ __align__(16) unsigned char smem[];
-    constexpr int LA = BM / 32, LB = BN / 32, LPS = LA + LB;   // direct loads of a lane per k block
-    constexpr int TM = BM / 32, TN = BN / 32;                  // 16 x 16 MFMA blocks of a wavefront (2 x 2 wavefronts)
-    constexpr int kStage = (BM + BN) * kTileRow;
+    constexpr int LA = ring_t::kLoadsA, LB = ring_t::kLoadsB, TM = ring_t::TM, TN = ring_t::TN;
     const int N = 2 * d;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 1, wn = wave & 1;
-    const int nks = d / kTileBK;
+    const int nks = d / ring::kBlockK;
 
     int tm, tn;
     tile_coords<8>((int)blockIdx.x, tiles_m, tiles_n, tm, tn);
@@ -88,10 +64,8 @@ __global__ __launch_bounds__(256, BM * BN <= 128 * 128 ? 2 : 1) void kv_gemm_til
         bn[j] = nb < N ? bvec[nb + j] : 0.f;
     }
 
-    // ---- direct loads: load i of wavefront w fills LDS rows 8 (w + 4 i) .. + 7 of a unit; lane l writes row l / 8,
-    // physical chunk l % 8, and fetches logical chunk (l % 8) ^ ((row / 2) % 8), so 8 lanes fetch one 128-byte line
-    const int l_row = 8 * wave + (lane >> 3);
-    const int l_chunk = (lane & 7) ^ ((4 * (wave & 1) + (lane >> 4)) & 7);
+    // ---- direct loads; rows past the end are clamped to the last one
+    ring_t r(smem, tid, wave);
     int64_t a_bytes = (M - m0) * (int64_t)d * 2, b_bytes = ((int64_t)N - n0) * d * 2;
     if (a_bytes > 0x7fffffff) a_bytes = 0x7fffffff;            // a tile spans < 2^30 bytes
     if (b_bytes > 0x7fffffff) b_bytes = 0x7fffffff;
@@ -101,100 +75,34 @@ __global__ __launch_bounds__(256, BM * BN <= 128 * 128 ? 2 : 1) void kv_gemm_til
     const int rb = N - n0 < BN ? N - n0 - 1 : BN - 1;
     int a_voff[LA], b_voff[LB];
 #pragma unroll
-    for (int i = 0; i < LA; ++i) {
-        const int r = l_row + 32 * i;
-        a_voff[i] = ((r < ra ? r : ra) * d + l_chunk * 8) * 2;
-    }
+    for (int i = 0; i < LA; ++i) a_voff[i] = ((r.a_row(i) < ra ? r.a_row(i) : ra) * d + r.lane_chunk * 8) * 2;
 #pragma unroll
-    for (int i = 0; i < LB; ++i) {
-        // LDS row rho of the weight unit: wavefront column rho / (BN/2), MFMA block j, block column c; it holds weight
-        // row (BN/2) (rho / (BN/2)) + TN c + j, so that a lane ends up with TN consecutive features
-        const int rho = l_row + 32 * i;
-        const int w = rho / (BN / 2), in = rho % (BN / 2);
-        const int r = w * (BN / 2) + TN * (in & 15) + (in >> 4);
-        b_voff[i] = ((r < rb ? r : rb) * d + l_chunk * 8) * 2;
-    }
+    for (int i = 0; i < LB; ++i) b_voff[i] = ((r.b_row(i) < rb ? r.b_row(i) : rb) * d + r.lane_chunk * 8) * 2;
     auto issue = [&](int slot, int kb, int i) {
-        unsigned char *dst = smem + slot * kStage + wave * 1024;
         // weights first: they come from HBM, the activations mostly from L2
         if (i < LB)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(b_rsrc, (lds_ptr_t)(dst + BM * kTileRow + i * 4096), 16, b_voff[i], kb * kTileRow, 0, 0);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(b_rsrc, r.b_dst(slot, i), 16, b_voff[i], kb * ring::kRowBytes, 0, 0);
         else
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, (lds_ptr_t)(dst + (i - LB) * 4096), 16, a_voff[i - LB], kb * kTileRow, 0, 0);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, r.a_dst(slot, i - LB), 16, a_voff[i - LB], kb * ring::kRowBytes, 0, 0);
     };
 
-    // ---- fragment reads: row lane % 16 (+ 16 i) of the wavefront's part, logical chunk 4 ks + lane / 16
-    const int fr = lane & 15, fc = lane >> 4;
-    int frag_off[2];
-#pragma unroll
-    for (int ks = 0; ks < 2; ++ks) frag_off[ks] = fr * kTileRow + (((4 * ks + fc) ^ ((fr >> 1) & 7)) << 4);
-    const int a_rd = wm * (BM / 2) * kTileRow, b_rd = BM * kTileRow + wn * (BN / 2) * kTileRow;
-    vec8_t fa[2][TM], fb[2][TN];
-    auto read_frag = [&](int ks, int slot, int which) {        // in the order the MFMAs need them: a[0], b[..], a[1..]
-        const unsigned char *src = smem + slot * kStage + frag_off[ks];
-        if (which == 0 || which > TN) {
-            const int i = which == 0 ? 0 : which - TN;
-            fa[ks][i] = *reinterpret_cast<const vec8_t *>(src + a_rd + i * (16 * kTileRow));
-        } else {
-            fb[ks][which - 1] = *reinterpret_cast<const vec8_t *>(src + b_rd + (which - 1) * (16 * kTileRow));
-        }
-    };
-
-    float4_t acc[TM][TN];
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = float4_t{0.f, 0.f, 0.f, 0.f};
-
+    r.clear();
     for (int s = 0; s < NS; ++s) {
         if (s < nks) {
 #pragma unroll
-            for (int i = 0; i < LPS; ++i) issue(s, s, i);
+            for (int i = 0; i < ring_t::kLoads; ++i) issue(s, s, i);
         }
     }
-    wait_blocks<NS - 1, LPS>(nks < NS ? nks - 1 : NS - 1);
-    asm volatile("s_barrier" ::: "memory");
-#pragma unroll
-    for (int q = 0; q < TM + TN; ++q) read_frag(0, 0, q);
-
-    constexpr int kMma = TM * TN, kFrags = TM + TN;
-    constexpr int kSlotsA = kMma > kFrags ? kMma : kFrags;
-    constexpr int kSlotsB = kSlotsA > LPS ? kSlotsA : LPS;
-    int cur = 0;
-    // One k block (kind 0: last; 1: a next block exists; 2: and block kb + NS exists).  Its first half multiplies
-    // fragments that are in registers already and reads those of the second half; then this wavefront waits for its
-    // loads of block kb + 1 and meets the others, after which block kb + 1 is complete in LDS and block kb's slot
-    // (every read of it has come back) takes block kb + NS; the second half reads the first fragments of block kb + 1.
-    auto block = [&](auto kind, int kb) {
-        constexpr int KIND = decltype(kind)::value;
-        const int nxt = cur + 1 == NS ? 0 : cur + 1;
-#pragma unroll
-        for (int q = 0; q < kSlotsA; ++q) {
-            if (q < kMma) acc[q / TN][q % TN] = Elem<DT>::mfma_16x16x32(fa[0][q / TN], fb[0][q % TN], acc[q / TN][q % TN]);
-            if (q < kFrags) read_frag(1, cur, q);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        if constexpr (KIND == 2) wait_blocks<NS - 2, LPS>(NS - 2);
-        if constexpr (KIND == 1) wait_blocks<NS - 2, LPS>(nks - 2 - kb);
-        if constexpr (KIND > 0) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int q = 0; q < kSlotsB; ++q) {
-            if (q < kMma) acc[q / TN][q % TN] = Elem<DT>::mfma_16x16x32(fa[1][q / TN], fb[1][q % TN], acc[q / TN][q % TN]);
-            if (KIND > 0 && q < kFrags) read_frag(0, nxt, q);
-            if (KIND == 2 && q < LPS) issue(cur, kb + NS, q);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        cur = nxt;
-    };
+    r.start(nks);
     int kb = 0;
-    for (; kb + NS < nks; ++kb) block(std::integral_constant<int, 2>{}, kb);
-    for (; kb + 1 < nks; ++kb) block(std::integral_constant<int, 1>{}, kb);
-    block(std::integral_constant<int, 0>{}, kb);
+    auto next = [&](int slot, int i) { issue(slot, kb + NS, i); };
+    for (; kb + NS < nks; ++kb) r.template block<2>(next, 0);
+    for (; kb + 1 < nks; ++kb) r.template block<1>(next, nks - 2 - kb);
+    r.template block<0>(next, 0);
 
     // ---- statistics, constants of the layer, 16-bit rounding, head split.  Rows past the last token stand for it (their
     // operand loads were clamped to its row): they store the same bytes to the same place.
-    RowDst *tab = reinterpret_cast<RowDst *>(smem + NS * kStage);
+    RowDst *tab = reinterpret_cast<RowDst *>(smem + NS * ring_t::kStage);
     if (tid < BM) tab[tid] = my_row;
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     if (nb >= N) return;
@@ -207,12 +115,12 @@ __global__ __launch_bounds__(256, BM * BN <= 128 * 128 ? 2 : 1) void kv_gemm_til
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const RowDst row = my[16 * i + r];
+        for (int e4 = 0; e4 < 4; ++e4) {
+            const RowDst row = my[16 * i + e4];
             out_t v;
 #pragma unroll
             for (int j = 0; j < TN; ++j)
-                v[j] = __builtin_bit_cast(unsigned short, (elem_t)__builtin_fmaf(acc[i][j][r], row.rstd, __builtin_fmaf(row.nmr, cn[j], bn[j])));
+                v[j] = __builtin_bit_cast(unsigned short, (elem_t)__builtin_fmaf(r.acc[i][j][e4], row.rstd, __builtin_fmaf(row.nmr, cn[j], bn[j])));
             __builtin_nontemporal_store(v, reinterpret_cast<out_t *>(dst_base + row.base));
         }
 #endif
@@ -264,7 +172,7 @@ static_assert(sizeof(kLaunch) / sizeof(kLaunch[0]) == forms::kCount, "one kernel
 
 hipError_t launch_kv_gemm_form(const KvGemmArgs &a, int form, hipStream_t s)
 {
-    if (a.M <= 0 || a.d % kTileBK != 0 || form < 0 || form >= forms::kCount) return hipErrorInvalidValue;
+    if (a.M <= 0 || a.d % ring::kBlockK != 0 || form < 0 || form >= forms::kCount) return hipErrorInvalidValue;
     return kLaunch[form](a, s);
 }
 

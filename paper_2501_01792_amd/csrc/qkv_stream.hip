@@ -13,18 +13,18 @@
 //     the same work whatever the number of tiles; a run leaves one fp32 part per tile that it meets, and the order in
 //     which parts are added is fixed by the sizes.  The cut is that of Q, K and V also where only Q is asked for: q must
 //     not depend on whether K / V rows are produced.
-//   * Both operands of a unit are one stage of an LDS ring filled by direct loads (16 bytes per lane, 8 lanes per
-//     128-byte line, XOR swizzle on the global side); the ring runs on across tiles, so the loads never drain.
+//   * Both operands of a unit are one stage of the LDS ring of mma_ring.h, which runs on across tiles, so the loads never
+//     drain.
 //   * The weights are asked for non-temporally: xhat (up to 2.4 MB), which every workgroup reads once per tile, stays in
 //     L2 (d = 7168, B = 32: 70 -> 61 us).  64-feature units read xhat twice as often (B = 128: 95 us against 87).
-//   * 4 wavefronts, 2 x 2; fragments double-buffered in registers, one barrier per unit, as in kv_gemm_tile.hip.  One
-//     workgroup with a ring as deep as the LDS allows beat two with half of it each (B = 64: 69 us against 71).
+//   * One workgroup with a ring as deep as the LDS allows beat two with half of it each (B = 64: 69 us against 71).
 //   * Non-temporal stores of the parts were slower (B = 64, d = 7168: 74 us): the finishing kernel finds them in cache.
 // Measured, fp16, Q + K + V, new weights in every call, against the one-launch kernel: d = 7168, B = 32 / 64 / 128: 60 / 69 /
 // 87 us (79 / 105 / 110; 308 MB of weights); d = 4096, B = 128: 38 (68); d = 9216, B = 128: 134 (152).  Error against 64
 // bits 2.9e-4 (3.6e-4: two roundings on the way into the product); bf16 2.35e-3 (2.8e-3).
 #include "hk_internal.h"
 #include "elem.h"
+#include "mma_ring.h"
 #include "qkv_dst.h"
 
 #include <type_traits>
@@ -32,10 +32,7 @@
 namespace hk {
 namespace {
 
-typedef __attribute__((address_space(3))) void *lds_ptr_t;
-
-constexpr int kUnitK = 64;                                  // reduction elements of a unit: 128-byte LDS rows
-constexpr int kRowBytes = kUnitK * 2;
+constexpr int kUnitK = ring::kBlockK;                       // reduction elements of a unit: a block of the ring
 constexpr int kStreamed = 2;                                // cache policy of the weight loads: non-temporal, the rows stay in L2
 constexpr int kMinRun = 4;                                  // fewest units of a run worth a part of its own
 
@@ -125,18 +122,6 @@ __global__ __launch_bounds__(256) void qkv_norm_kernel(const typename Elem<DT>::
         if (tid + 256 * i < nvec) put(v[i], tid + 256 * i);
 }
 
-// Waits until at most r (<= R) of the youngest units this wavefront has asked for, LPS loads each, are in flight (stores
-// of parts count too: the wait is then for more than it needs).
-template <int R, int LPS>
-__device__ __forceinline__ void wait_units(int r)
-{
-    if constexpr (R > 0) {
-        if (r < R) return wait_units<R - 1, LPS>(r);
-    }
-    static_assert(R * LPS <= 63, "vmcnt counts to 63");
-    __builtin_amdgcn_s_waitcnt((R * LPS & 15) | ((R * LPS >> 4) << 14) | 0x0F70);   // vmcnt(R * LPS)
-}
-
 struct StreamArgs {
     const void *xhat, *Wq, *Wkv;
     float *part;
@@ -144,50 +129,35 @@ struct StreamArgs {
     int split;                                                 // workgroups that share a run: each takes BN features of its tiles
 };
 
-template <int BM, int BN, int NS>
-constexpr int stream_lds_bytes() { return NS * (BM + BN) * kRowBytes; }
 // Workgroups of a compute unit: two where the LDS of one allows it.
 template <int BM, int BN, int NS>
-constexpr int stream_per_cu() { return stream_lds_bytes<BM, BN, NS>() <= 80 * 1024 ? 2 : 1; }
+constexpr int stream_per_cu() { return ring::lds_bytes<BM, BN, NS>() <= 80 * 1024 ? 2 : 1; }
 
 template <int BM, int BN, int NS, int DT>
 __global__ __launch_bounds__(256, (stream_per_cu<BM, BN, NS>())) void qkv_stream_kernel(StreamArgs p)
 {
 #if defined(__HIP_DEVICE_COMPILE__)                            // (the host pass drops the kernel's stub over a direct load in this body)
     typedef typename Elem<DT>::T elem_t;
-    typedef typename Elem<DT>::V8 vec8_t;
+    typedef ring::Ring<BM, BN, NS, DT> ring_t;
     extern __shared__ __align__(16) unsigned char smem[];
-    constexpr int LA = BM / 32, LB = BN / 32, LPS = LA + LB;   // direct loads of a lane per unit
-    constexpr int TM = BM / 32, TN = BN / 32;                  // 16 x 16 MFMA blocks of a wavefront (2 x 2 wavefronts)
-    constexpr int kStage = (BM + BN) * kRowBytes;
-    const int tid = threadIdx.x, lane = tid & 63;
+    constexpr int LA = ring_t::kLoadsA, LB = ring_t::kLoadsB, TM = ring_t::TM, TN = ring_t::TN;
+    const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave >> 1, wn = wave & 1;
     const int d = p.d, nks = p.nks;
     const int run = (int)blockIdx.x / p.split, part = (int)blockIdx.x % p.split;
     const int u_begin = run_begin(run, p.units, p.runs);
     const int u_end = run_begin(run + 1, p.units, p.runs);
     const int n = (u_end < p.live ? u_end : p.live) - u_begin; // >= 1: no more runs than units, none past the live ones
 
-    // ---- direct loads: load i of wavefront w fills LDS rows 8 (w + 4 i) .. + 7 of an operand; lane l writes row l / 8,
-    // physical chunk l % 8, and fetches logical chunk (l % 8) ^ ((row / 2) % 8), so 8 lanes fetch one 128-byte line
-    const int l_row = 8 * wave + (lane >> 3);
-    const int l_chunk = (lane & 7) ^ ((4 * (wave & 1) + (lane >> 4)) & 7);
+    ring_t r(smem, tid, wave);
     const __amdgpu_buffer_rsrc_t a_rsrc =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<elem_t *>(static_cast<const elem_t *>(p.xhat)), 0, p.B * d * 2, 0x00020000);
     int a_voff[LA], b_voff[LB];
 #pragma unroll
-    for (int i = 0; i < LA; ++i) {
-        const int r = l_row + 32 * i;
-        a_voff[i] = ((r < p.B ? r : p.B - 1) * d + l_chunk * 8) * 2;   // rows past the end: the last row, never stored
-    }
+    for (int i = 0; i < LA; ++i)                               // rows past the end: the last row, never stored
+        a_voff[i] = ((r.a_row(i) < p.B ? r.a_row(i) : p.B - 1) * d + r.lane_chunk * 8) * 2;
 #pragma unroll
-    for (int i = 0; i < LB; ++i) {
-        // LDS row rho: wavefront column rho / (BN/2), MFMA block j, block column c; it holds weight row
-        // (BN/2) (rho / (BN/2)) + TN c + j, so that a lane ends up with TN consecutive features
-        const int rho = l_row + 32 * i, w = rho / (BN / 2), in = rho % (BN / 2);
-        b_voff[i] = ((w * (BN / 2) + TN * (in & 15) + (in >> 4)) * d + l_chunk * 8) * 2;
-    }
+    for (int i = 0; i < LB; ++i) b_voff[i] = (r.b_row(i) * d + r.lane_chunk * 8) * 2;
     // the unit to ask for next: its tile's rows and its place on the reduction axis
     int ask_tile = u_begin / nks, ask_k = u_begin % nks;
     auto tile_rsrc = [&](int tile) {
@@ -197,12 +167,11 @@ __global__ __launch_bounds__(256, (stream_per_cu<BM, BN, NS>())) void qkv_stream
     };
     __amdgpu_buffer_rsrc_t b_rsrc = tile_rsrc(ask_tile);
     auto issue = [&](int slot, int i) {
-        unsigned char *dst = smem + slot * kStage + wave * 1024;
         // weights first: they come from HBM, the rows from L2
         if (i < LB)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(b_rsrc, (lds_ptr_t)(dst + BM * kRowBytes + i * 4096), 16, b_voff[i], ask_k * kRowBytes, 0, kStreamed);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(b_rsrc, r.b_dst(slot, i), 16, b_voff[i], ask_k * ring::kRowBytes, 0, kStreamed);
         else
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, (lds_ptr_t)(dst + (i - LB) * 4096), 16, a_voff[i - LB], ask_k * kRowBytes, 0, 0);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, r.a_dst(slot, i - LB), 16, a_voff[i - LB], ask_k * ring::kRowBytes, 0, 0);
     };
     auto asked = [&](bool more) {                              // more: another unit of this run will be asked for
         if (++ask_k == nks) {
@@ -212,80 +181,29 @@ __global__ __launch_bounds__(256, (stream_per_cu<BM, BN, NS>())) void qkv_stream
         }
     };
 
-    // ---- fragment reads: row lane % 16 (+ 16 i) of the wavefront's part, logical chunk 4 ks + lane / 16
-    const int fr = lane & 15, fc = lane >> 4;
-    int frag_off[2];
-#pragma unroll
-    for (int ks = 0; ks < 2; ++ks) frag_off[ks] = fr * kRowBytes + (((4 * ks + fc) ^ ((fr >> 1) & 7)) << 4);
-    const int a_rd = wm * (BM / 2) * kRowBytes, b_rd = BM * kRowBytes + wn * (BN / 2) * kRowBytes;
-    vec8_t fa[2][TM], fb[2][TN];
-    auto read_frag = [&](int ks, int slot, int which) {        // in the order the MFMAs need them: a[0], b[..], a[1..]
-        const unsigned char *src = smem + slot * kStage + frag_off[ks];
-        if (which == 0 || which > TN) {
-            const int i = which == 0 ? 0 : which - TN;
-            fa[ks][i] = *reinterpret_cast<const vec8_t *>(src + a_rd + i * (16 * kRowBytes));
-        } else {
-            fb[ks][which - 1] = *reinterpret_cast<const vec8_t *>(src + b_rd + (which - 1) * (16 * kRowBytes));
-        }
-    };
-    float4_t acc[TM][TN];
-    auto clear = [&]() {
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j) acc[i][j] = float4_t{0.f, 0.f, 0.f, 0.f};
-    };
-    clear();
-
+    r.clear();
     for (int s = 0; s < NS; ++s) {
         if (s < n) {
 #pragma unroll
-            for (int i = 0; i < LPS; ++i) issue(s, i);
+            for (int i = 0; i < ring_t::kLoads; ++i) issue(s, i);
             asked(s + 1 < n);
         }
     }
-    wait_units<NS - 1, LPS>(n < NS ? n - 1 : NS - 1);
-    asm volatile("s_barrier" ::: "memory");
-#pragma unroll
-    for (int q = 0; q < TM + TN; ++q) read_frag(0, 0, q);
+    r.start(n);
 
-    constexpr int kMma = TM * TN, kFrags = TM + TN;
-    constexpr int kSlotsA = kMma > kFrags ? kMma : kFrags;
-    constexpr int kSlotsB = kSlotsA > LPS ? kSlotsA : LPS;
-    int cur = 0, tile = u_begin / nks, k = u_begin % nks;
-    // One unit (kind 0: the run's last; 1: a next one exists; 2: and unit i + NS exists).  Its first half multiplies
-    // fragments that are in registers already and reads those of the second half; then this wavefront waits for its loads
-    // of unit i + 1 and meets the others, after which that unit is complete in LDS and the slot of unit i (every read of
-    // it has come back) takes unit i + NS; the second half reads the first fragments of unit i + 1.
+    int tile = u_begin / nks, k = u_begin % nks;
+    // One unit (kind as in Ring::block), and the part of a tile that ends with it.
     auto unit = [&](auto kind, int i) {
         constexpr int KIND = decltype(kind)::value;
-        const int nxt = cur + 1 == NS ? 0 : cur + 1;
-#pragma unroll
-        for (int q = 0; q < kSlotsA; ++q) {
-            if (q < kMma) acc[q / TN][q % TN] = Elem<DT>::mfma_16x16x32(fa[0][q / TN], fb[0][q % TN], acc[q / TN][q % TN]);
-            if (q < kFrags) read_frag(1, cur, q);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        if constexpr (KIND == 2) wait_units<NS - 2, LPS>(NS - 2);
-        if constexpr (KIND == 1) wait_units<NS - 2, LPS>(n - 2 - i);
-        if constexpr (KIND > 0) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int q = 0; q < kSlotsB; ++q) {
-            if (q < kMma) acc[q / TN][q % TN] = Elem<DT>::mfma_16x16x32(fa[1][q / TN], fb[1][q % TN], acc[q / TN][q % TN]);
-            if (KIND > 0 && q < kFrags) read_frag(0, nxt, q);
-            if (KIND == 2 && q < LPS) issue(cur, q);
-            __builtin_amdgcn_sched_barrier(0);
-        }
+        r.template block<KIND>(issue, n - 2 - i);
         if constexpr (KIND == 2) asked(i + NS + 1 < n);
-        cur = nxt;
         if (++k == nks || KIND == 0) {                         // the tile ends here for this run: its part leaves
             float4_t *dst = reinterpret_cast<float4_t *>(p.part + (int64_t)((tile + run) * p.split + part) * (BM * BN));
 #pragma unroll
             for (int ii = 0; ii < TM; ++ii)
 #pragma unroll
-                for (int j = 0; j < TN; ++j) dst[(ii * TN + j) * 256 + tid] = acc[ii][j];
-            clear();
+                for (int j = 0; j < TN; ++j) dst[(ii * TN + j) * 256 + tid] = r.acc[ii][j];
+            r.clear();
             k = 0;
             ++tile;
         }
@@ -386,7 +304,7 @@ hipError_t launch_dt(const QkvArgs &a, int cus, hipStream_t s)
     t.live = tiles * t.nks;
     t.runs = stream_runs(t.units, stream_per_cu<BM, BN, NS>() * cus);
     auto kern = qkv_stream_kernel<BM, BN, NS, DT>;
-    constexpr int lds = stream_lds_bytes<BM, BN, NS>();
+    constexpr int lds = ring::lds_bytes<BM, BN, NS>();
     static_assert(lds <= 160 * 1024, "the workgroup must fit the LDS of a compute unit");
     static LdsOnce lds_once;
     e = allow_dynamic_lds(reinterpret_cast<const void *>(kern), lds, lds_once);
