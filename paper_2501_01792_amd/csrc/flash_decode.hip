@@ -12,8 +12,8 @@
 //     A range may cover the end of one pair and the start of the next; for every pair it touches
 //     a wavefront emits one un-normalised partial (m, l, o[dh]) at index (wavefront + pair), which
 //     is unique, and makes the partials of one pair a contiguous run.  A second small kernel
-//     merges the run of every pair by log-sum-exp.  Wavefronts never talk to each other: no LDS,
-//     no barrier.
+//     merges the run of every pair by log-sum-exp.  Wavefronts of this kernel never talk to each other:
+//     no LDS, no barrier.  (Those of the merge may: attn_merge.h.)
 //   * A wavefront consumes 64 tokens at a time (attn_tile.h).  dh/8 lanes cover one row with 16-byte loads, so
 //     every load instruction of a wavefront reads whole, consecutive rows (1 KiB contiguous), and all K and V
 //     loads of the 64 tokens are issued before the first use: 128 registers of rows, 3 wavefronts per SIMD.  Left to
@@ -21,8 +21,9 @@
 //     and in bf16 they were widened on arrival (246 registers, 2 per SIMD).
 //   * Small problems are cut into ranges of one step each, aligned to the pairs, so that they too fill the chip and pay
 //     one latency (with at least 128 tokens per range, 64,000 positions ran on 125 of 256 compute units).
-// Measured (kernel alone): 4.8 GB in 718 us (6.73 TB/s; 731 before all rows were asked for at once), 2.1 GB bf16 in
-// 312 us (6.7 TB/s; 327), 33 MB of one request in 7.8 us (26).
+// Measured with the merge (profiles/decode_attention_cached.txt; in brackets with V asked for behind K, at least 128 tokens a
+// range and a merge that walks the partials one by one): 4.8 GB fp16 727 us, 6.65 TB/s (737), bf16 747 (771); 268 MB 43.9
+// (47.5); 33 MB of one request 9.9 (36.4).
 #include "hk_internal.h"
 #include "elem.h"
 #include "attn_merge.h"

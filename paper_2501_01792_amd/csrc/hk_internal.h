@@ -40,14 +40,14 @@ struct KvGemmArgs {
     int d, n_heads, head_dim;
     int L_act, L_cap, tok_off;
     int tile;              // 0 = choose, else 128 or 256
-    int dtype;             // 0: fp16, 1: bf16 (bf16 always takes the 256 x 256 kernel)
+    int dtype;             // 0: fp16, 1: bf16 (always on a prepared layer)
     int cu_limit = 0;      // > 0: the persistent 256 x 256 kernel uses at most this many compute units (the others stay
                            // free for a kernel on another stream); 0: all of them
 };
 // LayerNorm-fused K/V projection: K_out/V_out rows <- LN(act) x Wkv^T + bkv, head-split.
 hipError_t launch_kv_gemm(const KvGemmArgs &a, hipStream_t s);
-// Whether launch_kv_gemm takes the 256 x 256 streaming kernel for this problem (tile: 0 = choose, 128, 256).
-// That kernel works on a prepared layer (Wp, cvec, bvec), so the caller must supply one.
+// Whether launch_kv_gemm works on a prepared layer (Wp, cvec, bvec) for this problem, so that the caller must supply one
+// (tile: 0 = choose, 128, 256).
 bool kv_gemm_uses_prepared(int64_t M, int d, int tile, int dtype = 0);
 // Whether it takes a form that works on the prepared layer when one is given (and its row statistics then carry the
 // layer's factor).
@@ -79,7 +79,7 @@ struct AttnArgs {
 };
 // Wavefronts of the attention kernels (contiguous and paged) that stay resident together on an MI355X: 256 compute
 // units x 4 SIMDs x 3 wavefronts (a wavefront holds the K and V rows of a whole step, 128 registers of <= 168).
-// 2048, 4096 and 6144 wavefronts were level with 3072 or up to 5 % slower (2.1 GB cached: 329, 331, 331 against 328 us;
+// Builds with 2048, 4096 and 6144 were level with 3072 or up to 5 % slower (2.1 GB cached: 329, 331, 331 against 328 us;
 // 67 MB: 26.9, 27.6, 27.7 against 26.1 us).
 constexpr int kAttnResidentWaves = 256 * 4 * 3;
 constexpr int kAttnMaxWaves = 1 << 20;

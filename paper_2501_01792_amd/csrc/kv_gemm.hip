@@ -188,7 +188,7 @@ hipError_t launch_tile(const KvGemmArgs &a, hipStream_t s)
 
 bool kv_gemm_uses_prepared(int64_t M, int d, int tile, int dtype)
 {
-    if (dtype == 1) return true;                           // bf16: one kernel for every problem size
+    if (dtype == 1) return true;                           // bf16: the folded product for every problem size
     // Large problems: 256x256 tiles (highest reuse per LDS byte).  Problems with too few such tiles to occupy the 256
     // compute units take 128x128 tiles, unless the caller brings a prepared layer (preparing one is a pass over the
     // weights).

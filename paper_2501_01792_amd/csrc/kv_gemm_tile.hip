@@ -10,9 +10,9 @@
 //   * The main loop is that of mma_ring.h: a k block (64 reduction elements) of both operands is one stage of an LDS ring
 //     of NS stages filled by direct loads, all NS asked for before the first is used.
 //   * Tiles are walked column panel by column panel over up to 8 row tiles inside an XCD: a weight panel leaves HBM once.
-// Measured with its row statistics (ln_stats, 4 to 6 us of it), fp16, against the 128 x 128 kernel with the LayerNorm
-// prologue / the 256 x 256 kernel: d = 4096, M = 64: 24.6 us (93.6 / 75.3); M = 512: 45.6 (93.9 / 79.1); M = 1024: 67.5
-// (112 / 86.2); d = 9216, M = 8: 77 (201 / 156); M = 256: 144 (214 / 168); d = 768, M = 512: 9.4 (22.8 / 23.0).
+// Measured with its row statistics, fp16 (profiles/kv_gemm_tile_forms.txt; in brackets the 128 x 128 kernel with the LayerNorm
+// prologue / the 256 x 256 kernel): d = 4096, M = 64: 18.6 us (73 / 71); M = 512: 42 (76 / 73); M = 1024: 67 (102 / 74);
+// d = 9216, M = 8: 72 (201 / 154); M = 256: 147 (210 / 163); d = 768, M = 512: 8.8 (21 / 22).
 #include "hk_internal.h"
 #include "elem.h"
 #include "kv_gemm_common.h"

@@ -11,8 +11,9 @@
 // (wavefront + pair); a second kernel merges each pair's run of partials.  What differs is the address
 // of a token: the block table is read with scalar loads, one entry for every 16 tokens of a step (steps are
 // aligned to 64 tokens inside a pair, so that 16 tokens never straddle a block), during the step before.
-// Measured (kernel alone, 16-token blocks in random order): 403 MB of 32 ragged requests in 69 us (92 before ranges
-// were moved to whole steps and the entries fetched ahead), 3.6 GB in 564 us (592).
+// Measured with the merge (profiles/decode_attention_cached.txt, 16-token blocks in random order; in brackets with ranges
+// that end inside a step, entries fetched when they are needed and a merge that walks the partials one by one): 411 MB of
+// 32 ragged requests 72.8 us (90.5), 7.6 GB 1180 (1212), 33 MB of one request 12.4 (42).
 #include "hk_internal.h"
 #include "elem.h"
 #include "attn_merge.h"
@@ -51,7 +52,6 @@ __global__ __launch_bounds__(kThreads, 3) void paged_decode_kernel(
     int B, int H, int blk_log2, int64_t total_host, const int64_t *__restrict__ total_dev, int W, float scale_log2e,
     float *__restrict__ partial)
 {
-    typedef typename Elem<DT>::T elem_t;
     typedef typename Elem<DT>::V8 half8_t;
     typedef attn::Tile<DH, DT> tile_t;
     constexpr int LPR = tile_t::LPR, RPL = tile_t::RPL, NL = tile_t::NL;

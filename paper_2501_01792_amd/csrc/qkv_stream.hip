@@ -19,9 +19,10 @@
 //     L2 (d = 7168, B = 32: 70 -> 61 us).  64-feature units read xhat twice as often (B = 128: 95 us against 87).
 //   * One workgroup with a ring as deep as the LDS allows beat two with half of it each (B = 64: 69 us against 71).
 //   * Non-temporal stores of the parts were slower (B = 64, d = 7168: 74 us): the finishing kernel finds them in cache.
-// Measured, fp16, Q + K + V, new weights in every call, against the one-launch kernel: d = 7168, B = 32 / 64 / 128: 60 / 69 /
-// 87 us (79 / 105 / 110; 308 MB of weights); d = 4096, B = 128: 38 (68); d = 9216, B = 128: 134 (152).  Error against 64
-// bits 2.9e-4 (3.6e-4: two roundings on the way into the product); bf16 2.35e-3 (2.8e-3).
+// Measured, fp16, Q + K + V, new weights in every call, in brackets the one-launch kernel
+// (profiles/qkv_single_kernel_vs_three_launches.txt): d = 7168, B = 32 / 64 / 128: 64 / 72 / 90 us (83 / 113 / 120; 308 MB of
+// weights); d = 4096, B = 128: 39 (69); d = 9216, B = 128: 136 to 140 (148 to 169, two sessions).  Error against 64 bits
+// 2.9e-4 (3.6e-4: two roundings on the way into the product); bf16 2.35e-3 (2.8e-3).
 #include "hk_internal.h"
 #include "elem.h"
 #include "mma_ring.h"

@@ -7,10 +7,11 @@
     python -m paper_2501_01792_amd.measure overlap [--config opt6.7b] [--iters 20]
     python -m paper_2501_01792_amd.measure gemm    [--config opt66b] [--iters 6]
     python -m paper_2501_01792_amd.measure read    [--config opt66b] [--iters 5]
+    python -m paper_2501_01792_amd.measure attn
     python -m paper_2501_01792_amd.measure tiles
     python -m paper_2501_01792_amd.measure qkvlines
 
-Each prints one JSON line (``tiles`` and ``qkvlines`` a table in front of it).  Inputs are drawn on the GPU with the scales of the benchmark recipe (timing only;
+Each prints one JSON line (the last three a table in front of it).  Inputs are drawn on the GPU with the scales of the benchmark recipe (timing only;
 parity is the tests' business).  ``qkv`` measures hk_qkv_current (Sec. 4.2.2, QKV generation of the current
 token) COLD: the weights of one layer fit in the 256 MB last-level cache, which a real decoder of dozens of
 layers would have evicted by the time a layer comes round again, so a 512 MiB buffer is read between calls.
@@ -25,7 +26,8 @@ regeneration GEMM (all of its tokens as checkpoints) alternately with a plain li
 (torch.addmm, i.e. hipBLASLt: no LayerNorm, row-major output), as a comparator for what this GPU sustains on the shape.
 ``read`` measures how fast the workload's checkpoint rows stream from HBM with the load structure of the streaming
 kernels (32 rows per wavefront, 20 KiB in flight each) for four shapes of one load instruction, plain and non-temporal.
-``tiles`` measures the projection on a prepared layer (with its row statistics) on every tile form over widths and numbers
+``attn`` measures the decode attention over cached tokens alone (both kernels of it), contiguous and through block tables of
+16-token blocks in random order, from one request to batches that fill the memory.  ``tiles`` measures the projection on a prepared layer (with its row statistics) on every tile form over widths and numbers
 of tokens, beside the form that the library takes.  ``qkvlines`` measures hk_qkv_current as a single kernel (a workspace of
 256 bytes) against the form that it takes with the workspace it asks for, over widths and rows, Q + K + V and Q alone, new
 weights in every call; only sizes where the two differ are printed.
@@ -401,6 +403,50 @@ def _replayed_us(calls, reps=5):
     return float(np.median(ts))
 
 
+def measure_attn(args):
+    import ctypes
+    import torch
+    from . import binding as hk
+    print("%-11s %-5s %4s %4s %4s %11s %10s %10s %7s" % ("", "type", "H", "dh", "B", "tokens", "GB", "us", "TB/s"))
+    rows = []
+    for el, name in ((torch.float16, "f16"), (torch.bfloat16, "bf16")):
+        for H, dh, B, lo, hi in ((12, 64, 1, 300, 300), (32, 128, 1, 1999, 1999), (32, 128, 8, 512, 512), (32, 128, 32, 512, 512),
+                                 (32, 128, 32, 512, 1024), (40, 128, 64, 512, 512), (72, 128, 64, 2048, 2048), (72, 128, 64, 2048, 4096)):
+            n = lambda *s: torch.empty(s, dtype=el, device="cuda").normal_()
+            q = n(B, H, dh)
+            out = torch.empty_like(q)
+            shape = hk.make_shape(H * dh, H, dtype=1 if el == torch.bfloat16 else 0)
+            if lo == hi:                                       # requests of one length: contiguous too
+                K, V = n(B, H, lo, dh), n(B, H, lo, dh)
+                z = torch.zeros(16, dtype=el, device="cuda")
+                ws = hk.new_workspace(hk.hk_workspace_bytes(shape, B, lo, 0))
+                us = _replayed_us([lambda: hk.hybrid_decode_attn(q, K, V, None, (z, z, z, z), 1.0, out=out, workspace=ws)] * 10)
+                rows.append(("contiguous", name, H, dh, B, B * lo, us))
+                del K, V
+            rng = np.random.default_rng(hi)
+            lens = rng.integers(lo, hi + 1, B).astype(np.int32)
+            nb = (lens + 15) // 16
+            ids, table, at = rng.permutation(int(nb.sum())), np.zeros((B, int(nb.max())), np.int32), 0
+            for b in range(B):
+                table[b, :nb[b]] = ids[at:at + nb[b]]
+                at += nb[b]
+            K, V = n(int(nb.sum()), H, 16, dh), n(int(nb.sum()), H, 16, dh)
+            tb, sl = torch.from_numpy(table).cuda(), torch.from_numpy(lens).cuda()
+            cu = torch.from_numpy(np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)).cuda()
+            total = int(lens.sum())
+            cache = hk.make_paged_cache(K, V, None, tb, sl, cu, total, 16, 0, el=el)
+            ws = hk.new_workspace(int(hk.lib().hk_paged_workspace_bytes(ctypes.byref(shape), B, ctypes.byref(cache))))
+            us = _replayed_us([lambda: hk.paged_decode_attn(q, K, V, None, tb, sl, 16, None, n_act_used=0, out=out, workspace=ws,
+                                                            cu_tokens=cu, total_tokens=total)] * 10)
+            rows.append(("paged", name, H, dh, B, total, us))
+            del K, V
+            for r in rows[-2 if lo == hi else -1:]:
+                gb = r[5] * H * dh * 4 / 1e9
+                print("%-11s %-5s %4d %4d %4d %11d %10.3f %10.1f %7.2f" % (*r[:6], gb, r[6], gb / r[6] * 1e3), flush=True)
+    print(json.dumps({"entry": "decode attention over cached tokens", "sizes": len(rows)}))
+    return 0
+
+
 def measure_tiles(args):
     import torch
     from . import binding as hk, probe
@@ -461,7 +507,7 @@ def measure_qkvlines(args):
 
 def main():
     ap = argparse.ArgumentParser(description=__doc__, formatter_class=argparse.RawDescriptionHelpFormatter)
-    ap.add_argument("what", choices=["qkv", "paged", "loop", "overlap", "gemm", "read", "tiles", "qkvlines"])
+    ap.add_argument("what", choices=["qkv", "paged", "loop", "overlap", "gemm", "read", "attn", "tiles", "qkvlines"])
     ap.add_argument("--config", default=None)
     ap.add_argument("--iters", type=int, default=20)
     ap.add_argument("--block-tokens", type=int, default=16)
@@ -490,6 +536,8 @@ def main():
         return measure_overlap(args)
     if args.what == "read":
         return measure_read(args)
+    if args.what == "attn":
+        return measure_attn(args)
     if args.what == "tiles":
         return measure_tiles(args)
     if args.what == "qkvlines":
