@@ -4,8 +4,8 @@
 // Bound by latency, not bytes (a pair has 1 .. a few dozen partials of 520 bytes): P wavefronts share a pair's run,
 // each takes its part kBatch slots at a time with every load of a batch issued before the first use, and the P
 // results meet in LDS.  With one thread per element walking the slots one after the other (two dependent passes, and
-// 64-bit divisions in front) the merge of 32 pairs of 16 partials took 11.3 us and that of 4608 pairs of 2 took 18.4 us;
-// now 4.0 us (32 partials by then) and 7.6 us.
+// 64-bit divisions in front) the merge of 4608 pairs of one or two partials took 15.9 us and that of 7168 pairs 22.8; now 6.8
+// and 8.7 us (profiles/hybrid_step_opt66b.txt, hybrid_step_opt30b.txt).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
