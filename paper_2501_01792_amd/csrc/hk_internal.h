@@ -37,6 +37,7 @@ struct KvGemmArgs {
     void *K_out;           // [B, H, L_cap, dh] fp16
     void *V_out;
     int64_t M;             // B * L_act
+    int64_t m_begin = 0;   // launch_kv_gemm_form, tiles below 256 x 256: rows before it are left out
     int d, n_heads, head_dim;
     int L_act, L_cap, tok_off;
     int tile;              // 0 = choose, else 128 or 256

@@ -29,22 +29,54 @@ constexpr TileForm kForms[] = {
 };
 constexpr int kCount = sizeof(kForms) / sizeof(kForms[0]);
 
-// Index of the form with the least estimated time for the compute unit with the most tiles, first + more (n - 1) with
-// n = tiles of the busiest of `cus` units; M tokens, 2 d output features.
-inline int pick(int64_t M, int d, int cus)
+// Tiles of a form over M tokens and 2 d output features, and the estimated time for the compute unit with the most of them:
+// first + more (n - 1) with n = tiles of the busiest of `cus` units.
+inline int64_t row_tiles(const TileForm &f, int64_t M) { return (M + f.bm - 1) / f.bm; }
+inline int64_t col_tiles(const TileForm &f, int d) { return (2 * d + f.bn - 1) / f.bn; }
+inline double estimate(const TileForm &f, int64_t M, int d, int cus)
 {
-    int best = 0;
-    double least = 0.;
-    for (int i = 0; i < kCount; ++i) {
-        const TileForm &f = kForms[i];
-        const int64_t tiles = ((M + f.bm - 1) / f.bm) * ((2 * (int64_t)d + f.bn - 1) / f.bn);
-        const double t = f.first + f.more * (double)((tiles + cus - 1) / cus - 1);
-        if (i == 0 || t < least) {
+    return f.first + f.more * (double)((row_tiles(f, M) * col_tiles(f, d) + cus - 1) / cus - 1);
+}
+
+// Index of the form with the least estimated time, of those from `from` on.
+inline int pick(int64_t M, int d, int cus, int from = 0)
+{
+    int best = from;
+    double least = estimate(kForms[from], M, d, cus);
+    for (int i = from + 1; i < kCount; ++i) {
+        const double t = estimate(kForms[i], M, d, cus);
+        if (t < least) {
             best = i;
             least = t;
         }
     }
     return best;
+}
+
+// One launch for all rows, or two: 256 x 256 tiles for as many rows as fill their rounds over the compute units, and the form
+// that suits them for the rows whose tiles would have been a partly filled round.  A second launch adds its gap and its
+// first loads, about 5 us; and the estimate has to gain a fifth of a round, because a round that few units take part in is
+// faster than a full one (the clock is up, the memory idle): cut there too, 1551 rows of d = 7168 took 298 us against 281,
+// 4000 of d = 9216 1067 against 1004.  Measured with the row statistics, one launch -> two, fp16: d = 4096, 2500 rows: 168 -> 138
+// us, 12608: 642 -> 611; d = 5120, 1551 rows: 177 -> 138; d = 7168, 2500 rows: 444 -> 388; d = 9216, 12608 rows: 3358 -> 3181;
+// from 20 rounds on it is level.  (First launches on smaller tiles never came out ahead.)
+struct Plan {
+    int form;
+    int64_t rows;           // of the first launch; the others are the second's
+    int rest_form;
+};
+constexpr double kSecondUs = 5., kSure = 0.2;
+inline Plan plan(int64_t M, int d, int cus)
+{
+    const Plan one = {pick(M, d, cus), M, 0};
+    const TileForm &f = kForms[0];
+    const int64_t cols = col_tiles(f, d), tiles = row_tiles(f, M) * cols;
+    if (tiles < cus) return one;
+    const int64_t rows = tiles / cus * cus / cols * f.bm;                   // row tiles that fit the full rounds
+    if (rows <= 0 || rows >= M) return one;
+    const int rest = pick(M - rows, d, cus, 1);
+    const double two = estimate(f, rows, d, cus) + estimate(kForms[rest], M - rows, d, cus) + kSecondUs * 64 / d + kSure * f.more;
+    return two < estimate(kForms[one.form], M, d, cus) ? Plan{0, rows, rest} : one;
 }
 
 }  // namespace forms

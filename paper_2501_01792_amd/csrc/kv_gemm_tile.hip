@@ -32,7 +32,7 @@ __global__ __launch_bounds__(256, BM * BN <= 128 * 128 ? 2 : 1) void kv_gemm_til
     const typename Elem<DT>::T *__restrict__ act, const float2 *__restrict__ stats,
     const typename Elem<DT>::T *__restrict__ Wp, const float *__restrict__ cvec, const float *__restrict__ bvec,
     typename Elem<DT>::T *__restrict__ K_out, typename Elem<DT>::T *__restrict__ V_out,
-    int64_t M, int d, int n_heads, int head_dim, int L_act, int L_cap, int tok_off, int tiles_m, int tiles_n)
+    int64_t m_begin, int64_t M, int d, int n_heads, int head_dim, int L_act, int L_cap, int tok_off, int tiles_m, int tiles_n)
 {
 #if defined(__HIP_DEVICE_COMPILE__)                            // (the host pass drops the kernel's stub over a direct load in this body)
     typedef typename Elem<DT>::T elem_t;
@@ -47,7 +47,7 @@ __global__ __launch_bounds__(256, BM * BN <= 128 * 128 ? 2 : 1) void kv_gemm_til
 
     int tm, tn;
     tile_coords<8>((int)blockIdx.x, tiles_m, tiles_n, tm, tn);
-    const int64_t m0 = (int64_t)tm * BM;
+    const int64_t m0 = m_begin + (int64_t)tm * BM;
     const int n0 = tn * BN;
 
     // ---- what the epilogue needs from memory, asked for first
@@ -130,7 +130,7 @@ template <int BM, int BN, int NS, int DT>
 hipError_t launch_tile_dt(const KvGemmArgs &a, hipStream_t s)
 {
     typedef typename Elem<DT>::T elem_t;
-    const int64_t tiles_m = (a.M + BM - 1) / BM;
+    const int64_t tiles_m = (a.M - a.m_begin + BM - 1) / BM;
     const int tiles_n = (2 * a.d + BN - 1) / BN;
     if (tiles_m * tiles_n > 0x7fffffffLL) return hipErrorInvalidValue;
     auto kern = kv_gemm_tile_kernel<BM, BN, NS, DT>;
@@ -142,7 +142,7 @@ hipError_t launch_tile_dt(const KvGemmArgs &a, hipStream_t s)
     hipLaunchKernelGGL(kern, dim3((unsigned)(tiles_m * tiles_n)), dim3(256), lds, s,
                        static_cast<const elem_t *>(a.act), a.stats, static_cast<const elem_t *>(a.Wp), a.cvec, a.bvec,
                        static_cast<elem_t *>(a.K_out), static_cast<elem_t *>(a.V_out),
-                       a.M, a.d, a.n_heads, a.head_dim, a.L_act, a.L_cap, a.tok_off, (int)tiles_m, tiles_n);
+                       a.m_begin, a.M, a.d, a.n_heads, a.head_dim, a.L_act, a.L_cap, a.tok_off, (int)tiles_m, tiles_n);
     return hipGetLastError();
 }
 
@@ -172,7 +172,8 @@ static_assert(sizeof(kLaunch) / sizeof(kLaunch[0]) == forms::kCount, "one kernel
 
 hipError_t launch_kv_gemm_form(const KvGemmArgs &a, int form, hipStream_t s)
 {
-    if (a.M <= 0 || a.d % ring::kBlockK != 0 || form < 0 || form >= forms::kCount) return hipErrorInvalidValue;
+    if (a.m_begin < 0 || a.M <= a.m_begin || (form == 0 && a.m_begin != 0) || a.d % ring::kBlockK != 0 || form < 0 || form >= forms::kCount)
+        return hipErrorInvalidValue;
     return kLaunch[form](a, s);
 }
 
@@ -181,7 +182,14 @@ hipError_t launch_kv_gemm_prepared(const KvGemmArgs &a, hipStream_t s)
     int dev = 0, cus = 0;
     const hipError_t e = current_device_cus(&dev, &cus);
     if (e != hipSuccess) return e;
-    return launch_kv_gemm_form(a, forms::pick(a.M, a.d, cus), s);
+    const forms::Plan p = forms::plan(a.M, a.d, cus);
+    KvGemmArgs part = a;
+    part.M = p.rows;
+    const hipError_t first = launch_kv_gemm_form(part, p.form, s);
+    if (first != hipSuccess || p.rows == a.M) return first;
+    part.m_begin = p.rows;
+    part.M = a.M;
+    return launch_kv_gemm_form(part, p.rest_form, s);
 }
 
 }  // namespace hk
