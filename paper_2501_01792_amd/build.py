@@ -19,7 +19,7 @@ PROBE_SRC = [os.path.join(HERE, "probe", "mfma_rate.hip"),     # measurement aid
 PROBE_LIB = os.path.join(HERE, "probe", "libhkprobe.so")
 PROBE_LT_SRC = os.path.join(HERE, "probe", "library_gemm.hip")  # the vendor GEMM's candidate kernels, timed (links hipBLASLt)
 PROBE_LT_LIB = os.path.join(HERE, "probe", "libhkprobe_lt.so")
-SOURCES = ["api.hip", "device_info.hip", "ln_stats.hip", "kv_gemm.hip", "kv_gemm_fold.hip", "kv_gemm_tile.hip", "flash_decode.hip", "paged_decode.hip", "paged_append.hip", "qkv_current.hip", "qkv_stream.hip", "absorbed.hip", "policy.hip"]
+SOURCES = ["api.hip", "device_info.hip", "ln_stats.hip", "kv_gemm.hip", "kv_gemm_fold.hip", "kv_gemm_tile.hip", "flash_decode.hip", "paged_decode.hip", "paged_append.hip", "qkv_current.hip", "qkv_stream.hip", "absorbed.hip", "absorbed_stream.hip", "policy.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",

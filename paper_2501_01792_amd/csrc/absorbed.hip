@@ -21,11 +21,9 @@
 //
 // Kernels (B sequences, H heads, L_act checkpoint rows per sequence):
 //   carry   U[h,b,:]  = q[b,h,:] W'_K,h          rows of W' reduced       column_product (MFMA)
-//   scores  raw[b,h,t] = x[b,t,:] . U[h,b,:]     rows of x streamed       skinny::slab_product, or block_product from
-//                                                                         65536 rows on (MFMA); also the LayerNorm
-//                                                                         statistics of the rows
-//   softmax w[b,h,t]  = p_t rstd_t / l           one wavefront per (b,h)
-//   gather  Y[b,h,:]  = sum_t w[b,h,t] x[b,t,:] - sum_t w[b,h,t] mean_t   rows of x reduced   column_product (MFMA)
+//   scores  w[b,h,t], from x[b,t,:] . U[h,b,:]   rows of x streamed       absorbed_stream.hip (MFMA); also the LayerNorm
+//                                                                         statistics of the rows and their softmax
+//   gather  Y[b,h,:]  = sum_t w[b,h,t] (x[b,t,:] - mean_t)   rows of x reduced   absorbed_stream.hip (MFMA)
 //   project o[b,h,:]  = W'_V,h Y[b,h,:] + b'_V   rows of W' streamed      skinny::slab_product (MFMA), joins the cached part;
 //                                                                         layers of 5120 features or more: block_product
 //                                                                         with the reduction axis cut over workgroups, then
@@ -43,21 +41,6 @@ typedef float float4_t __attribute__((ext_vector_type(4)));
 typedef short short4_t __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) short4_t *lds_short4_ptr;
 
-constexpr float kNegBig = -1.0e30f;
-
-__device__ __forceinline__ float wave_sum(float v)
-{
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
-}
-__device__ __forceinline__ float wave_max(float v)
-{
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, 64));
-    return v;
-}
-
 // ---------------------------------------------------------------------------------------------------------
 // column_product: Out[z][m][c] = sum_r A[z][m][r] * S[z][r][c]   (m < a_rows <= 32 RB, r < R, c < n_cols)
 //
@@ -68,19 +51,16 @@ __device__ __forceinline__ float wave_max(float v)
 // (ds_read_b64_tr_b16; rows 192 bytes apart, so that the four rows one such read touches fall on disjoint banks).  The small operand A (few rows, reduction axis contiguous, zero
 // beyond R up to the next multiple of 64) is the same for the four wavefronts of a workgroup: it is fetched
 // once per 64 reduction elements with whole-line loads, two tiles ahead, and shared through a double-buffered
-// LDS tile (one barrier per 64 reduction elements).  The result (minus an optional per-row constant, in fp32)
-// leaves through the private LDS block so that it is stored as whole 128-byte rows.
+// LDS tile (one barrier per 64 reduction elements).  The result leaves through the private LDS block so that it is
+// stored as whole 128-byte rows.  A last workgroup of every z takes the two dot products of the rows of A with
+// per-row-of-S constants (cvec, bvec).
 struct ColArgs {
     const _Float16 *S; int64_t s_batch, ld_s; int R, n_cols;
     const _Float16 *A; int64_t a_batch, ld_a; int a_rows;
     _Float16 *Out; int64_t o_batch, ld_out;
-    const float *shift; int64_t shift_batch; int shift_stride;   // optional: Out[z][m][:] -= shift[z shift_batch + m shift_stride]
-    // optional, for rows that live in blocks of 2^blk_log2 (>= 16) rows scattered over a pool: row r of batch z is
-    // row r % block of pool block blk_list[z list_pitch + r / block] (S then points at the pool, s_batch = 0), and
-    // batch z has R_list[z] rows (0: the output rows of z are zero)
-    const int32_t *blk_list; int list_pitch, blk_log2;
-    const int32_t *R_list;
+    const float *cvec, *bvec; float2 *c12; int c12_stride;     // c12[m c12_stride + z] = (A[z][m] . cvec[z R ..], A[z][m] . bvec[z R ..])
     int s_dt, a_dt;                                        // storage types of S and of A (Out is fp16)
+    int nt;                                                // Out is stored non-temporally
 };
 
 constexpr int kColBlock = 64;                              // columns of one wavefront
@@ -91,7 +71,7 @@ constexpr int kTileBytes = 32 * 128;                       // 32 operand rows x 
 template <int RB>
 constexpr int col_lds_bytes() { return 4 * kColStage + 2 * RB * kTileBytes; }
 
-template <int RB, int SDT, int ADT>
+template <int RB, int SDT, int ADT, bool NT>
 __global__ __launch_bounds__(256) void column_product_kernel(ColArgs p)
 {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -99,13 +79,30 @@ __global__ __launch_bounds__(256) void column_product_kernel(ColArgs p)
     constexpr int XS = kColPitch;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (blockIdx.x == gridDim.x - 1) {                     // 4 threads a row of A
+        const int64_t zc = blockIdx.y;
+        for (int m = tid >> 2; m < p.a_rows; m += 64) {
+            float c1 = 0.f, c2 = 0.f;
+            for (int r = tid & 3; r < p.R; r += 4) {
+                const float a = skinny::stored_to_float<ADT>(p.A + zc * p.a_batch + (int64_t)m * p.ld_a + r);
+                c1 = __builtin_fmaf(a, p.cvec[zc * p.R + r], c1);
+                c2 = __builtin_fmaf(a, p.bvec[zc * p.R + r], c2);
+            }
+            c1 += __shfl_xor(c1, 1, 64);
+            c1 += __shfl_xor(c1, 2, 64);
+            c2 += __shfl_xor(c2, 1, 64);
+            c2 += __shfl_xor(c2, 2, 64);
+            if ((tid & 3) == 0) p.c12[(int64_t)m * p.c12_stride + zc] = make_float2(c1, c2);
+        }
+        return;
+    }
     int c0 = (blockIdx.x * 4 + wave) * kColBlock;
     const bool live = c0 < p.n_cols;                       // a wavefront past the last column block works on the
     if (!live) c0 = p.n_cols - kColBlock;                  // last one (it shares the barriers) and stores nothing
     const int64_t z = blockIdx.y;
     const _Float16 *S = p.S + z * p.s_batch + c0;
     const _Float16 *A = p.A + z * p.a_batch;
-    const int R = p.R_list ? p.R_list[z] : p.R;            // uniform over the workgroup
+    const int R = p.R;
     const int steps = (R + 15) / 16;
     const int tiles = (steps + 3) / 4;
 
@@ -146,19 +143,12 @@ __global__ __launch_bounds__(256) void column_product_kernel(ColArgs p)
     const int last = steps - 1, last_tile = tiles - 1;
     auto clamp = [&](int sc) { return sc < last ? sc : last; };
     auto load_s = [&](int slot, int sc) {
-        // the 16 rows of a step share a block; its number comes through a scalar load (sc and z are uniform), which
-        // does not wait for the vector loads in flight
         const int r0 = 16 * sc;
-        int64_t first = r0;
-        if (p.blk_list) {
-            const int32_t bid = p.blk_list[z * p.list_pitch + (r0 >> p.blk_log2)];
-            first = ((int64_t)bid << p.blk_log2) + (r0 & ((1 << p.blk_log2) - 1));
-        }
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
             int rr = 8 * j + g_row;
             if (r0 + rr >= R) rr = R - 1 - r0;             // rows past the end meet zeros of A; r0 < R for every step asked for
-            sv[slot][j] = *reinterpret_cast<const half8_t *>(S + (first + rr) * p.ld_s + 8 * g_chunk);
+            sv[slot][j] = *reinterpret_cast<const half8_t *>(S + (int64_t)(r0 + rr) * p.ld_s + 8 * g_chunk);
         }
     };
     auto load_a = [&](int slot, int g) {
@@ -171,16 +161,6 @@ __global__ __launch_bounds__(256) void column_product_kernel(ColArgs p)
         for (int rb = 0; rb < RB; ++rb)
             *reinterpret_cast<half8_t *>(tile + (buf * RB + rb) * kTileBytes + t_wr) = skinny::to_half8<ADT>(av[slot][rb]);
     };
-    if (R <= 0) {                                          // nothing to sum (uniform over the workgroup: no barrier is missed)
-        if (live) {
-            _Float16 *Out0 = p.Out + z * p.o_batch + c0;
-            half8_t zero8;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) zero8[i] = (_Float16)0.f;
-            for (int m = g_row; m < p.a_rows; m += 8) *reinterpret_cast<half8_t *>(Out0 + (int64_t)m * p.ld_out + 8 * g_chunk) = zero8;
-        }
-        return;
-    }
     // Every load of the loop is unconditional (steps and tiles past the end re-read the last one), so that
     // the number of loads in flight at each wait is a compile-time fact.
     load_a(0, 0);
@@ -234,37 +214,34 @@ __global__ __launch_bounds__(256) void column_product_kernel(ColArgs p)
     _Float16 *Out = p.Out + z * p.o_batch + c0;
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
-        float sub[16];
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            int m = 32 * rb + 8 * (r >> 2) + 4 * lh + (r & 3);
-            if (m >= p.a_rows) m = p.a_rows - 1;
-            sub[r] = p.shift ? p.shift[z * p.shift_batch + (int64_t)m * p.shift_stride] : 0.f;
-        }
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
             for (int r = 0; r < 16; ++r)
                 *reinterpret_cast<_Float16 *>(my + (8 * (r >> 2) + 4 * lh + (r & 3)) * XS + 2 * (32 * nb + ln)) =
-                    (_Float16)(acc[rb][nb][r] - sub[r]);
+                    (_Float16)acc[rb][nb][r];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int m = 32 * rb + 8 * j + g_row;
             const half8_t o = *reinterpret_cast<const half8_t *>(my + (8 * j + g_row) * XS + 16 * g_chunk);
-            if (m < p.a_rows) *reinterpret_cast<half8_t *>(Out + (int64_t)m * p.ld_out + 8 * g_chunk) = o;
+            half8_t *dst = reinterpret_cast<half8_t *>(Out + (int64_t)m * p.ld_out + 8 * g_chunk);
+            if (m < p.a_rows) {
+                if constexpr (NT) __builtin_nontemporal_store(o, dst);
+                else *dst = o;
+            }
         }
     }
 }
 
-template <int RB, int SDT, int ADT>
+template <int RB, int SDT, int ADT, bool NT>
 hipError_t launch_col_as(const ColArgs &p, int batches, hipStream_t s)
 {
-    auto kern = column_product_kernel<RB, SDT, ADT>;
+    auto kern = column_product_kernel<RB, SDT, ADT, NT>;
     constexpr int lds = col_lds_bytes<RB>();
     static LdsOnce lds_once;
     hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(kern), lds, lds_once);
     if (e != hipSuccess) return e;
-    const int blocks_x = (p.n_cols / kColBlock + 3) / 4;
+    const int blocks_x = (p.n_cols / kColBlock + 3) / 4 + 1;      // and the one of the dot products
     hipLaunchKernelGGL(kern, dim3((unsigned)blocks_x, (unsigned)batches), dim3(256), lds, s, p);
     return hipGetLastError();
 }
@@ -272,9 +249,8 @@ hipError_t launch_col_as(const ColArgs &p, int batches, hipStream_t s)
 template <int RB>
 hipError_t launch_col(const ColArgs &p, int batches, hipStream_t s)
 {
-    if (p.s_dt == 0 && p.a_dt == 0) return launch_col_as<RB, 0, 0>(p, batches, s);
-    if (p.s_dt == 1 && p.a_dt == 1) return launch_col_as<RB, 1, 1>(p, batches, s);
-    if (p.s_dt == 1 && p.a_dt == 0) return launch_col_as<RB, 1, 0>(p, batches, s);
+    if (p.s_dt == 0 && p.a_dt == 0) return p.nt ? launch_col_as<RB, 0, 0, true>(p, batches, s) : launch_col_as<RB, 0, 0, false>(p, batches, s);
+    if (p.s_dt == 1 && p.a_dt == 1) return p.nt ? launch_col_as<RB, 1, 1, true>(p, batches, s) : launch_col_as<RB, 1, 1, false>(p, batches, s);
     return hipErrorInvalidValue;
 }
 
@@ -292,207 +268,6 @@ hipError_t launch_column_product(const ColArgs &p, int batches, hipStream_t s)
 }
 
 // ---------------------------------------------------------------------------------------------------------
-// scores: raw[b][h][t] = (x[b,t,:] - x[b,t,0]) . U[h,b,:] for the checkpoint rows of one sequence, and the
-// LayerNorm statistics of those rows from the same pass:
-//   stats[b L_act + t] = (rstd, mean, -(mean - x[b,t,0]) rstd, -)
-// The rows enter the product minus their first element, so that a large row mean is neither multiplied with
-// the rounding error of U nor left to cancel later.  Workgroup ids are regrouped so that the workgroups of one
-// sequence, which share that sequence's U rows, run on one XCD and find them in its L2.
-__device__ __forceinline__ float4 row_stats(float s1, float s2, float first, int d, float eps)
-{
-    const float inv_d = 1.0f / (float)d;
-    const float dm = s1 * inv_d;                           // mean - first element
-    const float var = fmaxf(__builtin_fmaf(-dm, dm, s2 * inv_d), 0.f);
-    const float rstd = 1.0f / __builtin_sqrtf(var + eps);
-    return make_float4(rstd, first + dm, -dm * rstd, 0.f);
-}
-
-// Few checkpoint rows in all: a slab of 32 rows per workgroup, the reduction axis cut over its 4 wavefronts
-// (skinny::slab_product), so that even a small problem fills the chip.  Every workgroup reads all of U[:,b,:].
-template <int RB, int DT>
-__global__ __launch_bounds__(256) void absorbed_scores_kernel(const _Float16 *__restrict__ act, const _Float16 *__restrict__ U,
-                                                              float *__restrict__ raw, float4 *__restrict__ stats,
-                                                              int B, int L_act, int Lp, int H, int d, float eps)
-{
-    extern __shared__ __align__(16) unsigned char smem[];
-    const int tid = threadIdx.x;
-    const int slabs = (L_act + skinny::kSlab - 1) / skinny::kSlab;
-    const int item = gemm::xcd_regroup(blockIdx.x, slabs * B);
-    const int64_t b = item / slabs;
-    const int t0 = (item % slabs) * skinny::kSlab;
-    const int rows = L_act - t0 < skinny::kSlab ? L_act - t0 : skinny::kSlab;
-    const _Float16 *S = act + (b * L_act + t0) * d;
-    float (*red)[RB * 32][skinny::kSlab] = skinny::slab_product<RB, false, true, DT>(S, rows, d, U + b * d, H, (int64_t)B * d, d, smem);
-    for (int idx = tid; idx < H * skinny::kSlab; idx += 256) {
-        const int h = idx / skinny::kSlab, c = idx % skinny::kSlab;
-        if (c < rows)
-            raw[(b * H + h) * Lp + t0 + c] = (red[0][h][c] + red[1][h][c]) + (red[2][h][c] + red[3][h][c]);
-    }
-    if (tid < rows) {
-        float (*mom)[skinny::kSlab][2] = skinny::moments<RB>(smem);
-        const float s1 = (mom[0][tid][0] + mom[1][tid][0]) + (mom[2][tid][0] + mom[3][tid][0]);
-        const float s2 = (mom[0][tid][1] + mom[1][tid][1]) + (mom[2][tid][1] + mom[3][tid][1]);
-        stats[b * L_act + t0 + tid] = row_stats(s1, s2, (float)skinny::stored_to_half<DT>(S + (int64_t)tid * d), d, eps);
-    }
-}
-
-// Many checkpoint rows: 128 rows per workgroup (skinny::block_product): U is read once per 128 rows instead of
-// once per 32, and scores and statistics are stored straight from registers.
-template <int RB, int DT>
-__global__ __launch_bounds__(256) void absorbed_scores_block_kernel(const _Float16 *__restrict__ act, const _Float16 *__restrict__ U,
-                                                                    float *__restrict__ raw, float4 *__restrict__ stats,
-                                                                    int B, int L_act, int Lp, int H, int d, float eps)
-{
-    extern __shared__ __align__(16) unsigned char smem[];
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int blocks = (L_act + 127) / 128;
-    const int item = gemm::xcd_regroup(blockIdx.x, blocks * B);
-    const int64_t b = item / blocks;
-    const int t0 = (item % blocks) * 128;
-    const int tw = t0 + 32 * wave;                         // first row of this wavefront
-    const int rows = L_act - tw < 32 ? (L_act - tw > 0 ? L_act - tw : 0) : 32;
-    float16_t acc[RB];
-    float m1[4], m2[4];
-    _Float16 first[4];
-    skinny::block_product<RB, false, true, DT>(act + (b * L_act + t0) * d, L_act - t0 < 128 ? L_act - t0 : 128, d,
-                                           U + b * d, H, (int64_t)B * d, 0, d / 64, smem, acc, m1, m2, first);
-    const int ln = lane & 31, lh = lane >> 5;
-    if (ln < rows) {
-#pragma unroll
-        for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int h = 32 * rb + 8 * (r >> 2) + 4 * lh + (r & 3);
-                if (h < H) raw[(b * H + h) * Lp + tw + ln] = acc[rb][r];
-            }
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int row = 8 * j + (lane >> 3);
-        if ((lane & 7) == 0 && row < rows) stats[b * L_act + tw + row] = row_stats(m1[j], m2[j], (float)first[j], d, eps);
-    }
-}
-
-// softmax over the checkpoint rows of one (sequence, head), one wavefront each.  In the log2 domain:
-//   s_t = sl (rstd_t f raw_t + k_t c1 + c2),  k_t = -(mean_t - x_t[0]) rstd_t,  c1 = q . c_K,h,  c2 = q . b'_K,h,
-//   f the factor of the prepared layer's scaled weights,
-//   sl = scale log2(e);   w_t = fp16(2^(s_t - m) rstd_t / l), zero from L_act to the next multiple of 64;
-//   sums = (m, l, sum_t w_t mean_t with the stored w_t, -)
-template <int DT>
-__global__ __launch_bounds__(256) void absorbed_softmax_kernel(const _Float16 *__restrict__ q,
-                                                               const float *__restrict__ raw, const float4 *__restrict__ stats,
-                                                               const float *__restrict__ cvec, const float *__restrict__ bvec,
-                                                               _Float16 *__restrict__ w, float4 *__restrict__ sums,
-                                                               int B, int H, int head_dim, int L_all, int Lp, float sl,
-                                                               const int32_t *__restrict__ n_rows, int stats_pitch)
-{
-    const int lane = threadIdx.x & 63;
-    const int bh = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (bh >= B * H) return;                               // whole wavefront leaves together; no barrier in this kernel
-    const int b = bh / H, h = bh % H;
-    const int L_act = n_rows ? n_rows[b] : L_all;          // sequences may have their own numbers of rows (0: no weight at all)
-    float c1 = 0.f, c2 = 0.f;
-    for (int e = lane; e < head_dim; e += 64) {
-        const float qe = skinny::stored_to_float<DT>(q + (int64_t)bh * head_dim + e);
-        c1 = __builtin_fmaf(qe, cvec[h * head_dim + e], c1);
-        c2 = __builtin_fmaf(qe, bvec[h * head_dim + e], c2);
-    }
-    c1 = wave_sum(c1);
-    c2 = wave_sum(c2);
-    const float *r = raw + (int64_t)bh * Lp;
-    const float4 *st = stats + (int64_t)b * stats_pitch;
-    // Every load is unconditional (rows past the end re-read the last row and are masked afterwards) and loads come in
-    // batches of kBatch rows per lane: a load under a per-row test makes the compiler wait for it before the next one
-    // is issued, and the kernel then pays one memory latency per row and lane.
-    const int t_last = L_act > 0 ? L_act - 1 : 0;          // row 0 of the scratch rows is readable even without rows
-    constexpr int kBatch = 8;
-    const float wscale = bvec[2 * H * head_dim];           // of the scaled weights that U was formed with
-    auto score_of = [&](const float4 &s4, float rv) { return sl * (__builtin_fmaf(s4.x, rv * wscale, __builtin_fmaf(s4.z, c1, c2))); };
-    // The first 64 kKeep rows stay in registers (score, rstd, mean), so that up to that many rows are read once
-    // (the statistics of a row are shared by all heads: re-reading them per pass made this kernel L2-bound);
-    // rows beyond are read again in each of the three passes.  (Keeping 64 scores per lane and re-reading the
-    // statistics in the last pass instead was slower: 57 against 32 us on 2048 rows, no faster on 4096.)
-    constexpr int kKeep = 32;
-    float sc[kKeep], rs[kKeep], mn[kKeep];
-    float mx = kNegBig;
-#pragma unroll
-    for (int c = 0; c < kKeep; c += kBatch) {
-        float4 s4[kBatch];
-        float rv[kBatch];
-#pragma unroll
-        for (int u = 0; u < kBatch; ++u) {
-            const int t = lane + 64 * (c + u), tc = t < t_last ? t : t_last;
-            s4[u] = st[tc];
-            rv[u] = r[tc];
-        }
-#pragma unroll
-        for (int u = 0; u < kBatch; ++u) {
-            const bool valid = lane + 64 * (c + u) < L_act;
-            sc[c + u] = valid ? score_of(s4[u], rv[u]) : kNegBig;
-            rs[c + u] = valid ? s4[u].x : 0.f;
-            mn[c + u] = valid ? s4[u].y : 0.f;
-            mx = fmaxf(mx, sc[c + u]);
-        }
-    }
-    // rows beyond the kept ones, kBatch per lane at a time: fn(row, valid, score, rstd, mean)
-    auto tail_rows = [&](auto fn, int end) {
-        for (int t0 = lane + 64 * kKeep; t0 - lane < end; t0 += 64 * kBatch) {
-            float4 s4[kBatch];
-            float rv[kBatch];
-#pragma unroll
-            for (int u = 0; u < kBatch; ++u) {
-                const int t = t0 + 64 * u, tc = t < t_last ? t : t_last;
-                s4[u] = st[tc];
-                rv[u] = r[tc];
-            }
-#pragma unroll
-            for (int u = 0; u < kBatch; ++u) {
-                const int t = t0 + 64 * u;
-                fn(t, t < L_act, score_of(s4[u], rv[u]), s4[u].x, s4[u].y);
-            }
-        }
-    };
-    tail_rows([&](int, bool valid, float sv, float, float) { if (valid) mx = fmaxf(mx, sv); }, L_act);
-    mx = wave_max(mx);
-    float l = 0.f;
-#pragma unroll
-    for (int i = 0; i < kKeep; ++i)
-        if (lane + 64 * i < L_act) l += __builtin_amdgcn_exp2f(sc[i] - mx);
-    tail_rows([&](int, bool valid, float sv, float, float) { if (valid) l += __builtin_amdgcn_exp2f(sv - mx); }, L_act);
-    l = wave_sum(l);
-    const float inv = l > 0.f ? 1.0f / l : 0.f;
-    _Float16 *wr = w + (int64_t)bh * Lp;
-    // w is read (by the weighted row sum) up to the next multiple of 64 past the sequence's own rows, and must be
-    // zero from L_act on; what lies beyond, up to the pitch, is never read
-    const int fill = (L_act + 63) & ~63;                   // <= Lp
-    float mu = 0.f;
-#pragma unroll
-    for (int i = 0; i < kKeep; ++i) {
-        const int t = lane + 64 * i;
-        if (t < fill) {
-            _Float16 wt = (_Float16)0.f;
-            if (t < L_act) {
-                wt = (_Float16)(__builtin_amdgcn_exp2f(sc[i] - mx) * rs[i] * inv);
-                mu = __builtin_fmaf((float)wt, mn[i], mu);
-            }
-            wr[t] = wt;
-        }
-    }
-    tail_rows([&](int t, bool valid, float sv, float rstd, float mean) {
-        if (t < fill) {
-            _Float16 wt = (_Float16)0.f;
-            if (valid) {
-                wt = (_Float16)(__builtin_amdgcn_exp2f(sv - mx) * rstd * inv);
-                mu = __builtin_fmaf((float)wt, mean, mu);
-            }
-            wr[t] = wt;
-        }
-    }, fill);
-    mu = wave_sum(mu);
-    if (lane == 0) sums[bh] = make_float4(mx, l, mu, 0.f);
-}
-
 // project: o_a[b,h,e] = W'_V[h dh + e, :] . Y[b,h,:] + b'_V for a slab of 32 output features of one head, then
 // the join with the cached segment's (maximum, denominator, output).  Workgroup ids are regrouped so that the
 // slabs of one head, which share that head's Y rows, run on one XCD.
@@ -510,7 +285,7 @@ __global__ __launch_bounds__(256) void absorbed_project_kernel(const _Float16 *_
     const int h = item / per_head;
     const int n0 = h * head_dim + (item % per_head) * skinny::kSlab;   // first V feature of the slab
     float (*red)[RB * 32][skinny::kSlab] = skinny::slab_product<RB, true, false, DT>(
-        Wv + (int64_t)n0 * d, skinny::kSlab, d, Y + (int64_t)h * d, Bc, (int64_t)H * d, d, smem);
+        [=](int r) { return Wv + ((int64_t)n0 + r) * d; }, skinny::kSlab, Y + (int64_t)h * d, Bc, (int64_t)H * d, d, smem);
     for (int idx = tid; idx < Bc * skinny::kSlab; idx += 256) {
         const int b = idx / skinny::kSlab, c = idx % skinny::kSlab;
         const int n = n0 + c;
@@ -548,10 +323,8 @@ __global__ __launch_bounds__(256) void absorbed_project_block_kernel(const _Floa
     const int k_begin = ks * steps_per_part;                               // < steps: the launcher leaves no part empty
     const int k_steps = steps - k_begin < steps_per_part ? steps - k_begin : steps_per_part;
     float16_t acc[RB];
-    float m1[4], m2[4];
-    _Float16 first[4];
-    skinny::block_product<RB, true, false, DT>(Wv + (int64_t)h * head_dim * d, head_dim, d, Y + (int64_t)h * d, Bc, (int64_t)H * d,
-                                           k_begin, k_steps, smem, acc, m1, m2, first);
+    skinny::block_product<RB, true, DT>(Wv + (int64_t)h * head_dim * d, head_dim, d, Y + (int64_t)h * d, Bc, (int64_t)H * d,
+                                        k_begin, k_steps, smem, acc);
     // acc[rb][r]: sequence 32 rb + 8 (r/4) + 4 (lane/32) + r%4, feature 32 wave + lane%32 of the head
     const int ln = lane & 31, lh = lane >> 5;
     const int c = 32 * wave + ln;
@@ -608,31 +381,6 @@ __global__ __launch_bounds__(256) void absorbed_join_kernel(const float *__restr
 // Below, the slab form of the projection is used (measured: 15.4 against 12.5 + 4.4 us at d = 4096, B = 32;
 // 37 against 21 + 5 us at d = 5120, B = 64; 97 against 49 + 5 us at d = 9216, B = 64).
 constexpr int kProjectBlockMinD = 5120;
-constexpr int64_t kBlockModeMinRows = 128 * 512;           // from here on 128-row workgroups still fill the chip twice
-
-template <int RB, int DT>
-hipError_t launch_scores_as(const AbsorbedArgs &a, int Lp, hipStream_t s)
-{
-    const bool block_mode = (int64_t)a.B * a.L_act >= kBlockModeMinRows;
-    const int per = block_mode ? 128 : skinny::kSlab;
-    const int64_t items = (int64_t)((a.L_act + per - 1) / per) * a.B;
-    if (items > 0x7fffffffLL) return hipErrorInvalidValue;
-    auto kern = block_mode ? absorbed_scores_block_kernel<RB, DT> : absorbed_scores_kernel<RB, DT>;
-    const int lds = block_mode ? skinny::block_lds_bytes<RB>() : skinny::lds_bytes<RB>() + skinny::kMomentBytes;
-    static LdsOnce lds_once;
-    hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(kern), lds, lds_once);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3((unsigned)items), dim3(256), lds, s,
-                       static_cast<const _Float16 *>(a.act), static_cast<const _Float16 *>(a.U), a.w_raw, a.stats,
-                       a.B, a.L_act, Lp, a.H, a.d, a.eps);
-    return hipGetLastError();
-}
-
-template <int RB>
-hipError_t launch_scores(const AbsorbedArgs &a, int Lp, hipStream_t s)
-{
-    return a.dt == 1 ? launch_scores_as<RB, 1>(a, Lp, s) : launch_scores_as<RB, 0>(a, Lp, s);
-}
 
 template <int RB, int DT>
 hipError_t launch_project_as(const AbsorbedArgs &a, int b0, int Bc, hipStream_t s)
@@ -709,14 +457,9 @@ void absorbed_project_parts(int d, int H, int *parts, int *steps_per_part)
 
 namespace {
 
-// What the steps of the checkpoint part need beyond AbsorbedArgs when the rows live in pool blocks.
-struct PagedRows {
-    const int32_t *blk_list;   // [B, list_pitch]: the checkpoint blocks of every request, in logical order
-    const int32_t *n_rows;     // [B]: checkpoint rows of every request
-    int list_pitch, blk_log2;
-};
-
-hipError_t launch_carry(const AbsorbedArgs &a, hipStream_t s)
+// rows: checkpoint rows in all.  Where they outgrow the last-level cache U is stored non-temporally: left dirty in the cache
+// it was written back under the score pass (85 MB, 2.4 GB of rows: 437 against 381 us for that pass, 50 for this one either way).
+hipError_t launch_carry(const AbsorbedArgs &a, int64_t rows, hipStream_t s)
 {
     const int64_t d = a.d;
     // the queries through the key weights, at most kAbsorbMaxBatch sequences per launch
@@ -726,38 +469,19 @@ hipError_t launch_carry(const AbsorbedArgs &a, hipStream_t s)
         c.S = static_cast<const _Float16 *>(a.Wp); c.s_batch = (int64_t)a.head_dim * d; c.ld_s = d; c.R = a.head_dim; c.n_cols = a.d;
         c.A = static_cast<const _Float16 *>(a.q) + b0 * d; c.a_batch = a.head_dim; c.ld_a = d; c.a_rows = Bc;
         c.Out = static_cast<_Float16 *>(a.U) + b0 * d; c.o_batch = a.B * d; c.ld_out = d;
-        c.shift = nullptr; c.shift_batch = 0; c.shift_stride = 0;
-        c.blk_list = nullptr; c.list_pitch = 0; c.blk_log2 = 0; c.R_list = nullptr;
+        c.cvec = a.cvec; c.bvec = a.bvec; c.c12 = a.c12 + (int64_t)b0 * a.H; c.c12_stride = a.H;
         c.s_dt = a.dt; c.a_dt = a.dt;                      // prepared weights and queries as stored
+        c.nt = absorbed_streams(rows, a.d);
         const hipError_t e = launch_column_product(c, a.H, s);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
 }
 
-// softmax, weighted row sum, output projection and join; pr == nullptr: a.L_act contiguous rows per sequence
-hipError_t launch_after_scores(const AbsorbedArgs &a, int Lp, const PagedRows *pr, hipStream_t s)
+// output projection and join
+hipError_t launch_output(const AbsorbedArgs &a, hipStream_t s)
 {
-    const int64_t d = a.d;
     hipError_t e;
-    const int64_t BH = (int64_t)a.B * a.H;
-    hipLaunchKernelGGL(a.dt == 1 ? absorbed_softmax_kernel<1> : absorbed_softmax_kernel<0>, dim3((unsigned)((BH + 3) / 4)), dim3(256), 0, s,
-                       static_cast<const _Float16 *>(a.q), a.w_raw, a.stats, a.cvec, a.bvec,
-                       static_cast<_Float16 *>(a.w), a.sums, a.B, a.H, a.head_dim, a.L_act, Lp,
-                       a.scale * 1.4426950408889634f, pr ? pr->n_rows : static_cast<const int32_t *>(nullptr),
-                       pr ? Lp : a.L_act);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    {
-        ColArgs c;
-        c.S = static_cast<const _Float16 *>(a.act); c.s_batch = pr ? 0 : (int64_t)a.L_act * d; c.ld_s = d; c.R = a.L_act; c.n_cols = a.d;
-        c.A = static_cast<const _Float16 *>(a.w); c.a_batch = (int64_t)a.H * Lp; c.ld_a = Lp; c.a_rows = a.H;
-        c.Out = static_cast<_Float16 *>(a.Y); c.o_batch = a.H * d; c.ld_out = d;
-        c.shift = &a.sums[0].z; c.shift_batch = 4 * (int64_t)a.H; c.shift_stride = 4;
-        c.blk_list = pr ? pr->blk_list : nullptr; c.list_pitch = pr ? pr->list_pitch : 0; c.blk_log2 = pr ? pr->blk_log2 : 0;
-        c.R_list = pr ? pr->n_rows : nullptr;
-        c.s_dt = a.dt; c.a_dt = 0;                         // checkpoint rows as stored, weights w in fp16
-        if ((e = launch_column_product(c, a.B, s)) != hipSuccess) return e;
-    }
     for (int b0 = 0; b0 < a.B; b0 += kAbsorbMaxBatch) {
         const int Bc = a.B - b0 < kAbsorbMaxBatch ? a.B - b0 : kAbsorbMaxBatch;
         const bool block_mode = a.proj_part != nullptr && a.d >= kProjectBlockMinD;
@@ -777,14 +501,12 @@ hipError_t launch_after_scores(const AbsorbedArgs &a, int Lp, const PagedRows *p
 // its row of the block table (entries < 0: checkpoint block ~entry).
 //
 // index: one wavefront per request walks its table row and leaves (a) the request's checkpoint blocks in logical
-// order (list), their count, the rows of the last of them (only a request's final block can be partly filled) and
-// the request's number of checkpoint rows; (b) the same view of its KV blocks: a table row that holds only them,
+// order (list) and the request's number of checkpoint rows (only its final block can be partly filled); (b) the same view of its KV blocks: a table row that holds only them,
 // in order, and the request's number of cached tokens, i.e. what the block-table attention kernel needs to walk
 // the cached tokens alone.  Checkpoint blocks outside the pool prefix in use are left out.
 __global__ __launch_bounds__(256) void paged_index_kernel(const int32_t *__restrict__ table, int max_blocks,
                                                           const int32_t *__restrict__ seq_len, int blk_log2, int n_act_used, int B,
-                                                          int32_t *__restrict__ list, int32_t *__restrict__ count,
-                                                          int32_t *__restrict__ last_rows, int32_t *__restrict__ n_rows,
+                                                          int32_t *__restrict__ list, int32_t *__restrict__ n_rows,
                                                           int32_t *__restrict__ kv_table, int32_t *__restrict__ kv_len)
 {
     const int lane = threadIdx.x & 63;
@@ -815,102 +537,43 @@ __global__ __launch_bounds__(256) void paged_index_kernel(const int32_t *__restr
             const int rest = len - (last << blk_log2);
             return ((n_blocks - 1) << blk_log2) + (rest < bt ? rest : bt);
         };
-        count[b] = k0;
         n_rows[b] = rows_of(k0, last_i);
-        last_rows[b] = k0 > 0 ? n_rows[b] - ((k0 - 1) << blk_log2) : bt;
         kv_len[b] = rows_of(c0, last_c);
     }
 }
 
-// cu[0] = 0, cu[b + 1] = cu[b] + len[b]: one wavefront, 64 requests per step.
-__global__ __launch_bounds__(64) void paged_prefix_kernel(const int32_t *__restrict__ len, int B, int64_t *__restrict__ cu)
+// cu[0] = 0, cu[b + 1] = cu[b] + len[b], and the same of the requests' blocks of 2^rows_log2 checkpoint rows: one wavefront,
+// 64 requests per step.
+__global__ __launch_bounds__(64) void paged_prefix_kernel(const int32_t *__restrict__ len, const int32_t *__restrict__ n_rows, int rows_log2,
+                                                          int B, int64_t *__restrict__ cu, int32_t *__restrict__ cu_items)
 {
     const int lane = threadIdx.x;
     int64_t carry = 0;
-    if (lane == 0) cu[0] = 0;
+    int32_t carry_i = 0;
+    if (lane == 0) {
+        cu[0] = 0;
+        cu_items[0] = 0;
+    }
     for (int base = 0; base < B; base += 64) {
         const int i = base + lane;
         int64_t v = i < B ? len[i] : 0;
+        int32_t n = i < B ? (n_rows[i] + (1 << rows_log2) - 1) >> rows_log2 : 0;
 #pragma unroll
         for (int off = 1; off < 64; off <<= 1) {
             const int64_t up = __shfl_up(v, off, 64);
-            if (lane >= off) v += up;
-        }
-        if (i < B) cu[i + 1] = carry + v;
-        carry += __shfl(v, 63, 64);
-    }
-}
-
-// scores of 128 checkpoint rows of one request, as absorbed_scores_block_kernel (U is read once per 128 rows);
-// rows are numbered inside the request in the order of its block list (raw, stats: pitch Lp per request) and
-// found through that list (a block holds at least 16 rows, so the 8 rows of a load share a block).
-template <int RB, int DT>
-__global__ __launch_bounds__(256) void paged_scores_kernel(const _Float16 *__restrict__ act_pool, const _Float16 *__restrict__ U,
-                                                           float *__restrict__ raw, float4 *__restrict__ stats,
-                                                           const int32_t *__restrict__ list, const int32_t *__restrict__ n_rows,
-                                                           int B, int max_blocks, int blk_log2, int groups, int Lp, int H, int d, float eps)
-{
-    extern __shared__ __align__(16) unsigned char smem[];
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int item = gemm::xcd_regroup(blockIdx.x, groups * B);
-    const int64_t b = item / groups;
-    const int r0 = (item % groups) * 128;                  // first row of the workgroup inside the request
-    const int total = n_rows[b];
-    if (r0 >= total) return;                               // uniform over the workgroup, before any barrier
-    const int n = total - r0 < 128 ? total - r0 : 128;
-    const int32_t *blocks = list + b * max_blocks;
-    const int mask = (1 << blk_log2) - 1;
-    auto row_of = [=](int r) {
-        const int rr = r0 + r;
-        return act_pool + (((int64_t)blocks[rr >> blk_log2] << blk_log2) + (rr & mask)) * d;
-    };
-    float16_t acc[RB];
-    float m1[4], m2[4];
-    _Float16 first[4];
-    skinny::block_product_rows<RB, false, true, DT>(row_of, n, U + b * d, H, (int64_t)B * d, 0, d / 64, smem, acc, m1, m2, first);
-    const int rw = r0 + 32 * wave;                         // first row of this wavefront
-    const int rows = total - rw < 32 ? (total - rw > 0 ? total - rw : 0) : 32;
-    const int ln = lane & 31, lh = lane >> 5;
-    if (ln < rows) {
-#pragma unroll
-        for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int h = 32 * rb + 8 * (r >> 2) + 4 * lh + (r & 3);
-                if (h < H) raw[(b * H + h) * Lp + rw + ln] = acc[rb][r];
+            const int32_t up_i = __shfl_up(n, off, 64);
+            if (lane >= off) {
+                v += up;
+                n += up_i;
             }
+        }
+        if (i < B) {
+            cu[i + 1] = carry + v;
+            cu_items[i + 1] = carry_i + n;
+        }
+        carry += __shfl(v, 63, 64);
+        carry_i += __shfl(n, 63, 64);
     }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int row = 8 * j + (lane >> 3);
-        if ((lane & 7) == 0 && row < rows) stats[b * Lp + rw + row] = row_stats(m1[j], m2[j], (float)first[j], d, eps);
-    }
-}
-
-template <int RB, int DT>
-hipError_t launch_paged_scores_as(const PagedAbsorbedArgs &p, int Lp, int blk_log2, hipStream_t s)
-{
-    const AbsorbedArgs &a = p.abs;
-    const int groups = (a.L_act + 127) / 128;              // of the longest request possible; shorter ones leave early
-    const int64_t items = (int64_t)a.B * groups;
-    if (items <= 0) return hipSuccess;
-    if (items > 0x7fffffffLL) return hipErrorInvalidValue;
-    auto kern = paged_scores_kernel<RB, DT>;
-    constexpr int lds = skinny::block_lds_bytes<RB>();
-    static LdsOnce lds_once;
-    hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(kern), lds, lds_once);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3((unsigned)items), dim3(256), lds, s,
-                       static_cast<const _Float16 *>(a.act), static_cast<const _Float16 *>(a.U), a.w_raw, a.stats,
-                       p.list, p.n_rows, a.B, p.max_blocks, blk_log2, groups, Lp, a.H, a.d, a.eps);
-    return hipGetLastError();
-}
-
-template <int RB>
-hipError_t launch_paged_scores(const PagedAbsorbedArgs &p, int Lp, int blk_log2, hipStream_t s)
-{
-    return p.abs.dt == 1 ? launch_paged_scores_as<RB, 1>(p, Lp, blk_log2, s) : launch_paged_scores_as<RB, 0>(p, Lp, blk_log2, s);
 }
 
 }  // namespace
@@ -920,17 +583,10 @@ hipError_t launch_absorbed(const AbsorbedArgs &a, hipStream_t s)
     if (a.B <= 0 || a.L_act <= 0) return hipSuccess;
     if (a.H > kAbsorbMaxHeads || a.d % 64 != 0 || a.B > 65535 || (int64_t)a.H * a.head_dim != a.d || (a.dt != 0 && a.dt != 1))
         return hipErrorInvalidValue;
-    const int Lp = absorbed_row_pitch(a.L_act);
-    hipError_t e = launch_carry(a, s);
-    if (e != hipSuccess) return e;
-    switch ((a.H + 31) / 32) {
-    case 1: e = launch_scores<1>(a, Lp, s); break;
-    case 2: e = launch_scores<2>(a, Lp, s); break;
-    case 3: e = launch_scores<3>(a, Lp, s); break;
-    default: e = launch_scores<4>(a, Lp, s); break;
-    }
-    if (e != hipSuccess) return e;
-    return launch_after_scores(a, Lp, nullptr, s);
+    const int64_t rows = (int64_t)a.B * a.L_act;
+    hipError_t e = launch_carry(a, rows, s);
+    if (e == hipSuccess) e = launch_absorbed_stream(a, nullptr, rows, s);
+    return e == hipSuccess ? launch_output(a, s) : e;
 }
 
 // The two views of the block table that the paged step without regeneration works on (see paged_index_kernel).
@@ -942,17 +598,18 @@ hipError_t launch_paged_index(const PagedAbsorbedArgs &p, hipStream_t s)
     int blk_log2 = 0;
     while ((1 << blk_log2) < p.block_tokens) ++blk_log2;
     hipLaunchKernelGGL(paged_index_kernel, dim3((unsigned)((a.B + 3) / 4)), dim3(256), 0, s,
-                       p.block_table, p.max_blocks, p.seq_len, blk_log2, p.n_act_used, a.B, p.list, p.count, p.last_rows, p.n_rows,
+                       p.block_table, p.max_blocks, p.seq_len, blk_log2, p.n_act_used, a.B, p.list, p.n_rows,
                        p.kv_table, p.kv_len);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(paged_prefix_kernel, dim3(1), dim3(64), 0, s, p.kv_len, a.B, p.kv_cu);
+    hipLaunchKernelGGL(paged_prefix_kernel, dim3(1), dim3(64), 0, s, p.kv_len, p.n_rows,
+                       absorbed_rows_log2((int64_t)p.n_act_used * p.block_tokens, a.d, a.H), a.B, p.kv_cu, p.cu_items);
     return hipGetLastError();
 }
 
 // After launch_paged_index (and the attention over the KV view).  a.abs: act = the activation pool, L_act =
 // max_blocks * block_tokens (the most rows a request can have), L_kv != 0 iff out_c / lse_c hold the attention
-// over the KV blocks; stats and w_raw, w have pitch absorbed_row_pitch(L_act).
+// over the KV blocks; w has pitch absorbed_row_pitch(L_act).
 hipError_t launch_paged_absorbed(const PagedAbsorbedArgs &p, hipStream_t s)
 {
     const AbsorbedArgs &a = p.abs;
@@ -963,19 +620,12 @@ hipError_t launch_paged_absorbed(const PagedAbsorbedArgs &p, hipStream_t s)
         return hipErrorInvalidValue;
     int blk_log2 = 0;
     while ((1 << blk_log2) < p.block_tokens) ++blk_log2;
-    const int Lp = absorbed_row_pitch(a.L_act);
-    hipError_t e = launch_carry(a, s);
-    if (e != hipSuccess) return e;
-    switch ((a.H + 31) / 32) {
-    case 1: e = launch_paged_scores<1>(p, Lp, blk_log2, s); break;
-    case 2: e = launch_paged_scores<2>(p, Lp, blk_log2, s); break;
-    case 3: e = launch_paged_scores<3>(p, Lp, blk_log2, s); break;
-    default: e = launch_paged_scores<4>(p, Lp, blk_log2, s); break;
-    }
-    if (e != hipSuccess) return e;
-    PagedRows pr;
-    pr.blk_list = p.list; pr.n_rows = p.n_rows; pr.list_pitch = p.max_blocks; pr.blk_log2 = blk_log2;
-    return launch_after_scores(a, Lp, &pr, s);
+    const int64_t rows = (int64_t)p.n_act_used * p.block_tokens;
+    hipError_t e = launch_carry(a, rows, s);
+    AbsorbedRows pr;
+    pr.list = p.list; pr.n_rows = p.n_rows; pr.cu_items = p.cu_items; pr.list_pitch = p.max_blocks; pr.blk_log2 = blk_log2;
+    if (e == hipSuccess) e = launch_absorbed_stream(a, &pr, rows, s);
+    return e == hipSuccess ? launch_output(a, s) : e;
 }
 
 }  // namespace hk

@@ -475,12 +475,19 @@ size_t absorbed_proj_floats(const hk_shape *s, int64_t B)
     return (size_t)parts * rows * s->d;
 }
 
+// Blocks of the score pass that a sequence of up to L rows has, `rows` of them in all sequences.
+size_t absorbed_blocks(const hk_shape *s, int64_t L, int64_t rows)
+{
+    const int log2 = hk::absorbed_rows_log2(rows, s->d, s->n_heads);
+    return (size_t)((L + (1 << log2) - 1) >> log2);
+}
+
 struct AbsorbedPlan {
     int64_t M, BH;
     int n_waves;               // wavefronts of the attention kernel over the cached segment
     int Lp;
     float scale;
-    size_t off_stats, off_prep, off_u, off_raw, off_w, off_sums, off_y, off_outc, off_lse, off_proj, off_partial, total;
+    size_t off_prep, off_u, off_c12, off_w, off_part, off_sums, off_y, off_outc, off_lse, off_proj, off_partial, total;
 };
 
 int make_absorbed_plan(const hk_shape *s, int64_t B, int64_t L_kv, int64_t L_act, AbsorbedPlan *p)
@@ -493,13 +500,13 @@ int make_absorbed_plan(const hk_shape *s, int64_t B, int64_t L_kv, int64_t L_act
     p->Lp = hk::absorbed_row_pitch((int)L_act);
     size_t end = 0;
     auto take = [&](size_t bytes) { const size_t at = end; end += align_up(bytes); return at; };
-    p->off_stats = take((size_t)p->M * sizeof(float4));
     p->off_prep = take(L_act > 0 ? prepared_layout(s->d).total : 0);
     const size_t bh = (size_t)p->BH;
     const bool act = L_act > 0;
     p->off_u = take(act ? bh * s->d * 2 : 0);
-    p->off_raw = take(act ? bh * p->Lp * 4 : 0);
+    p->off_c12 = take(act ? bh * sizeof(float2) : 0);
     p->off_w = take(act ? bh * p->Lp * 2 : 0);
+    p->off_part = take(act ? bh * absorbed_blocks(s, L_act, p->M) * sizeof(float4) : 0);
     p->off_sums = take(act ? bh * sizeof(float4) : 0);
     p->off_y = take(act ? bh * s->d * 2 : 0);
     p->off_outc = take(act ? bh * s->head_dim * 2 : 0);
@@ -580,13 +587,14 @@ int hk_hybrid_decode_attn_absorbed(const hk_shape *shape, const void *q,
         pp = dst;
     }
     hk::AbsorbedArgs a;
-    a.q = q; a.act = act; a.stats = reinterpret_cast<float4 *>(ws + p.off_stats);
+    a.q = q; a.act = act;
     a.Wp = pp + PL.off_w;
     a.cvec = reinterpret_cast<const float *>(pp + PL.off_c);
     a.bvec = reinterpret_cast<const float *>(pp + PL.off_b);
     a.U = ws + p.off_u;
-    a.w_raw = reinterpret_cast<float *>(ws + p.off_raw);
+    a.c12 = reinterpret_cast<float2 *>(ws + p.off_c12);
     a.w = ws + p.off_w;
+    a.part = reinterpret_cast<float4 *>(ws + p.off_part);
     a.sums = reinterpret_cast<float4 *>(ws + p.off_sums);
     a.Y = ws + p.off_y;
     a.out_c = ws + p.off_outc;
@@ -807,8 +815,8 @@ namespace {
 struct PagedAbsorbedPlan {
     int n_waves, Lp;
     float scale;
-    size_t off_stats, off_prep, off_u, off_raw, off_w, off_sums, off_y, off_outc, off_lse, off_list, off_count, off_last,
-        off_rows, off_kvtab, off_kvlen, off_kvcu, off_proj, off_partial, total;
+    size_t off_prep, off_u, off_c12, off_w, off_part, off_sums, off_y, off_outc, off_lse, off_list, off_rows, off_items, off_kvtab,
+        off_kvlen, off_kvcu, off_proj, off_partial, total;
 };
 
 int make_paged_absorbed_plan(const hk_shape *s, int64_t B, const hk_paged_cache *c, PagedAbsorbedPlan *p)
@@ -825,19 +833,18 @@ int make_paged_absorbed_plan(const hk_shape *s, int64_t B, const hk_paged_cache 
     const size_t b = (size_t)B, bh = b * s->n_heads;
     size_t end = 0;
     auto take = [&](size_t bytes) { const size_t at = end; end += align_up(bytes); return at; };
-    p->off_stats = take(act ? b * p->Lp * sizeof(float4) : 0);
     p->off_prep = take(act ? prepared_layout(s->d).total : 0);
     p->off_u = take(act ? bh * s->d * 2 : 0);
-    p->off_raw = take(act ? bh * p->Lp * 4 : 0);
+    p->off_c12 = take(act ? bh * sizeof(float2) : 0);
     p->off_w = take(act ? bh * p->Lp * 2 : 0);
+    p->off_part = take(act ? bh * absorbed_blocks(s, max_rows, (int64_t)c->n_act_used * c->block_tokens) * sizeof(float4) : 0);
     p->off_sums = take(act ? bh * sizeof(float4) : 0);
     p->off_y = take(act ? bh * s->d * 2 : 0);
     p->off_outc = take(act ? bh * s->head_dim * 2 : 0);
     p->off_lse = take(act ? bh * sizeof(float2) : 0);
     p->off_list = take(act ? b * c->max_blocks * sizeof(int32_t) : 0);
-    p->off_count = take(act ? b * sizeof(int32_t) : 0);
-    p->off_last = take(act ? b * sizeof(int32_t) : 0);
     p->off_rows = take(act ? b * sizeof(int32_t) : 0);
+    p->off_items = take(act ? (b + 1) * sizeof(int32_t) : 0);
     p->off_kvtab = take(act ? b * c->max_blocks * sizeof(int32_t) : 0);
     p->off_kvlen = take(act ? b * sizeof(int32_t) : 0);
     p->off_kvcu = take(act ? (b + 1) * sizeof(int64_t) : 0);
@@ -911,13 +918,14 @@ int hk_paged_decode_attn_absorbed(const hk_shape *shape, const void *q, int32_t 
     }
     hk::PagedAbsorbedArgs pa;
     hk::AbsorbedArgs &a = pa.abs;
-    a.q = q; a.act = cache->act_pool; a.stats = reinterpret_cast<float4 *>(ws + p.off_stats);
+    a.q = q; a.act = cache->act_pool;
     a.Wp = pp + PL.off_w;
     a.cvec = reinterpret_cast<const float *>(pp + PL.off_c);
     a.bvec = reinterpret_cast<const float *>(pp + PL.off_b);
     a.U = ws + p.off_u;
-    a.w_raw = reinterpret_cast<float *>(ws + p.off_raw);
+    a.c12 = reinterpret_cast<float2 *>(ws + p.off_c12);
     a.w = ws + p.off_w;
+    a.part = reinterpret_cast<float4 *>(ws + p.off_part);
     a.sums = reinterpret_cast<float4 *>(ws + p.off_sums);
     a.Y = ws + p.off_y;
     a.out_c = ws + p.off_outc;
@@ -932,9 +940,8 @@ int hk_paged_decode_attn_absorbed(const hk_shape *shape, const void *q, int32_t 
     pa.block_table = cache->block_table; pa.seq_len = cache->seq_len;
     pa.max_blocks = cache->max_blocks; pa.block_tokens = cache->block_tokens; pa.n_act_used = cache->n_act_used;
     pa.list = reinterpret_cast<int32_t *>(ws + p.off_list);
-    pa.count = reinterpret_cast<int32_t *>(ws + p.off_count);
-    pa.last_rows = reinterpret_cast<int32_t *>(ws + p.off_last);
     pa.n_rows = reinterpret_cast<int32_t *>(ws + p.off_rows);
+    pa.cu_items = reinterpret_cast<int32_t *>(ws + p.off_items);
     pa.kv_table = reinterpret_cast<int32_t *>(ws + p.off_kvtab);
     pa.kv_len = reinterpret_cast<int32_t *>(ws + p.off_kvlen);
     pa.kv_cu = reinterpret_cast<int64_t *>(ws + p.off_kvcu);

@@ -151,14 +151,14 @@ hipError_t launch_paged_decode(const PagedAttnArgs &a, hipStream_t s);
 struct AbsorbedArgs {
     const void *q;             // [B, H, dh]
     const void *act;           // [B, L_act, d]
-    float4 *stats;             // [B * L_act] scratch: (rstd, mean, -(mean - first element) rstd, -) of every checkpoint row
     const void *Wp;            // prepared layer: [2d, d] gamma-scaled weights,
     const float *cvec, *bvec;  //   [2d] and [2d + 1] as in KvGemmArgs
     void *U;                   // [H, B, d] fp16 scratch: the query carried through the key weights
-    float *w_raw;              // [B, H, Lp] fp32 scratch: x_t . U  (Lp = absorbed_row_pitch(L_act))
-    void *w;                   // [B, H, Lp] fp16 scratch: softmax weight times rstd, normalised; zero past L_act
-    float4 *sums;              // [B, H] scratch: (maximum, sum p, sum w mean, -)
-    void *Y;                   // [B, H, d] fp16 scratch: weighted sum of the raw checkpoint rows
+    float2 *c12;               // [B, H] scratch: (q . c_K, q . b'_K)
+    void *w;                   // [B, H, Lp] fp16 scratch: weights of the rows (Lp = absorbed_row_pitch(L_act)), see absorbed_stream.hip
+    float4 *part;              // [B, blocks, H] scratch: (reference, sum p, sum w mean, -) of every block of 2^absorbed_rows_log2 rows
+    float4 *sums;              // [B, H] scratch: (reference, sum p, -, -) of the sequence
+    void *Y;                   // [B, H, d] fp16 scratch: weighted sum of the checkpoint rows less their means
     const void *out_c;         // [B, H, dh]: attention over the cached segment alone (unused when L_kv == 0)
     const float2 *lse_c;       // [B, H]: its (maximum, denominator)
     void *out;                 // [B, H, dh]
@@ -170,8 +170,19 @@ struct AbsorbedArgs {
 };
 constexpr int kAbsorbMaxHeads = 128;   // heads (rows of the small operand of the score product) per sequence
 constexpr int kAbsorbMaxBatch = 128;   // sequences one launch of the output projection takes
-int absorbed_row_pitch(int L_act);     // elements between the rows of w_raw and w
+int absorbed_row_pitch(int L_act);     // elements between the rows of w
+int absorbed_rows_log2(int64_t rows, int d, int H);   // block of the score pass for `rows` checkpoint rows in all
 void absorbed_project_parts(int d, int H, int *parts, int *steps_per_part);   // how the output projection cuts its reduction axis
+bool absorbed_streams(int64_t rows, int d);                  // whether that many rows outgrow the last-level cache
+// Checkpoint rows in blocks of 2^blk_log2 rows scattered over a pool.
+struct AbsorbedRows {
+    const int32_t *list;       // [B, list_pitch]: the checkpoint blocks of every sequence, in logical order
+    const int32_t *n_rows;     // [B]: its checkpoint rows
+    const int32_t *cu_items;   // [B + 1]: prefix sums of its blocks of the score pass
+    int list_pitch, blk_log2;
+};
+// The two passes over the checkpoint rows, `rows` in all or at most: U, c12 -> w, part -> Y, sums (see absorbed_stream.hip).
+hipError_t launch_absorbed_stream(const AbsorbedArgs &a, const AbsorbedRows *pr, int64_t rows, hipStream_t s);
 // The checkpoint part of the decode attention without regenerating K/V (see absorbed.hip).
 hipError_t launch_absorbed(const AbsorbedArgs &a, hipStream_t s);
 
@@ -181,7 +192,8 @@ struct PagedAbsorbedArgs {
     const int32_t *seq_len;            // [B]
     int max_blocks, block_tokens, n_act_used;
     int32_t *list;                     // [B, max_blocks] scratch: the checkpoint blocks of every request in logical order
-    int32_t *count, *last_rows, *n_rows;   // [B] scratch each: their number, the rows of the last one, the request's checkpoint rows
+    int32_t *n_rows;                   // [B] scratch: the request's checkpoint rows
+    int32_t *cu_items;                 // [B + 1] scratch: prefix sums of its blocks of the score pass
     int32_t *kv_table;                 // [B, max_blocks] scratch: the KV blocks of every request in logical order
     int32_t *kv_len;                   // [B] scratch: the request's cached tokens
     int64_t *kv_cu;                    // [B + 1] scratch: their prefix sums

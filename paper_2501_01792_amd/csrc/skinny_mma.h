@@ -96,11 +96,11 @@ __device__ __forceinline__ float (*moments(unsigned char *smem))[kSlab][2]
     return reinterpret_cast<float (*)[kSlab][2]>(smem + lds_bytes<RB>());
 }
 
-// S: first row of the slab (row stride ld_s elements; rows >= s_rows are not read: the last valid row stands
+// row_of(c): address of streamed row c of the slab (rows >= s_rows are not read: the last valid row stands
 // in for them), stored as SDT.  A: first small row (row stride ld_a; rows >= a_rows likewise), fp16.  d % 64 == 0.
 // Returns red with red[w][m][c], w = 0..3, the partial sum of k quarter w; a barrier has been passed.
-template <int RB, bool NT, bool STATS = false, int SDT = 0>
-__device__ __forceinline__ float (*slab_product(const _Float16 *__restrict__ S, int s_rows, int64_t ld_s,
+template <int RB, bool NT, bool STATS, int SDT, typename RowOf>
+__device__ __forceinline__ float (*slab_product(RowOf row_of, int s_rows,
                                                 const _Float16 *__restrict__ A, int a_rows, int64_t ld_a,
                                                 int d, unsigned char *smem))[RB * 32][kSlab]
 {
@@ -121,7 +121,7 @@ __device__ __forceinline__ float (*slab_product(const _Float16 *__restrict__ S, 
     for (int j = 0; j < 4; ++j) {
         int c = 8 * j + g_row;
         if (c >= s_rows) c = s_rows - 1;                   // clamp: rows past the end are computed, never used
-        wp[j] = S + (int64_t)c * ld_s + 8 * g_chunk;
+        wp[j] = row_of(c) + 8 * g_chunk;
     }
     const _Float16 *xp[RB][4];
 #pragma unroll
@@ -278,42 +278,28 @@ __device__ __forceinline__ float (*slab_product(const _Float16 *__restrict__ S, 
 // wavefront's private LDS block (row-wise in, MFMA operand layout out) as in slab_product.  There is no
 // reduction across wavefronts: the result stays in registers,
 //   acc[rb][r] = D[32 rb + 8 (r/4) + 4 (lane/32) + r%4][32 wave + lane%32].
-// STATS: rows enter the product minus their first element; m1[j], m2[j] are the first two moments of row
-// 32 wave + 8 j + lane / 8 (complete in every lane of the row's 8), first[j] that row's first element.
 // All 256 threads must call it (barriers), with the same k range.  n_rows >= 1 rows of S are valid; rows
 // past them are computed from the last valid row and must not be stored.
 template <int RB>
 constexpr int block_lds_bytes() { return 4 * kBlockBytes + 2 * RB * kBlockBytes; }
 
-// row_of(r) is the address of streamed row r, r < n_rows (rows need not be evenly spaced: they may sit in
-// blocks scattered over a pool).
-// SDT: storage type of the streamed rows (the small operand A is fp16).
-template <int RB, bool NT, bool STATS, int SDT = 0, typename RowOf>
-__device__ __forceinline__ void block_product_rows(RowOf row_of, int n_rows,
-                                                   const _Float16 *__restrict__ A, int a_rows, int64_t ld_a,
-                                                   int k_begin, int k_steps, unsigned char *smem,
-                                                   float16_t (&acc)[RB], float (&m1)[4], float (&m2)[4], _Float16 (&first)[4])
+// S: first row of the block, ld_s the distance between rows; SDT: storage type of the streamed rows (the small operand A is
+// fp16).
+template <int RB, bool NT, int SDT = 0>
+__device__ __forceinline__ void block_product(const _Float16 *__restrict__ S, int n_rows, int64_t ld_s,
+                                              const _Float16 *__restrict__ A, int a_rows, int64_t ld_a,
+                                              int k_begin, int k_steps, unsigned char *smem, float16_t (&acc)[RB])
 {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g_row = lane >> 3, g_chunk = lane & 7;
     const int ln = lane & 31, lh = lane >> 5;
     const _Float16 *sp[4];
-    half2_t shift[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         int r = 32 * wave + 8 * j + g_row;
         if (r >= n_rows) r = n_rows - 1;
-        const _Float16 *row = row_of(r);
-        if constexpr (STATS) {
-            first[j] = stored_to_half<SDT>(row);
-            shift[j] = half2_t{first[j], first[j]};
-        } else {
-            first[j] = (_Float16)0.f;
-        }
-        sp[j] = row + 64 * (int64_t)k_begin + 8 * g_chunk;
-        m1[j] = 0.f;
-        m2[j] = 0.f;
+        sp[j] = S + (int64_t)r * ld_s + 64 * (int64_t)k_begin + 8 * g_chunk;
     }
     const int t_row = tid >> 3, t_chunk = tid & 7;         // the shared tile: thread -> (row of every 32-row block, chunk)
     const _Float16 *ap[RB];
@@ -372,18 +358,7 @@ __device__ __forceinline__ void block_product_rows(RowOf row_of, int n_rows,
                 put_a((u + 1) % kDepth, (sc + 1) & 1);     // the tile of step sc + 1, for the next pass
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
-                    half8_t piece = to_half8<SDT>(sv[u][j]);
-                    if constexpr (STATS) {
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            const half2_t pr = half2_t{piece[2 * e], piece[2 * e + 1]} - shift[j];
-                            m1[j] = __builtin_amdgcn_fdot2(pr, half2_t{(_Float16)1.f, (_Float16)1.f}, m1[j], false);
-                            m2[j] = __builtin_amdgcn_fdot2(pr, pr, m2[j], false);
-                            piece[2 * e] = pr[0];
-                            piece[2 * e + 1] = pr[1];
-                        }
-                    }
-                    *reinterpret_cast<half8_t *>(my + wr_off[j]) = piece;
+                    *reinterpret_cast<half8_t *>(my + wr_off[j]) = to_half8<SDT>(sv[u][j]);
                 }
                 // The operand fragments of k piece jj + 1 are read while the MFMAs of piece jj run: left to the
                 // compiler every MFMA waits for its own LDS read (register pressure makes it reuse one register set).
@@ -408,26 +383,6 @@ __device__ __forceinline__ void block_product_rows(RowOf row_of, int n_rows,
             }
         }
     }
-    if constexpr (STATS) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-            for (int off = 1; off < 8; off <<= 1) {
-                m1[j] += __shfl_xor(m1[j], off, 64);
-                m2[j] += __shfl_xor(m2[j], off, 64);
-            }
-    }
-}
-
-// Evenly spaced rows: S is the first row of the block, ld_s the distance between rows.
-template <int RB, bool NT, bool STATS, int SDT = 0>
-__device__ __forceinline__ void block_product(const _Float16 *__restrict__ S, int n_rows, int64_t ld_s,
-                                              const _Float16 *__restrict__ A, int a_rows, int64_t ld_a,
-                                              int k_begin, int k_steps, unsigned char *smem,
-                                              float16_t (&acc)[RB], float (&m1)[4], float (&m2)[4], _Float16 (&first)[4])
-{
-    block_product_rows<RB, NT, STATS, SDT>([=](int r) { return S + (int64_t)r * ld_s; }, n_rows, A, a_rows, ld_a, k_begin, k_steps,
-                                      smem, acc, m1, m2, first);
 }
 
 }  // namespace skinny
