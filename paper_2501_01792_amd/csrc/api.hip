@@ -355,6 +355,7 @@ int hybrid_step(const hk_shape *shape, const void *q,
     a.K1 = K_regen; a.V1 = V_regen; a.L1 = L_act;
     a.BH = (int)p.BH; a.head_dim = shape->head_dim; a.scale = p.scale;
     a.n_waves = p.n_waves;
+    a.ranges_given = shape->attn_splits > 0;
     a.partial = reinterpret_cast<float *>(ws + p.off_partial);
     a.out = out;
     a.lse = nullptr;
@@ -432,6 +433,7 @@ int hk_hybrid_decode_attn_two_stream(const hk_shape *shape, const void *q,
     a.K1 = nullptr; a.V1 = nullptr; a.L1 = 0;
     a.BH = (int)p.base.BH; a.head_dim = shape->head_dim; a.scale = p.base.scale;
     a.n_waves = p.waves_c;
+    a.ranges_given = shape->attn_splits > 0;
     a.partial = reinterpret_cast<float *>(ws + p.off_part_c);
     a.out = ws + p.off_out_c;
     a.lse = reinterpret_cast<float2 *>(ws + p.off_lse_c);
@@ -567,6 +569,7 @@ int hk_hybrid_decode_attn_absorbed(const hk_shape *shape, const void *q,
         a.K1 = nullptr; a.V1 = nullptr; a.L1 = 0;
         a.BH = (int)p.BH; a.head_dim = shape->head_dim; a.scale = p.scale;
         a.n_waves = p.n_waves;
+        a.ranges_given = shape->attn_splits > 0;
         a.partial = reinterpret_cast<float *>(ws + p.off_partial);
         a.out = L_act > 0 ? static_cast<void *>(ws + p.off_outc) : out;
         a.lse = L_act > 0 ? reinterpret_cast<float2 *>(ws + p.off_lse) : nullptr;
@@ -950,6 +953,7 @@ int hk_paged_decode_attn_absorbed(const hk_shape *shape, const void *q, int32_t 
         // attention over the cached tokens alone, through the KV view of the table; how many there are only the
         // device knows (the launch is sized for all tokens being cached)
         t.block_table = pa.kv_table; t.seq_len = pa.kv_len; t.cu_tokens = pa.kv_cu; t.total_dev = pa.kv_cu + B;
+        t.other_tokens = (int64_t)cache->n_act_used * cache->block_tokens;
         t.out = ws + p.off_outc;
         t.lse = reinterpret_cast<float2 *>(ws + p.off_lse);
         if (hk::launch_paged_decode(t, hs) != hipSuccess) return HK_ERR_LAUNCH;

@@ -14,13 +14,15 @@
 //     is unique, and makes the partials of one pair a contiguous run.  A second small kernel
 //     merges the run of every pair by log-sum-exp.  Wavefronts of this kernel never talk to each other:
 //     no LDS, no barrier.  (Those of the merge may: attn_merge.h.)
+//   * Where a workgroup per pair keeps the chip as busy (pair_in_one_launch), its wavefronts merge in LDS and there is
+//     neither a second kernel nor a partial in memory.
 //   * A wavefront consumes 64 tokens at a time (attn_tile.h).  dh/8 lanes cover one row with 16-byte loads, so
 //     every load instruction of a wavefront reads whole, consecutive rows (1 KiB contiguous), and all K and V
 //     loads of the 64 tokens are issued before the first use: 128 registers of rows, 3 wavefronts per SIMD.  Left to
 //     the compiler (4 per SIMD) the V rows were asked for behind the K rows' use, a second memory latency per step,
 //     and in bf16 they were widened on arrival (246 registers, 2 per SIMD).
-//   * Small problems are cut into ranges of one step each, aligned to the pairs, so that they too fill the chip and pay
-//     one latency (with at least 128 tokens per range, 64,000 positions ran on 125 of 256 compute units).
+//   * Small problems that are cut into ranges have ranges of one step each, aligned to the pairs, so that they too fill the
+//     chip and pay one latency (with at least 128 tokens per range, 64,000 positions ran on 125 of 256 compute units).
 // Measured with the merge (profiles/decode_attention_cached.txt; in brackets with V asked for behind K, at least 128 tokens a
 // range and a merge that walks the partials one by one): 4.8 GB fp16 727 us, 6.65 TB/s (737), bf16 747 (771); 268 MB 43.9
 // (47.5); 33 MB of one request 9.9 (36.4).
@@ -99,6 +101,57 @@ __global__ __launch_bounds__(kThreads, 3) void flash_decode_kernel(
     }
 }
 
+// One workgroup per pair: its P wavefronts take the steps of the two segments in turn and merge in LDS, so that one launch
+// does what the ranges and their merge do in two (pair_in_one_launch says when).  Bound by the latency of a step and of a
+// launch for short contexts; for long ones by what one compute unit can ask for, 58 GB/s: 8 wavefronts of a pair were no
+// faster than 4.  1 and 2 wavefronts a pair, several pairs a workgroup, for contexts of as many steps.
+template <int DH, int DT, int P>
+__global__ __launch_bounds__(kThreads, 3) void flash_pair_kernel(
+    const typename Elem<DT>::T *__restrict__ q,
+    const typename Elem<DT>::T *__restrict__ K0, const typename Elem<DT>::T *__restrict__ V0,
+    const typename Elem<DT>::T *__restrict__ K1, const typename Elem<DT>::T *__restrict__ V1,
+    int L0, int L1, int BH, float scale_log2e, typename Elem<DT>::T *__restrict__ out, float2 *__restrict__ lse)
+{
+    typedef typename Elem<DT>::T elem_t;
+    typedef typename Elem<DT>::V8 half8_t;
+    typedef attn::Tile<DH, DT> tile_t;
+    constexpr int LPR = tile_t::LPR, RPL = tile_t::RPL, NL = tile_t::NL;
+    __shared__ __align__(16) float part[kWavesPerBlock][DH + 2];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int bh = blockIdx.x * (kWavesPerBlock / P) + wave / P;
+    const bool live = bh < BH;
+    if (!live) bh = BH - 1;              // works on the last pair (the workgroup shares a barrier), stores nothing
+    const int g = lane / LPR, c = lane % LPR;
+    const half8_t qv = *reinterpret_cast<const half8_t *>(q + (int64_t)bh * DH + c * 8);
+    tile_t tile;
+    tile.clear();
+    const int n0 = (L0 + kTile - 1) / kTile, n = n0 + (L1 + kTile - 1) / kTile;     // steps of the two segments
+    for (int s = wave % P; s < n; s += P) {
+        const bool second = s >= n0;
+        const int Ls = second ? L1 : L0, tb = (second ? s - n0 : s) * kTile;
+        const int64_t at = ((int64_t)bh * Ls + tb) * DH;
+        const int rows = Ls - tb < kTile ? Ls - tb : kTile;
+        const __amdgpu_buffer_rsrc_t Kt = attn::step_rows((second ? K1 : K0) + at, rows, DH);
+        const __amdgpu_buffer_rsrc_t Vt = attn::step_rows((second ? V1 : V0) + at, rows, DH);
+        half8_t kr[NL], vr[NL];
+#pragma unroll
+        for (int i = 0; i < NL; ++i) kr[i] = attn::step_load<half8_t>(Kt, i, lane);
+#pragma unroll
+        for (int i = 0; i < NL; ++i) vr[i] = attn::step_load<half8_t>(Vt, i, lane);
+        __builtin_amdgcn_sched_barrier(0);                     // every load of the step is on its way before the first use
+        tile.consume(qv, kr, vr, lane, c * RPL + g < rows, scale_log2e);
+    }
+    tile.store(part[wave], lane);
+    __syncthreads();
+    if (!live || wave % P != 0) return;
+    merge::Shared<DH, 1> none;
+    float m, l, o[DH / 64];
+    merge::merge_run<DH, 1>(part[wave], P, none, m, l, o);
+    merge::store_row<DH>(out + (int64_t)bh * DH, o, l);
+    if (lse && lane == 0) lse[bh] = make_float2(m, l);
+}
+
 // Log-sum-exp merge of the partials of every (sequence, head), P wavefronts each: those of the wavefronts whose range
 // meets the pair's positions [bh L, (bh+1) L), at indices (wavefront + bh).
 template <int DH, int DT, int P>
@@ -120,6 +173,28 @@ __global__ __launch_bounds__(merge::kThreads) void merge_partials_kernel(const f
     if (lse && (threadIdx.x & 63) == 0) lse[bh] = make_float2(m, l);
 }
 
+int pair_steps(int L0, int L1) { return (L0 + kTile - 1) / kTile + (L1 + kTile - 1) / kTile; }
+
+// One workgroup per pair, or ranges and a merge?  Ranges balance any number of pairs over the chip, at the price of a second
+// launch, partials in memory and ranges that end inside a pair.  n counts 16 KB of K and V, what a step of 64 tokens of
+// head_dim 64 reads.  Measured over 1 to 4608 pairs x 200 to 4096 tokens, both head dimensions and types, one workgroup per pair
+// against ranges (us, replayed from a graph, fp16, head_dim 128 unless said):
+//   * short contexts: 8 pairs of 400 tokens 6.3 / 8.0, 72 of 200 5.2 / 8.7; at 1000 tokens 8 pairs take 11.4 / 8.9 and 32 take
+//     11.9 / 9.7: too few compute units ask for the rows
+//   * from 128 pairs on: 128 of 1000 tokens 15.5 / 17.0, of 4096 52.4 / 49.3
+//   * 180 to 256 pairs, nearly one per compute unit: 200 of 1000 tokens 19.4 / 25.0, of 4096 68.7 / 75.4; 256: 23.8 / 27.9, 86.4 / 92.7
+//   * 257 to 447: some compute units get two: 290 of 700 tokens faster, of 1000 32.1 / 31.8; 352 of 2000 70.7 / 67.4
+//   * from 448 on the workgroups' own order evens that out: 480 of 2000 tokens 81.6 / 86.3, 4608 707 / 731; level from 3000
+//     tokens on (1100 pairs 273 / 269)
+bool pair_in_one_launch(int64_t pairs, int steps, int head_dim)
+{
+    const int n = steps * (head_dim / 64);
+    if (pairs < 128) return n <= 16;
+    if (pairs < 180) return n <= 32;
+    if (pairs <= 256) return true;
+    return n <= (pairs < 448 ? 24 : 64);
+}
+
 template <int DH, int DT, int P>
 void launch_merge(const AttnArgs &a, int L, int64_t total, hipStream_t s)
 {
@@ -135,6 +210,21 @@ hipError_t launch_dh(const AttnArgs &a, hipStream_t s)
     const int L = a.L0 + a.L1;
     const int64_t total = (int64_t)a.BH * L;
     const float scale_log2e = a.scale * 1.4426950408889634f;
+    const int steps = pair_steps(a.L0, a.L1);
+    if (!a.ranges_given && pair_in_one_launch(a.BH, steps, DH)) {
+        auto launch = [&](auto kern, int per_block) {
+            hipLaunchKernelGGL(kern, dim3((unsigned)((a.BH + per_block - 1) / per_block)), dim3(kThreads), 0, s,
+                               static_cast<const elem_t *>(a.q),
+                               static_cast<const elem_t *>(a.K0), static_cast<const elem_t *>(a.V0),
+                               static_cast<const elem_t *>(a.K1), static_cast<const elem_t *>(a.V1),
+                               a.L0, a.L1, a.BH, scale_log2e, static_cast<elem_t *>(a.out), a.lse);
+        };
+        if (steps == 1) launch(flash_pair_kernel<DH, DT, 1>, 4);
+        else if (steps == 2) launch(flash_pair_kernel<DH, DT, 2>, 2);
+        else launch(flash_pair_kernel<DH, DT, 4>, 1);
+        const hipError_t e = hipGetLastError();
+        return e == hipSuccess && a.after_main ? hipEventRecord(a.after_main, s) : e;
+    }
     const unsigned blocks = (unsigned)((a.n_waves + kWavesPerBlock - 1) / kWavesPerBlock);
     hipLaunchKernelGGL((flash_decode_kernel<DH, DT>), dim3(blocks), dim3(kThreads), 0, s,
                        static_cast<const elem_t *>(a.q),

@@ -72,6 +72,7 @@ struct AttnArgs {
     int head_dim;          // 64 or 128
     float scale;           // multiplies q.k
     int n_waves;           // wavefronts that share the BH * (L0 + L1) token positions equally (attn_wavefronts)
+    bool ranges_given = false;   // the caller asked for that many: short contexts are cut into them too
     float *partial;        // [n_waves + BH, dh + 2] fp32
     void *out;             // [BH, dh] fp16
     float2 *lse;           // optional [BH]: (running maximum in the log2 domain, softmax denominator) of every pair
@@ -134,6 +135,7 @@ struct PagedAttnArgs {
     const int32_t *seq_len;            // [B] tokens per request
     const int64_t *cu_tokens;          // [B + 1] exclusive prefix sums of seq_len
     int64_t total_tokens;              // cu_tokens[B]
+    int64_t other_tokens = 0;          // about so many of them are not in this table (a view of a larger cache)
     int max_blocks, P_kv, P_act, block_tokens;
     int B, H, head_dim;
     float scale;

@@ -10,7 +10,8 @@
 // ranges, one per resident wavefront; a wavefront emits one partial per pair it touches at index
 // (wavefront + pair); a second kernel merges each pair's run of partials.  What differs is the address
 // of a token: the block table is read with scalar loads, one entry for every 16 tokens of a step (steps are
-// aligned to 64 tokens inside a pair, so that 16 tokens never straddle a block), during the step before.
+// aligned to 64 tokens inside a pair, so that 16 tokens never straddle a block), during the step before.  Where a workgroup
+// per pair keeps the chip as busy (pair_in_one_launch), its wavefronts merge in LDS and there is no second kernel.
 // Measured with the merge (profiles/decode_attention_cached.txt, 16-token blocks in random order; in brackets with ranges
 // that end inside a step, entries fetched when they are needed and a merge that walks the partials one by one): 411 MB of
 // 32 ragged requests 72.8 us (90.5), 7.6 GB 1180 (1212), 33 MB of one request 12.4 (42).
@@ -40,6 +41,47 @@ __device__ __forceinline__ int request_of(const int64_t *__restrict__ cu, int B,
         if ((int64_t)H * cu[mid] <= p) lo = mid; else hi = mid;
     }
     return lo;
+}
+
+// Table entries of a step of 64 tokens: one for every 16 of them, which never straddle a block (block_tokens >= 16).
+__device__ __forceinline__ void entries_of(const int32_t *__restrict__ tab, int tb, int last_block, int blk_log2, int32_t (&e)[4])
+{
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int bi = (tb + 16 * j) >> blk_log2;
+        e[j] = tab[bi < last_block ? bi : last_block];
+    }
+}
+
+// Asks for the K and V rows of a step: `rows` tokens from tb on, entries `ent`.
+template <int DH, int DT>
+__device__ __forceinline__ void load_step(
+    const typename Elem<DT>::T *__restrict__ K_pool, const typename Elem<DT>::T *__restrict__ V_pool,
+    const typename Elem<DT>::T *__restrict__ K_regen, const typename Elem<DT>::T *__restrict__ V_regen,
+    const int32_t (&ent)[4], int P_kv, int P_act, int64_t blk_elems, int h, int blk, int tb, int rows, int lane,
+    typename Elem<DT>::V8 (&kr)[attn::Tile<DH, DT>::NL], typename Elem<DT>::V8 (&vr)[attn::Tile<DH, DT>::NL])
+{
+    typedef typename Elem<DT>::V8 half8_t;
+    constexpr int NL = attn::Tile<DH, DT>::NL, kPer = 16 / attn::Tile<DH, DT>::RPL;   // loads of 16 tokens
+    __amdgpu_buffer_rsrc_t kb[4], vb[4];                       // 16 tokens each
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int32_t e = __builtin_amdgcn_readfirstlane(ent[j]);
+        bool is_act = e < 0;
+        int pb = is_act ? ~e : e;
+        if ((is_act ? P_act : P_kv) <= 0) { is_act = !is_act; pb = 0; }   // a corrupt table cannot leave
+        const int P = is_act ? P_act : P_kv;                              // the pools (one is not empty)
+        pb = pb < P ? pb : P - 1;
+        const int64_t at = (int64_t)pb * blk_elems + (int64_t)(h * blk + ((tb + 16 * j) & (blk - 1))) * DH;
+        const int here = rows - 16 * j;
+        const int n = here < 0 ? 0 : here < 16 ? here : 16;
+        kb[j] = attn::step_rows((is_act ? K_regen : K_pool) + at, n, DH);
+        vb[j] = attn::step_rows((is_act ? V_regen : V_pool) + at, n, DH);
+    }
+#pragma unroll
+    for (int i = 0; i < NL; ++i) kr[i] = attn::step_load<half8_t>(kb[i / kPer], i % kPer, lane);
+#pragma unroll
+    for (int i = 0; i < NL; ++i) vr[i] = attn::step_load<half8_t>(vb[i / kPer], i % kPer, lane);
 }
 
 template <int DH, int DT>
@@ -94,47 +136,71 @@ __global__ __launch_bounds__(kThreads, 3) void paged_decode_kernel(
         tile_t tile;
         tile.clear();
 
-        // table entries of a step: one for every 16 of its tokens, which never straddle a block (block_tokens >= 16)
-        auto entries_of = [&](int tb, int32_t (&e)[4]) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int bi = (tb + 16 * j) >> blk_log2;
-                e[j] = tab[bi < last_block ? bi : last_block];
-            }
-        };
         int32_t ent[4] = {0, 0, 0, 0};
-        if (t_first < t_last) entries_of(t_first, ent);
+        if (t_first < t_last) entries_of(tab, t_first, last_block, blk_log2, ent);
         for (int tb = t_first; tb < t_last; tb += kTile) {
             half8_t kr[NL], vr[NL];
             const int rows = t_last - tb < kTile ? t_last - tb : kTile;
-            __amdgpu_buffer_rsrc_t kb[4], vb[4];                   // 16 tokens each
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int32_t e = __builtin_amdgcn_readfirstlane(ent[j]);
-                bool is_act = e < 0;
-                int pb = is_act ? ~e : e;
-                if ((is_act ? P_act : P_kv) <= 0) { is_act = !is_act; pb = 0; }   // a corrupt table cannot leave
-                const int P = is_act ? P_act : P_kv;                              // the pools (one is not empty)
-                pb = pb < P ? pb : P - 1;
-                const int64_t at = (int64_t)pb * blk_elems + (int64_t)(h * blk + ((tb + 16 * j) & (blk - 1))) * DH;
-                const int here = rows - 16 * j;
-                const int n = here < 0 ? 0 : here < 16 ? here : 16;
-                kb[j] = attn::step_rows((is_act ? K_regen : K_pool) + at, n, DH);
-                vb[j] = attn::step_rows((is_act ? V_regen : V_pool) + at, n, DH);
-            }
-            constexpr int kPer = 16 / RPL;                         // loads of 16 tokens
-#pragma unroll
-            for (int i = 0; i < NL; ++i) kr[i] = attn::step_load<half8_t>(kb[i / kPer], i % kPer, lane);
-#pragma unroll
-            for (int i = 0; i < NL; ++i) vr[i] = attn::step_load<half8_t>(vb[i / kPer], i % kPer, lane);
+            load_step<DH, DT>(K_pool, V_pool, K_regen, V_regen, ent, P_kv, P_act, blk_elems, h, blk, tb, rows, lane, kr, vr);
             // the next step's entries (scalar loads) are on their way while this step's rows arrive
-            if (tb + kTile < t_last) entries_of(tb + kTile, ent);
+            if (tb + kTile < t_last) entries_of(tab, tb + kTile, last_block, blk_log2, ent);
             __builtin_amdgcn_sched_barrier(0);                     // every load of the step is on its way before the first use
             tile.consume(qv, kr, vr, lane, c * RPL + g < rows, scale_log2e);
         }
         tile.store(partial + ((int64_t)w + pair) * (DH + 2), lane);
         p = base + (int64_t)h * len + t_end;
     }
+}
+
+// One workgroup per (request, head): its wavefronts take the steps of the pair in turn and merge in LDS, so that one launch
+// does what the ranges and their merge do in two (pair_in_one_launch says when), and no wavefront looks for its request.
+template <int DH, int DT>
+__global__ __launch_bounds__(kThreads, 3) void paged_pair_kernel(
+    const typename Elem<DT>::T *__restrict__ q,
+    const typename Elem<DT>::T *__restrict__ K_pool, const typename Elem<DT>::T *__restrict__ V_pool,
+    const typename Elem<DT>::T *__restrict__ K_regen, const typename Elem<DT>::T *__restrict__ V_regen,
+    const int32_t *__restrict__ table, int max_blocks, int P_kv, int P_act, const int32_t *__restrict__ seq_len,
+    int H, int blk_log2, float scale_log2e, typename Elem<DT>::T *__restrict__ out, float2 *__restrict__ lse)
+{
+    typedef typename Elem<DT>::V8 half8_t;
+    typedef attn::Tile<DH, DT> tile_t;
+    constexpr int LPR = tile_t::LPR, RPL = tile_t::RPL, NL = tile_t::NL, P = kWavesPerBlock;
+    __shared__ __align__(16) float part[P][DH + 2];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int pair = blockIdx.x, r = pair / H, h = pair % H;
+    const int g = lane / LPR, c = lane % LPR;
+    const int blk = 1 << blk_log2;
+    const int64_t blk_elems = (int64_t)H * blk * DH;
+    const int len = seq_len[r];
+    const int last_block = (len - 1) >> blk_log2;              // used only when there are tokens
+    const int32_t *tab = table + (int64_t)r * max_blocks;
+    const half8_t qv = *reinterpret_cast<const half8_t *>(q + (int64_t)pair * DH + c * 8);
+    tile_t tile;
+    tile.clear();
+    int32_t ent[4] = {0, 0, 0, 0};
+    if (wave * kTile < len) entries_of(tab, wave * kTile, last_block, blk_log2, ent);
+    for (int tb = wave * kTile; tb < len; tb += P * kTile) {
+        half8_t kr[NL], vr[NL];
+        const int rows = len - tb < kTile ? len - tb : kTile;
+        load_step<DH, DT>(K_pool, V_pool, K_regen, V_regen, ent, P_kv, P_act, blk_elems, h, blk, tb, rows, lane, kr, vr);
+        if (tb + P * kTile < len) entries_of(tab, tb + P * kTile, last_block, blk_log2, ent);   // while the rows arrive
+        __builtin_amdgcn_sched_barrier(0);                     // every load of the step is on its way before the first use
+        tile.consume(qv, kr, vr, lane, c * RPL + g < rows, scale_log2e);
+    }
+    tile.store(part[wave], lane);
+    __syncthreads();
+    if (wave != 0) return;
+    const bool some = len > 0;
+    merge::Shared<DH, 1> none;
+    float m, l, o[DH / 64];
+    merge::merge_run<DH, 1>(part[0], P, none, m, l, o);
+    if (!some) {                         // no context: the softmax is over nothing; define the output as zero
+#pragma unroll
+        for (int e = 0; e < DH / 64; ++e) o[e] = 0.f;
+    }
+    merge::store_row<DH>(out + (int64_t)pair * DH, o, some ? l : 1.f);
+    if (lse && lane == 0) lse[pair] = some ? make_float2(m, l) : make_float2(kNegBig, 0.f);
 }
 
 // Merge of the partials of every (request, head), P wavefronts each: positions [H cu[r] + h len, + len) of the line.
@@ -184,6 +250,25 @@ void launch_merge(const PagedAttnArgs &a, int64_t total, hipStream_t s)
                        static_cast<typename Elem<DT>::T *>(a.out), a.lse);
 }
 
+// One workgroup per pair, or ranges and a merge?  As in flash_decode.hip (which has the figures of pairs of one length), with
+// the longest length that the table has room for; n counts 16 KB of K and V.  Lengths that differ make the ranges worse (a
+// wavefront searches its requests, and steps over those that end) and leave compute units to the long pairs: half of the
+// requests 16 tokens, half L, 256 pairs, L = 1000: 16.1 us against 27.6; 1024 pairs, L = 2000: 93.5 against 122; lengths L/2 to L, 32
+// requests x 32 heads, L = 1000: 71.7 against 77.0; 2560 pairs, L = 2000: 320 against 326; 864, L = 4000: 232 against 230.
+// What a workgroup per pair cannot balance is a few long requests among many short ones: beyond short contexts the tokens have to
+// be those of 224 pairs of full length, or half of what the table has room for where there are fewer than 448 pairs.
+bool pair_in_one_launch(const PagedAttnArgs &a)
+{
+    const int64_t pairs = (int64_t)a.B * a.H, longest = (int64_t)a.max_blocks * a.block_tokens;
+    const int64_t n = (longest + kTile - 1) / kTile * (a.head_dim / 64);
+    if (n <= 16) return true;
+    const int64_t tokens = a.total_tokens - a.other_tokens, room = longest * a.B;
+    if (pairs >= 448) return n <= 64 && tokens * a.H >= 224 * longest;
+    if (pairs < 128 || 2 * tokens < room) return false;
+    if (pairs < 180) return n <= 32;
+    return pairs <= 256 || n <= 24;
+}
+
 template <int DH, int DT>
 hipError_t launch_dh(const PagedAttnArgs &a, hipStream_t s)
 {
@@ -192,6 +277,15 @@ hipError_t launch_dh(const PagedAttnArgs &a, hipStream_t s)
     const float scale_log2e = a.scale * 1.4426950408889634f;
     int blk_log2 = 0;
     while ((1 << blk_log2) < a.block_tokens) ++blk_log2;
+    if (total > 0 && pair_in_one_launch(a)) {
+        hipLaunchKernelGGL((paged_pair_kernel<DH, DT>), dim3((unsigned)(a.B * a.H)), dim3(kThreads), 0, s,
+                           static_cast<const elem_t *>(a.q),
+                           static_cast<const elem_t *>(a.K_pool), static_cast<const elem_t *>(a.V_pool),
+                           static_cast<const elem_t *>(a.K_regen), static_cast<const elem_t *>(a.V_regen),
+                           a.block_table, a.max_blocks, a.P_kv, a.P_act, a.seq_len, a.H, blk_log2, scale_log2e,
+                           static_cast<elem_t *>(a.out), a.lse);
+        return hipGetLastError();
+    }
     if (total > 0) {
         const unsigned blocks = (unsigned)((a.n_waves + kWavesPerBlock - 1) / kWavesPerBlock);
         hipLaunchKernelGGL((paged_decode_kernel<DH, DT>), dim3(blocks), dim3(kThreads), 0, s,
