@@ -170,32 +170,54 @@ def hk_regen_offsets(shape: hk_shape, B: int, L_act: int):
 
 
 # ----------------------------------------------------------------------------- torch-facing calls
+_Tensor = None                                               # torch.Tensor, once torch is needed
+
+
 def _dev_ptr(t, name, dtype=None):
-    import torch
+    """Address of a contiguous GPU tensor (None stays None: a null pointer)."""
+    global _Tensor
     if t is None:
         return None
-    if not isinstance(t, torch.Tensor) or not t.is_cuda:
+    if _Tensor is None:
+        import torch
+        _Tensor = torch.Tensor
+    if not isinstance(t, _Tensor) or not t.is_cuda:
         raise TypeError("%s must be a GPU tensor (there is no CPU path)" % name)
     if not t.is_contiguous():
         raise ValueError("%s must be contiguous" % name)
     if dtype is not None and t.dtype != dtype:
         raise TypeError("%s must be %s" % (name, dtype))
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _stream_ptr(stream):
+    """The hipStream_t of ``stream``, or of the current device's current stream: its handle alone, without the Stream object
+    that torch.cuda.current_stream builds around it on every call."""
+    if stream is not None:
+        return stream.cuda_stream
     import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+
+
+def _regenerated(workspace, el, offsets, size):
+    """Contiguous views [B, H, L, dh] of the workspace at the two byte offsets: one view of another type and a strided one
+    each (4 us; a slice, a view of another type and a reshape each took 8, as long as a launch)."""
+    if workspace.dim() != 1 or workspace.element_size() != 1 or workspace.numel() % 2 or workspace.storage_offset() % 2:
+        n = 2 * size[0] * size[1] * size[2] * size[3]
+        return tuple(workspace[o:o + n].view(el).view(size) for o in offsets)
+    w = workspace.view(el)
+    first = w.storage_offset()
+    row = max(size[2], 1) * size[3]
+    stride = (size[1] * row, row, size[3], 1)
+    return tuple(w.as_strided(size, stride, first + o // 2) for o in offsets)
 
 
 def _params(ln_w, ln_b, Wkv, bkv, prepared=None, el=None):
-    import torch
-    f16 = el or torch.float16
-    pp = _dev_ptr(prepared, "prepared")
-    return hk_layer_params(_dev_ptr(ln_w, "ln_w", f16).value, _dev_ptr(ln_b, "ln_b", f16).value,
-                           _dev_ptr(Wkv, "Wkv", f16).value, _dev_ptr(bkv, "bkv", f16).value,
-                           pp.value if pp is not None else None)
+    if el is None:
+        import torch
+        el = torch.float16
+    return hk_layer_params(_dev_ptr(ln_w, "ln_w", el), _dev_ptr(ln_b, "ln_b", el), _dev_ptr(Wkv, "Wkv", el),
+                           _dev_ptr(bkv, "bkv", el), _dev_ptr(prepared, "prepared"))
 
 
 def hk_prepared_bytes(shape: hk_shape) -> int:
@@ -280,11 +302,7 @@ def hybrid_decode_attn(q, K_cache, V_cache, act, layer_params, ratio, out=None, 
     if st != HK_OK:
         raise HybridKVError(st, "hk_hybrid_decode_attn")
     if return_regen:
-        n = B * H * L_act * dh
-        k_off, v_off = hk_regen_offsets(shape, B, L_act)
-        K = workspace[k_off:k_off + 2 * n].view(f16).view(B, H, L_act, dh)
-        V = workspace[v_off:v_off + 2 * n].view(f16).view(B, H, L_act, dh)
-        return out, K, V
+        return (out,) + _regenerated(workspace, f16, hk_regen_offsets(shape, B, L_act), (B, H, L_act, dh))
     return out
 
 
@@ -490,7 +508,7 @@ def make_paged_cache(K_pool, V_pool, act_pool, block_table, seq_len, cu_tokens, 
     f16 = el or torch.float16
     P_kv = 0 if K_pool is None else K_pool.shape[0]
     P_act = 0 if act_pool is None else act_pool.shape[0]
-    ptr = lambda t, name, dt: (_dev_ptr(t, name, dt).value if t is not None else None)
+    ptr = _dev_ptr
     return hk_paged_cache(ptr(K_pool, "K_pool", f16), ptr(V_pool, "V_pool", f16), ptr(act_pool, "act_pool", f16),
                           ptr(block_table, "block_table", torch.int32), ptr(seq_len, "seq_len", torch.int32),
                           ptr(cu_tokens, "cu_tokens", torch.int64), int(total_tokens), P_kv, P_act,
