@@ -2,7 +2,7 @@
 // says which), in three launches:
 //   norm   xhat = LayerNorm(x) [B, d] in the storage type (fp32 statistics, one rounding), and the checkpoint copy
 //   stream parts of xhat [Wq; Wkv]^T, fp32, from a fixed number of persistent workgroups
-//   finish sum of the parts, bias, rounding, store of q and of the K / V rows
+//   finish sum of the parts, bias, rounding, store of q and of the K / V rows (in the stream kernel where the parts are large)
 //
 // What bounds it: one pass over the weights (6 d^2 bytes).  The one-launch kernel builds the normalised tile, the two
 // correction sums and the operand layout on the vector ALU and in LDS beside the products, in every workgroup: with 64 to
@@ -13,19 +13,28 @@
 //     the same work whatever the number of tiles; a run leaves one fp32 part per tile that it meets, and the order in
 //     which parts are added is fixed by the sizes.  The cut is that of Q, K and V also where only Q is asked for: q must
 //     not depend on whether K / V rows are produced.
-//   * Both operands of a unit are one stage of the LDS ring of mma_ring.h, which runs on across tiles, so the loads never
-//     drain.
+//   * xhat and the weights have wavefronts and LDS rings of their own: loads of one wavefront land in order, and the rows (L2)
+//     behind weights (HBM) came as late as those.  A fifth wavefront asks for the rows, a block of 64 reduction elements per
+//     stage, shared by the four that multiply (one barrier per stage, with the next stage's fragments read behind it); each
+//     of the four asks for the weights of its own features and needs nobody to tell it that they are there.  Against one
+//     ring for both: B = 128, d = 7168: 90.5 -> 87.8 us, 9216: 139 -> 132; B <= 32 level.
+//   * Weights straight to registers in the operand layout, 64 bytes of a row per load, ran at 4.5 TB/s: whole lines through LDS.
 //   * The weights are asked for non-temporally: xhat (up to 2.4 MB), which every workgroup reads once per tile, stays in
-//     L2 (d = 7168, B = 32: 70 -> 61 us).  64-feature units read xhat twice as often (B = 128: 95 us against 87).
-//   * One workgroup with a ring as deep as the LDS allows beat two with half of it each (B = 64: 69 us against 71).
-//   * Non-temporal stores of the parts were slower (B = 64, d = 7168: 74 us): the finishing kernel finds them in cache.
+//     L2 (d = 7168, B = 32: 70 -> 61 us).
+//   * Q alone is a third of the units: two workgroups share a run then, 64 features each (d = 4096, B = 64 / 128: 24.1 / 30.9 ->
+//     20.0 / 24.2 us; d = 7168: 50.3 / 66 -> 39.6 / 48.7; with up to 32 rows it was so before: 35.8 -> 34.7).
+//   * Where the parts are large (kFusedParts) there is no finishing kernel: a wavefront that has part of a tile stores it and
+//     counts itself; the last of those that share the 32 features reads the other parts and finishes, in the same order of
+//     addition.  The last one's own part is never read, and the launch and its pass over all parts go (d = 7168, B = 128: 87.8 ->
+//     84 us, 9216: 132 -> 125); with small parts the chain store, count, read at the end of the last run is the longer one
+//     (d = 4096, B = 128: 37.4 -> 40.4; 7168, B = 32: 61.6 -> 63.4).
+//   * Non-temporal stores of the parts were slower (B = 64, d = 7168: 74 us against 72): the finishing kernel finds them in cache.
 // Measured, fp16, Q + K + V, new weights in every call, in brackets the one-launch kernel
-// (profiles/qkv_single_kernel_vs_three_launches.txt): d = 7168, B = 32 / 64 / 128: 64 / 72 / 90 us (83 / 113 / 120; 308 MB of
-// weights); d = 4096, B = 128: 39 (69); d = 9216, B = 128: 136 to 140 (148 to 169, two sessions).  Error against 64 bits
+// (profiles/qkv_single_kernel_vs_three_launches.txt): d = 7168, B = 32 / 64 / 128: 62 / 70 / 84 us (83 / 113 / 120; 308 MB of
+// weights); d = 4096, B = 128: 37 (69); d = 9216, B = 128: 125 (148 to 169, two sessions).  Error against 64 bits
 // 2.9e-4 (3.6e-4: two roundings on the way into the product); bf16 2.35e-3 (2.8e-3).
 #include "hk_internal.h"
 #include "elem.h"
-#include "mma_ring.h"
 #include "qkv_dst.h"
 
 #include <type_traits>
@@ -33,8 +42,10 @@
 namespace hk {
 namespace {
 
-constexpr int kUnitK = ring::kBlockK;                       // reduction elements of a unit: a block of the ring
+constexpr int kUnitK = 64;                                  // reduction elements of a unit: 128-byte LDS rows
 constexpr int kStreamed = 2;                                // cache policy of the weight loads: non-temporal, the rows stay in L2
+constexpr int kCoherent = 16;                               // cache policy (sc1) of parts that another XCD reads in the same launch
+constexpr int64_t kFusedParts = 2400000;                    // rows (a multiple of 32) x features from which the last wavefront finishes
 constexpr int kMinRun = 4;                                  // fewest units of a run worth a part of its own
 
 // Runs: workgroup w of n takes units [w u / n, (w + 1) u / n).  A tile's parts come from consecutive workgroups; the part
@@ -66,11 +77,12 @@ __global__ __launch_bounds__(256) void qkv_norm_kernel(const typename Elem<DT>::
                                                        const typename Elem<DT>::T *__restrict__ beta,
                                                        typename Elem<DT>::T *__restrict__ xhat,
                                                        typename Elem<DT>::T *__restrict__ act_dst, int64_t act_row_stride,
-                                                       int d, float eps, PagedDst pd)
+                                                       int d, float eps, PagedDst pd, int32_t *__restrict__ arrived, int n_arrived)
 {
     typedef typename Elem<DT>::T elem_t;
     typedef typename Elem<DT>::V8 vec8_t;
     __shared__ float buf[2][4];
+    for (int i = blockIdx.x * 256 + threadIdx.x; i < n_arrived; i += gridDim.x * 256) arrived[i] = 0;
     const int m = blockIdx.x, tid = threadIdx.x, nvec = d >> 3;
     const vec8_t *row = reinterpret_cast<const vec8_t *>(x + (int64_t)m * d);
     vec8_t *ckpt = nullptr;
@@ -124,140 +136,37 @@ __global__ __launch_bounds__(256) void qkv_norm_kernel(const typename Elem<DT>::
 }
 
 struct StreamArgs {
-    const void *xhat, *Wq, *Wkv;
-    float *part;
-    int B, d, q_tiles, nks, units, runs, live;                 // live: units that are asked for (the first ones)
-    int split;                                                 // workgroups that share a run: each takes BN features of its tiles
-};
-
-// Workgroups of a compute unit: two where the LDS of one allows it.
-template <int BM, int BN, int NS>
-constexpr int stream_per_cu() { return ring::lds_bytes<BM, BN, NS>() <= 80 * 1024 ? 2 : 1; }
-
-template <int BM, int BN, int NS, int DT>
-__global__ __launch_bounds__(256, (stream_per_cu<BM, BN, NS>())) void qkv_stream_kernel(StreamArgs p)
-{
-#if defined(__HIP_DEVICE_COMPILE__)                            // (the host pass drops the kernel's stub over a direct load in this body)
-    typedef typename Elem<DT>::T elem_t;
-    typedef ring::Ring<BM, BN, NS, DT> ring_t;
-    extern __shared__ __align__(16) unsigned char smem[];
-    constexpr int LA = ring_t::kLoadsA, LB = ring_t::kLoadsB, TM = ring_t::TM, TN = ring_t::TN;
-    const int tid = threadIdx.x;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int d = p.d, nks = p.nks;
-    const int run = (int)blockIdx.x / p.split, part = (int)blockIdx.x % p.split;
-    const int u_begin = run_begin(run, p.units, p.runs);
-    const int u_end = run_begin(run + 1, p.units, p.runs);
-    const int n = (u_end < p.live ? u_end : p.live) - u_begin; // >= 1: no more runs than units, none past the live ones
-
-    ring_t r(smem, tid, wave);
-    const __amdgpu_buffer_rsrc_t a_rsrc =
-        __builtin_amdgcn_make_buffer_rsrc(const_cast<elem_t *>(static_cast<const elem_t *>(p.xhat)), 0, p.B * d * 2, 0x00020000);
-    int a_voff[LA], b_voff[LB];
-#pragma unroll
-    for (int i = 0; i < LA; ++i)                               // rows past the end: the last row, never stored
-        a_voff[i] = ((r.a_row(i) < p.B ? r.a_row(i) : p.B - 1) * d + r.lane_chunk * 8) * 2;
-#pragma unroll
-    for (int i = 0; i < LB; ++i) b_voff[i] = (r.b_row(i) * d + r.lane_chunk * 8) * 2;
-    // the unit to ask for next: its tile's rows and its place on the reduction axis
-    int ask_tile = u_begin / nks, ask_k = u_begin % nks;
-    auto tile_rsrc = [&](int tile) {
-        const elem_t *W = tile < p.q_tiles ? static_cast<const elem_t *>(p.Wq) + (int64_t)(tile * p.split + part) * BN * d
-                                           : static_cast<const elem_t *>(p.Wkv) + (int64_t)((tile - p.q_tiles) * p.split + part) * BN * d;
-        return __builtin_amdgcn_make_buffer_rsrc(const_cast<elem_t *>(W), 0, BN * d * 2, 0x00020000);
-    };
-    __amdgpu_buffer_rsrc_t b_rsrc = tile_rsrc(ask_tile);
-    auto issue = [&](int slot, int i) {
-        // weights first: they come from HBM, the rows from L2
-        if (i < LB)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(b_rsrc, r.b_dst(slot, i), 16, b_voff[i], ask_k * ring::kRowBytes, 0, kStreamed);
-        else
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, r.a_dst(slot, i - LB), 16, a_voff[i - LB], ask_k * ring::kRowBytes, 0, 0);
-    };
-    auto asked = [&](bool more) {                              // more: another unit of this run will be asked for
-        if (++ask_k == nks) {
-            ask_k = 0;
-            ++ask_tile;
-            if (more) b_rsrc = tile_rsrc(ask_tile);
-        }
-    };
-
-    r.clear();
-    for (int s = 0; s < NS; ++s) {
-        if (s < n) {
-#pragma unroll
-            for (int i = 0; i < ring_t::kLoads; ++i) issue(s, i);
-            asked(s + 1 < n);
-        }
-    }
-    r.start(n);
-
-    int tile = u_begin / nks, k = u_begin % nks;
-    // One unit (kind as in Ring::block), and the part of a tile that ends with it.
-    auto unit = [&](auto kind, int i) {
-        constexpr int KIND = decltype(kind)::value;
-        r.template block<KIND>(issue, n - 2 - i);
-        if constexpr (KIND == 2) asked(i + NS + 1 < n);
-        if (++k == nks || KIND == 0) {                         // the tile ends here for this run: its part leaves
-            float4_t *dst = reinterpret_cast<float4_t *>(p.part + (int64_t)((tile + run) * p.split + part) * (BM * BN));
-#pragma unroll
-            for (int ii = 0; ii < TM; ++ii)
-#pragma unroll
-                for (int j = 0; j < TN; ++j) dst[(ii * TN + j) * 256 + tid] = r.acc[ii][j];
-            r.clear();
-            k = 0;
-            ++tile;
-        }
-    };
-    int i = 0;
-    for (; i + NS < n; ++i) unit(std::integral_constant<int, 2>{}, i);
-    for (; i + 1 < n; ++i) unit(std::integral_constant<int, 1>{}, i);
-    unit(std::integral_constant<int, 0>{}, i);
-#endif
-}
-
-// finish: a workgroup per (tile or part of it, 16-row blocks i of the wavefront rows); thread for thread the layout of the parts.
-struct FinishArgs {
-    const float *part;
-    const void *bq, *bkv;
+    const void *xhat, *Wq, *Wkv, *bq, *bkv;
     void *q_out, *K_dst, *V_dst;
-    int B, d, n_heads, head_dim, L_cap, tok_pos, q_tiles, nks, units, runs, split;
+    float *part;
+    int32_t *arrived;
+    int B, d, n_heads, head_dim, L_cap, tok_pos, q_tiles, nks, units, runs, live;   // live: units that are asked for (the first ones)
+    int split;                                                 // workgroups that share a run: each takes 64 TN features of its tiles
     PagedDst pd;
 };
 
-template <int BM, int BN, int DT>
-__global__ __launch_bounds__(256) void qkv_finish_kernel(FinishArgs p)
-{
+// Where the rows of 4 TN consecutive features from feature n of Q (is_q) or of K, V go, and their store, bias added and rounded.
+template <int TN, int DT>
+struct Output {
     typedef typename Elem<DT>::T elem_t;
-    typedef elem_t out_t __attribute__((ext_vector_type(BN / 32)));
-    constexpr int TN = BN / 32;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int tile = (int)blockIdx.x / p.split, part = (int)blockIdx.x % p.split, i = blockIdx.y;
-    const int m0 = (wave >> 1) * (BM / 2) + 16 * i + 4 * (lane >> 4);       // first of this thread's 4 rows
-    if (m0 >= p.B) return;                                                  // no barrier in this kernel
-    const int w0 = run_of(tile * p.nks, p.units, p.runs), w1 = run_of(tile * p.nks + p.nks - 1, p.units, p.runs);
-    const float4_t *src = reinterpret_cast<const float4_t *>(p.part + (int64_t)((tile + w0) * p.split + part) * (BM * BN)) + i * TN * 256 + tid;
-    float4_t sum[TN];
-#pragma unroll
-    for (int j = 0; j < TN; ++j) sum[j] = src[256 * j];
-    for (int w = w0 + 1; w <= w1; ++w) {
-        src += p.split * (BM * BN / 4);
-#pragma unroll
-        for (int j = 0; j < TN; ++j) sum[j] += src[256 * j];
+    typedef elem_t out_t __attribute__((ext_vector_type(4 * TN)));
+    const StreamArgs &p;
+    const bool is_q;
+    elem_t *dst;
+    out_t bias;
+
+    __device__ __forceinline__ Output(const StreamArgs &args, bool is_q_, int n) : p(args), is_q(is_q_)
+    {
+        bias = *reinterpret_cast<const out_t *>(static_cast<const elem_t *>(is_q ? p.bq : p.bkv) + n);
+        const int f = n < p.d ? n : n - p.d;
+        const int head_stride = p.pd.block_table ? (p.head_dim << p.pd.blk_log2) : p.L_cap * p.head_dim;
+        dst = is_q ? static_cast<elem_t *>(p.q_out) + n
+                   : static_cast<elem_t *>(n < p.d ? p.K_dst : p.V_dst) + (int64_t)(f / p.head_dim) * head_stride + f % p.head_dim;
     }
-    const bool is_q = tile < p.q_tiles;
-    const int n = ((is_q ? tile : tile - p.q_tiles) * p.split + part) * BN + (BN / 2) * (wave & 1) + TN * (lane & 15);   // first of TN features
-    const out_t bias = *reinterpret_cast<const out_t *>(static_cast<const elem_t *>(is_q ? p.bq : p.bkv) + n);
-    const int f = n < p.d ? n : n - p.d;
-    const int h = f / p.head_dim, e = f % p.head_dim;
-    const int head_stride = p.pd.block_table ? (p.head_dim << p.pd.blk_log2) : p.L_cap * p.head_dim;
-    elem_t *dst = is_q ? static_cast<elem_t *>(p.q_out) + n
-                       : static_cast<elem_t *>(n < p.d ? p.K_dst : p.V_dst) + (int64_t)h * head_stride + e;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int m = m0 + r;
-        if (m >= p.B) break;
-        int64_t base = -1;                                                  // or the row is not stored
+    __device__ __forceinline__ void store(int m, const float4_t (&sum)[TN]) const
+    {
+        if (m >= p.B) return;
+        int64_t base = -1;                                     // or the row is not stored
         if (is_q) {
             base = (int64_t)m * p.d;
         } else if (p.pd.block_table) {
@@ -268,13 +177,259 @@ __global__ __launch_bounds__(256) void qkv_finish_kernel(FinishArgs p)
         } else {
             base = ((int64_t)m * p.n_heads * p.L_cap + p.tok_pos) * p.head_dim;
         }
-        if (base >= 0) {
-            out_t o;
+        if (base < 0) return;
+        out_t o;
 #pragma unroll
-            for (int j = 0; j < TN; ++j) o[j] = (elem_t)(sum[j][r] + (float)bias[j]);
-            *reinterpret_cast<out_t *>(dst + base) = o;
-        }
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) o[4 * j + r] = (elem_t)(sum[j][r] + (float)bias[4 * j + r]);
+        *reinterpret_cast<out_t *>(dst + base) = o;
     }
+};
+
+template <int N>
+__device__ __forceinline__ void wait_vm()
+{
+    static_assert(N <= 63, "vmcnt counts to 63");
+    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0F70);
+}
+
+template <int MT, int TN, int NA, int NB>
+constexpr int stream_lds_bytes() { return (NA * MT * 16 + NB * 64 * TN) * kUnitK * 2; }
+
+// MT: blocks of 16 rows; TN: blocks of 16 features of a wavefront; NA, NB: stages of the rings of the rows and of a wavefront's
+// weights; FUSED: no finishing kernel follows.
+template <int MT, int TN, int NA, int NB, bool FUSED, int DT>
+__global__ __launch_bounds__(320) void qkv_stream_kernel(StreamArgs p)
+{
+#if defined(__HIP_DEVICE_COMPILE__)                            // (the host pass drops the kernel's stub over a direct load in this body)
+    typedef typename Elem<DT>::T elem_t;
+    typedef typename Elem<DT>::V8 vec8_t;
+    typedef __attribute__((address_space(3))) void *lds_ptr_t;
+    typedef unsigned u4_t __attribute__((ext_vector_type(4)));
+    extern __shared__ __align__(16) unsigned char smem[];
+    constexpr int kStage = MT * 16 * kUnitK * 2, BN = 64 * TN;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int d = p.d, nks = p.nks;
+    const int run = (int)blockIdx.x / p.split, part = (int)blockIdx.x % p.split;
+    const int u_begin = run_begin(run, p.units, p.runs);
+    const int u_end = run_begin(run + 1, p.units, p.runs);
+    const int n = (u_end < p.live ? u_end : p.live) - u_begin; // >= 1: no more runs than units, none past the live ones
+    const int tile0 = u_begin / nks, k0 = u_begin - tile0 * nks;
+
+    if (wave == 4) {                                           // ---- the rows: 8 of them a load, chunks swizzled by row / 2
+        constexpr int LA = 2 * MT;
+        int voff[LA];
+#pragma unroll
+        for (int i = 0; i < LA; ++i) {
+            const int q = 8 * i + (lane >> 3);
+            voff[i] = ((q < p.B ? q : p.B - 1) * d + 8 * ((lane & 7) ^ ((q >> 1) & 7))) * 2;       // rows past the end: never stored
+        }
+        const __amdgpu_buffer_rsrc_t rs =
+            __builtin_amdgcn_make_buffer_rsrc(const_cast<elem_t *>(static_cast<const elem_t *>(p.xhat)), 0, p.B * d * 2, 0x00020000);
+        int slot = 0, k = k0;
+        auto issue = [&] {
+#pragma unroll
+            for (int i = 0; i < LA; ++i)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr_t)(smem + slot * kStage + i * 1024), 16, voff[i], k * (kUnitK * 2), 0, 0);
+            slot = slot + 1 == NA ? 0 : slot + 1;
+            k = k + 1 == nks ? 0 : k + 1;
+        };
+        for (int s = 0; s < NA && s < n; ++s) issue();
+        for (int s = -1; s + 1 < n; ++s) {                     // stage s + 1 is there
+            if (s + NA - 1 < n) wait_vm<LA * (NA - 2)>();
+            else wait_vm<0>();
+            asm volatile("s_barrier" ::: "memory");            // and that of s is free
+            if (s >= 0 && s + NA < n) issue();
+        }
+        return;
+    }
+
+    // ---- the weights: each wavefront its own, in a ring of its own
+    constexpr int LB = 2 * TN, kMine = TN * 16 * kUnitK * 2;
+    unsigned char *mine = smem + NA * kStage + wave * (NB * kMine);
+    const int c = lane & 15, g = lane >> 4;
+    int voff[LB];
+#pragma unroll
+    for (int i = 0; i < LB; ++i) {                             // LDS row 16 j + c: so that a lane ends up with 4 TN consecutive features
+        const int row = 8 * i + (lane >> 3), cc = row & 15, j = row >> 4;
+        voff[i] = ((16 * TN * wave + 4 * TN * (cc >> 2) + 4 * j + (cc & 3)) * d + 8 * ((lane & 7) ^ ((row >> 1) & 7))) * 2;
+    }
+    auto tile_rsrc = [&](int tile) {
+        const elem_t *W = tile < p.q_tiles ? static_cast<const elem_t *>(p.Wq) + (int64_t)(tile * p.split + part) * BN * d
+                                           : static_cast<const elem_t *>(p.Wkv) + (int64_t)((tile - p.q_tiles) * p.split + part) * BN * d;
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<elem_t *>(W), 0, BN * d * 2, 0x00020000);
+    };
+    int ask_tile = tile0, ask_k = k0, ask_slot = 0, asked = 0;
+    __amdgpu_buffer_rsrc_t rs = tile_rsrc(ask_tile);
+    auto ask = [&] {
+#pragma unroll
+        for (int i = 0; i < LB; ++i)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr_t)(mine + ask_slot * kMine + i * 1024), 16, voff[i], ask_k * (kUnitK * 2), 0, kStreamed);
+        ask_slot = ask_slot + 1 == NB ? 0 : ask_slot + 1;
+        ++asked;
+        if (++ask_k == nks) {
+            ask_k = 0;
+            ++ask_tile;
+            if (asked < n) rs = tile_rsrc(ask_tile);
+        }
+    };
+    int foff[2];
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) foff[ks] = c * 128 + (((4 * ks + g) ^ ((c >> 1) & 7)) << 4);
+    vec8_t fa[2][MT], fb[2][TN];
+    auto read = [&](int ks, int slot, int own) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j) fb[ks][j] = *reinterpret_cast<const vec8_t *>(mine + own * kMine + j * 2048 + foff[ks]);
+#pragma unroll
+        for (int i = 0; i < MT; ++i) fa[ks][i] = *reinterpret_cast<const vec8_t *>(smem + slot * kStage + i * 2048 + foff[ks]);
+    };
+    float4_t acc[MT][TN];
+    auto clear = [&] {
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) acc[i][j] = float4_t{0.f, 0.f, 0.f, 0.f};
+    };
+    auto multiply = [&](int ks) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int i = 0; i < MT; ++i) acc[i][j] = Elem<DT>::mfma_16x16x32(fb[ks][j], fa[ks][i], acc[i][j]);
+    };
+    for (int s = 0; s < NB && s < n; ++s) ask();
+    clear();
+    if (n >= NB) wait_vm<LB * (NB - 1)>();
+    else wait_vm<0>();
+    asm volatile("s_barrier" ::: "memory");
+    read(0, 0, 0);
+    int tile = tile0, k = k0, cur = 0, own = 0;
+    constexpr int kPart = MT * TN * 256 * 16;                  // bytes of a part, thread for thread: a block of 16 x 16 is 1 KB of each wavefront
+    const __amdgpu_buffer_rsrc_t parts = __builtin_amdgcn_make_buffer_rsrc(p.part, 0, 0x7ffffff0, 0x00020000);
+    const int lane_at = (int)threadIdx.x * 16;
+    auto finish = [&] {
+        const bool is_q = tile < p.q_tiles;
+        const Output<TN, DT> out(p, is_q, ((is_q ? tile : tile - p.q_tiles) * p.split + part) * BN + 16 * TN * wave + 4 * TN * g);
+#pragma unroll
+        for (int i = 0; i < MT; ++i) out.store(16 * i + c, acc[i]);
+    };
+    // acc = the sum of the parts w0 .. w1 of the tile, acc itself in the place of this run's
+    auto add_others = [&](int w0, int w1) {
+        constexpr int IB = MT > 4 ? MT / 2 : MT;               // as many blocks at a time as there are registers for
+#pragma unroll
+        for (int i0 = 0; i0 < MT; i0 += IB) {
+            float4_t v[IB][TN], sum[IB][TN];
+            auto load = [&](int w) {
+                const int from = ((tile + w) * p.split + part) * kPart + i0 * TN * 4096;
+#pragma unroll
+                for (int i = 0; i < IB; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j)
+                        v[i][j] = __builtin_bit_cast(float4_t, __builtin_amdgcn_raw_buffer_load_b128(parts, lane_at, from + (i * TN + j) * 4096, kCoherent));
+            };
+            auto add = [&](bool first) {
+#pragma unroll
+                for (int i = 0; i < IB; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j) sum[i][j] = first ? v[i][j] : sum[i][j] + v[i][j];
+            };
+            for (int w = w0; w < run; ++w) {
+                load(w);
+                add(w == w0);
+            }
+#pragma unroll
+            for (int i = 0; i < IB; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j) sum[i][j] = run > w0 ? sum[i][j] + acc[i0 + i][j] : acc[i0 + i][j];
+            for (int w = run + 1; w <= w1; ++w) {
+                load(w);
+                add(false);
+            }
+#pragma unroll
+            for (int i = 0; i < IB; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j) acc[i0 + i][j] = sum[i][j];
+        }
+    };
+    auto leave = [&] {                                         // the tile ends here for this run
+        bool last = FUSED;
+        const int w0 = FUSED ? run_of(tile * nks, p.units, p.runs) : 0, w1 = FUSED ? run_of(tile * nks + nks - 1, p.units, p.runs) : 1;
+        if (w0 != w1) {
+            const int at = ((tile + run) * p.split + part) * kPart;
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4_t, acc[i][j]), parts, lane_at, at + (i * TN + j) * 4096, FUSED ? kCoherent : 0);
+            if constexpr (FUSED) {
+                // The wavefronts of the runs that share these features count themselves.  Parts are written and read as
+                // device-scope atomics are (sc1), and each has arrived (vmcnt) before its wavefront counts; nobody waits.
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                int before = 0;
+                if (lane == 0)
+                    before = __hip_atomic_fetch_add(p.arrived + (tile * p.split + part) * 4 + wave, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                last = __builtin_amdgcn_readfirstlane(before) == w1 - w0;
+                asm volatile("" ::: "memory");
+                if (last) add_others(w0, w1);
+            }
+        }
+        if constexpr (FUSED) {
+            if (last) finish();
+        }
+        clear();
+        k = 0;
+        ++tile;
+    };
+    for (int s = 0; s + 1 < n; ++s) {
+        read(1, cur, own);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(0);
+        __builtin_amdgcn_sched_barrier(0);
+        cur = cur + 1 == NA ? 0 : cur + 1;
+        own = own + 1 == NB ? 0 : own + 1;
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // the slots of this unit are free
+        if (s + NB < n) {
+            ask();
+            wait_vm<LB * (NB - 1)>();
+        } else {
+            wait_vm<0>();
+        }
+        asm volatile("s_barrier" ::: "memory");
+        read(0, cur, own);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(1);
+        __builtin_amdgcn_sched_barrier(0);
+        if (++k == nks) leave();
+    }
+    read(1, cur, own);
+    multiply(0);
+    multiply(1);
+    leave();
+#endif
+}
+
+// finish: a workgroup per (tile or part of it, block of 16 rows); thread for thread the layout of the parts.
+template <int MT, int TN, int DT>
+__global__ __launch_bounds__(256) void qkv_finish_kernel(StreamArgs p)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tile = (int)blockIdx.x / p.split, part = (int)blockIdx.x % p.split, i = blockIdx.y;
+    const int m = 16 * i + (lane & 15);
+    if (m >= p.B) return;                                                   // no barrier in this kernel
+    const int w0 = run_of(tile * p.nks, p.units, p.runs), w1 = run_of(tile * p.nks + p.nks - 1, p.units, p.runs);
+    const float4_t *src = reinterpret_cast<const float4_t *>(p.part) + (int64_t)((tile + w0) * p.split + part) * (MT * TN * 256) + i * TN * 256 + tid;
+    float4_t sum[TN];
+#pragma unroll
+    for (int j = 0; j < TN; ++j) sum[j] = src[256 * j];
+    for (int w = w0 + 1; w <= w1; ++w) {
+        src += p.split * (MT * TN * 256);
+#pragma unroll
+        for (int j = 0; j < TN; ++j) sum[j] += src[256 * j];
+    }
+    const bool is_q = tile < p.q_tiles;
+    const Output<TN, DT> out(p, is_q, ((is_q ? tile : tile - p.q_tiles) * p.split + part) * (64 * TN) + 16 * TN * wave + 4 * TN * (lane >> 4));
+    out.store(m, sum);
 }
 
 size_t align256(size_t n) { return (n + 255) / 256 * 256; }
@@ -285,58 +440,79 @@ int stream_runs(int units, int workgroups)
     return workgroups < most ? workgroups : most;
 }
 
-template <int BM, int BN, int NS, int SPLIT, int DT>
+template <int MT, int TN, int NA, int NB, int SPLIT, bool FUSED, int DT>
 hipError_t launch_dt(const QkvArgs &a, int cus, hipStream_t s)
 {
     typedef typename Elem<DT>::T elem_t;
     const PagedDst pd = paged_dst(a);
     elem_t *xhat = static_cast<elem_t *>(a.scratch);
     float *part = reinterpret_cast<float *>(static_cast<char *>(a.scratch) + align256((size_t)a.B * a.d * 2));
-    hipLaunchKernelGGL(qkv_norm_kernel<DT>, dim3((unsigned)a.B), dim3(256), 0, s, static_cast<const elem_t *>(a.x),
-                       static_cast<const elem_t *>(a.ln_w), static_cast<const elem_t *>(a.ln_b), xhat,
-                       static_cast<elem_t *>(a.act_dst), a.act_row_stride, a.d, a.eps, pd);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
     StreamArgs t;
-    t.xhat = xhat; t.Wq = a.Wq; t.Wkv = a.Wkv; t.part = part;
-    t.B = a.B; t.d = a.d; t.q_tiles = a.d / (BN * SPLIT); t.nks = a.d / kUnitK; t.split = SPLIT;
+    t.xhat = xhat; t.Wq = a.Wq; t.Wkv = a.Wkv; t.bq = a.bq; t.bkv = a.bkv; t.part = part;
+    t.q_out = a.q_out; t.K_dst = a.K_dst; t.V_dst = a.V_dst; t.pd = pd;
+    t.n_heads = a.n_heads; t.head_dim = a.head_dim; t.L_cap = a.L_cap; t.tok_pos = a.tok_pos;
+    t.B = a.B; t.d = a.d; t.q_tiles = a.d / (64 * TN * SPLIT); t.nks = a.d / kUnitK; t.split = SPLIT;
     const int tiles = a.K_dst ? 3 * t.q_tiles : t.q_tiles;
     t.units = 3 * t.q_tiles * t.nks;
     t.live = tiles * t.nks;
-    t.runs = stream_runs(t.units, stream_per_cu<BM, BN, NS>() * cus);
-    auto kern = qkv_stream_kernel<BM, BN, NS, DT>;
-    constexpr int lds = ring::lds_bytes<BM, BN, NS>();
+    t.runs = stream_runs(t.units, cus);
+    // the counters lie behind the last part, where qkv_stream_scratch_bytes has room for one more
+    t.arrived = reinterpret_cast<int32_t *>(part + (int64_t)(3 * t.q_tiles + t.runs - 1) * SPLIT * (MT * TN * 1024));
+    hipLaunchKernelGGL(qkv_norm_kernel<DT>, dim3((unsigned)a.B), dim3(256), 0, s, static_cast<const elem_t *>(a.x),
+                       static_cast<const elem_t *>(a.ln_w), static_cast<const elem_t *>(a.ln_b), xhat,
+                       static_cast<elem_t *>(a.act_dst), a.act_row_stride, a.d, a.eps, pd, t.arrived, FUSED ? tiles * SPLIT * 4 : 0);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    auto kern = qkv_stream_kernel<MT, TN, NA, NB, FUSED, DT>;
+    constexpr int lds = stream_lds_bytes<MT, TN, NA, NB>();
     static_assert(lds <= 160 * 1024, "the workgroup must fit the LDS of a compute unit");
     static LdsOnce lds_once;
     e = allow_dynamic_lds(reinterpret_cast<const void *>(kern), lds, lds_once);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3((unsigned)(SPLIT * (run_of(t.live - 1, t.units, t.runs) + 1))), dim3(256), lds, s, t);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    FinishArgs f;
-    f.part = part; f.bq = a.bq; f.bkv = a.bkv; f.q_out = a.q_out; f.K_dst = a.K_dst; f.V_dst = a.V_dst;
-    f.B = a.B; f.d = a.d; f.n_heads = a.n_heads; f.head_dim = a.head_dim; f.L_cap = a.L_cap; f.tok_pos = a.tok_pos;
-    f.q_tiles = t.q_tiles; f.nks = t.nks; f.units = t.units; f.runs = t.runs; f.split = SPLIT; f.pd = pd;
-    hipLaunchKernelGGL((qkv_finish_kernel<BM, BN, DT>), dim3((unsigned)(SPLIT * tiles), BM / 32), dim3(256), 0, s, f);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(SPLIT * (run_of(t.live - 1, t.units, t.runs) + 1))), dim3(320), lds, s, t);
+    if ((e = hipGetLastError()) != hipSuccess || FUSED) return e;
+    hipLaunchKernelGGL((qkv_finish_kernel<MT, TN, DT>), dim3((unsigned)(SPLIT * tiles), (unsigned)((a.B + 15) / 16)), dim3(256), 0, s, t);
     return hipGetLastError();
 }
 
-template <int BM, int BN, int NS, int SPLIT = 1>
+template <int MT, int TN, int NA, int NB, int SPLIT, bool FUSED = false>
+hipError_t launch_types(const QkvArgs &a, int cus, hipStream_t s)
+{
+    return a.dtype == 1 ? launch_dt<MT, TN, NA, NB, SPLIT, FUSED, 1>(a, cus, s) : launch_dt<MT, TN, NA, NB, SPLIT, FUSED, 0>(a, cus, s);
+}
+
+// Rings as deep as the LDS of a compute unit and the counter of loads (63) allow.
+template <int TN, int SPLIT>
 hipError_t launch_any(const QkvArgs &a, int cus, hipStream_t s)
 {
-    return a.dtype == 1 ? launch_dt<BM, BN, NS, SPLIT, 1>(a, cus, s) : launch_dt<BM, BN, NS, SPLIT, 0>(a, cus, s);
+    constexpr int W = 2 / TN;                                  // a stage of weights is 8 KB x TN
+    const int rows = (a.B + 31) / 32 * 32;
+    if constexpr (TN == 2) {
+        if ((int64_t)rows * 3 * a.d >= kFusedParts) {
+            if (rows == 128) return launch_types<8, TN, 5, 5, SPLIT, true>(a, cus, s);
+            if (rows == 96) return launch_types<6, TN, 5, 6, SPLIT, true>(a, cus, s);
+        }
+    }
+    switch (rows / 32) {
+    case 1: return launch_types<2, TN, 10, 7 * W, SPLIT>(a, cus, s);
+    case 2: return launch_types<4, TN, 6, 7 * W, SPLIT>(a, cus, s);
+    case 3: return launch_types<6, TN, 5, 6 * W, SPLIT>(a, cus, s);
+    default: return launch_types<8, TN, 5, 5 * W, SPLIT>(a, cus, s);
+    }
 }
 
 }  // namespace
 
 // Where the lines lie (measured, new weights in every call, replayed from a graph, us a call, one-launch kernel against
-// this one, fp16 / bf16 where they differ).  Three launches cost 12 to 14 us however small the layer, so many rows and wide
+// this one, fp16 / bf16 where they differ; next to the lines at 8192 and 8448 with rings that both operands shared, 0 to 3 %
+// slower than now).  Three launches cost 12 to 14 us however small the layer, so many rows and wide
 // layers come here.
-//   97 rows and more: every layer from d = 768 on: 25.0 / 28.1 against 15.1 (B = 128); 4096: 69 / 84 against 39; 7168:
-//     116 / 141 against 91; 9216: 148 / 179 against 136; 9152 (units of 64 features): 148 against 149 / 181 against 150
-//   65 to 96 rows: from d = 768 on: 18.8 / 20.9 against 13.5 (B = 65).  fp16 below 8448: 8192, B = 96: 118 against 108;
+//   97 rows and more: every layer from d = 768 on: 25.0 / 28.1 against 13.4 (B = 128); 4096: 69 / 84 against 37; 7168:
+//     116 / 141 against 84; 9216: 148 / 179 against 125; 9152 (units of 64 features): 148 against 149 / 181 against 150
+//   65 to 96 rows: from d = 768 on: 18.8 / 20.9 against 12.3 (B = 65).  fp16 below 8448: 8192, B = 96: 118 against 108;
 //     8256, B = 65: 114 against 107; 8448, B = 96: 111.7 against 116.6; 9216, B = 96: 118 against 127; 9152: 118 against
 //     137.  bf16 everywhere: 9216, B = 96: 145 against 128
-//   33 to 64 rows: from d = 2048 on: 20.6 / 23.7 against 18.0 (B = 33).  fp16 below 8192, where the one-launch kernel
+//   33 to 64 rows: from d = 2048 on: 20.6 / 23.7 against 17.6 (B = 33).  fp16 below 8192, where the one-launch kernel
 //     changes to workgroups of 128 features: 8128, B = 64: 132 against 97; 8192, B = 33: 91 against 95 and 101 against 98
 //     (two sessions); 8704: level.  bf16 below 8448: 8256, B = 64: 111 against 104; 8448: 101 against 103; 9152: 109
 //     against 123; 9216: level
@@ -373,27 +549,9 @@ hipError_t launch_qkv_stream(const QkvArgs &a, hipStream_t s)
     const hipError_t e = current_device_cus(&dev, &cus);
     if (e != hipSuccess) return e;
     if (cus > kQkvStreamCus) cus = kQkvStreamCus;
-    if (a.d % 128 != 0) {
-        switch ((a.B + 31) / 32) {
-        case 1: return launch_any<32, 64, 6>(a, cus, s);
-        case 2: return launch_any<64, 64, 5>(a, cus, s);
-        case 3: return launch_any<96, 64, 4>(a, cus, s);
-        default: return launch_any<128, 64, 3>(a, cus, s);
-        }
-    }
-    switch ((a.B + 31) / 32) {
-    case 1: {
-        // Q alone occupies a third of the compute units, each of which waits for its own units: two workgroups a run then,
-        // 64 features each, with a ring of more units.  The cut along the reduction, and with it the bits, is the same.
-        // Q alone, B = 1 / 32, fp16: d = 7168: 40.8 / 44.3 -> 29.6 / 35.0 us (one-launch kernel: 36.6 / 41.0), 9216: 60.3 /
-        // 65.7 -> 40.5 / 48.9 (46.5 / 53.8).  With more rows one workgroup a run is faster than the one-launch kernel too.
-        static_assert(stream_per_cu<32, 128, 7>() == stream_per_cu<32, 64, 12>(), "the cut follows the workgroups of a compute unit");
-        return a.K_dst ? launch_any<32, 128, 7>(a, cus, s) : launch_any<32, 64, 12, 2>(a, cus, s);
-    }
-    case 2: return launch_any<64, 128, 6>(a, cus, s);
-    case 3: return launch_any<96, 128, 5>(a, cus, s);
-    default: return launch_any<128, 128, 4>(a, cus, s);
-    }
+    if (a.d % 128 != 0) return launch_any<1, 1>(a, cus, s);
+    // Q alone: two workgroups a run, each with the same units along the reduction of 64 features, so the bits are the same
+    return a.K_dst ? launch_any<2, 1>(a, cus, s) : launch_any<1, 2>(a, cus, s);
 }
 
 }  // namespace hk
