@@ -112,7 +112,6 @@ __global__ __launch_bounds__(kThreads, 3) void flash_pair_kernel(
     const typename Elem<DT>::T *__restrict__ K1, const typename Elem<DT>::T *__restrict__ V1,
     int L0, int L1, int BH, float scale_log2e, typename Elem<DT>::T *__restrict__ out, float2 *__restrict__ lse)
 {
-    typedef typename Elem<DT>::T elem_t;
     typedef typename Elem<DT>::V8 half8_t;
     typedef attn::Tile<DH, DT> tile_t;
     constexpr int LPR = tile_t::LPR, RPL = tile_t::RPL, NL = tile_t::NL;
