@@ -1,4 +1,4 @@
-// The main loop of the products whose two operands both stream through LDS (kv_gemm_tile.hip): a BM x BN
+// The main loop of the products whose two operands both stream through LDS (kv_gemm_tile.hip, qkv_stream.hip): a BM x BN
 // output tile, 4 wavefronts, 2 x 2, (BM/2) x (BN/2) accumulators each in 16 x 16 x 32 MFMA blocks, and a ring of NS stages
 // in LDS, each a "block" of 64 reduction elements of both operands.
 //   * Loads go to LDS directly, 16 bytes per lane.  Load i of wavefront w fills LDS rows 8 (w + 4 i) .. + 7 of an operand;

@@ -35,6 +35,7 @@
 // 2.9e-4 (3.6e-4: two roundings on the way into the product); bf16 2.35e-3 (2.8e-3).
 #include "hk_internal.h"
 #include "elem.h"
+#include "mma_ring.h"
 #include "qkv_dst.h"
 
 #include <type_traits>
@@ -356,12 +357,22 @@ __global__ __launch_bounds__(320) void qkv_stream_kernel(StreamArgs p)
         bool last = FUSED;
         const int w0 = FUSED ? run_of(tile * nks, p.units, p.runs) : 0, w1 = FUSED ? run_of(tile * nks + nks - 1, p.units, p.runs) : 1;
         if (w0 != w1) {
-            const int at = ((tile + run) * p.split + part) * kPart;
+            const int slot = (tile + run) * p.split + part;
+            if constexpr (!FUSED) {
+                float4_t *dst = reinterpret_cast<float4_t *>(p.part) + (int64_t)slot * (kPart / 16) + threadIdx.x;
 #pragma unroll
-            for (int i = 0; i < MT; ++i)
+                for (int i = 0; i < MT; ++i)
 #pragma unroll
-                for (int j = 0; j < TN; ++j)
-                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4_t, acc[i][j]), parts, lane_at, at + (i * TN + j) * 4096, FUSED ? kCoherent : 0);
+                    for (int j = 0; j < TN; ++j) dst[(i * TN + j) * 256] = acc[i][j];
+            } else {
+                // The accumulators are not touched before these stores have completed, below: behind a raw buffer store with
+                // a scalar offset the compiler leaves no wait state, and cleared at once its last lanes could store zeros.
+#pragma unroll
+                for (int i = 0; i < MT; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j)
+                        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4_t, acc[i][j]), parts, lane_at, slot * kPart + (i * TN + j) * 4096, kCoherent);
+            }
             if constexpr (FUSED) {
                 // The wavefronts of the runs that share these features count themselves.  Parts are written and read as
                 // device-scope atomics are (sc1), and each has arrived (vmcnt) before its wavefront counts; nobody waits.
@@ -432,6 +443,148 @@ __global__ __launch_bounds__(256) void qkv_finish_kernel(StreamArgs p)
     out.store(m, sum);
 }
 
+// ---- layers that 128 does not divide: units of 64 features, both operands in one ring, two workgroups a compute unit and twice as
+// many runs, so that Q alone, a third of them, fills the chip (d = 9152, B = 64: 47 us; with rings of their own and one workgroup
+// a unit 72, where Q, K and V gain 1 to 3 %).
+// Workgroups of a compute unit: two where the LDS of one allows it.
+template <int BM, int BN, int NS>
+constexpr int ring_per_cu() { return ring::lds_bytes<BM, BN, NS>() <= 80 * 1024 ? 2 : 1; }
+
+template <int BM, int BN, int NS, int DT>
+__global__ __launch_bounds__(256, (ring_per_cu<BM, BN, NS>())) void qkv_ring_kernel(StreamArgs p)
+{
+#if defined(__HIP_DEVICE_COMPILE__)                            // (the host pass drops the kernel's stub over a direct load in this body)
+    typedef typename Elem<DT>::T elem_t;
+    typedef ring::Ring<BM, BN, NS, DT> ring_t;
+    extern __shared__ __align__(16) unsigned char smem[];
+    constexpr int LA = ring_t::kLoadsA, LB = ring_t::kLoadsB, TM = ring_t::TM, TN = ring_t::TN;
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int d = p.d, nks = p.nks;
+    const int run = (int)blockIdx.x / p.split, part = (int)blockIdx.x % p.split;
+    const int u_begin = run_begin(run, p.units, p.runs);
+    const int u_end = run_begin(run + 1, p.units, p.runs);
+    const int n = (u_end < p.live ? u_end : p.live) - u_begin; // >= 1: no more runs than units, none past the live ones
+
+    ring_t r(smem, tid, wave);
+    const __amdgpu_buffer_rsrc_t a_rsrc =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<elem_t *>(static_cast<const elem_t *>(p.xhat)), 0, p.B * d * 2, 0x00020000);
+    int a_voff[LA], b_voff[LB];
+#pragma unroll
+    for (int i = 0; i < LA; ++i)                               // rows past the end: the last row, never stored
+        a_voff[i] = ((r.a_row(i) < p.B ? r.a_row(i) : p.B - 1) * d + r.lane_chunk * 8) * 2;
+#pragma unroll
+    for (int i = 0; i < LB; ++i) b_voff[i] = (r.b_row(i) * d + r.lane_chunk * 8) * 2;
+    // the unit to ask for next: its tile's rows and its place on the reduction axis
+    int ask_tile = u_begin / nks, ask_k = u_begin % nks;
+    auto tile_rsrc = [&](int tile) {
+        const elem_t *W = tile < p.q_tiles ? static_cast<const elem_t *>(p.Wq) + (int64_t)(tile * p.split + part) * BN * d
+                                           : static_cast<const elem_t *>(p.Wkv) + (int64_t)((tile - p.q_tiles) * p.split + part) * BN * d;
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<elem_t *>(W), 0, BN * d * 2, 0x00020000);
+    };
+    __amdgpu_buffer_rsrc_t b_rsrc = tile_rsrc(ask_tile);
+    auto issue = [&](int slot, int i) {
+        // weights first: they come from HBM, the rows from L2
+        if (i < LB)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(b_rsrc, r.b_dst(slot, i), 16, b_voff[i], ask_k * ring::kRowBytes, 0, kStreamed);
+        else
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, r.a_dst(slot, i - LB), 16, a_voff[i - LB], ask_k * ring::kRowBytes, 0, 0);
+    };
+    auto asked = [&](bool more) {                              // more: another unit of this run will be asked for
+        if (++ask_k == nks) {
+            ask_k = 0;
+            ++ask_tile;
+            if (more) b_rsrc = tile_rsrc(ask_tile);
+        }
+    };
+
+    r.clear();
+    for (int s = 0; s < NS; ++s) {
+        if (s < n) {
+#pragma unroll
+            for (int i = 0; i < ring_t::kLoads; ++i) issue(s, i);
+            asked(s + 1 < n);
+        }
+    }
+    r.start(n);
+
+    int tile = u_begin / nks, k = u_begin % nks;
+    // One unit (kind as in Ring::block), and the part of a tile that ends with it.
+    auto unit = [&](auto kind, int i) {
+        constexpr int KIND = decltype(kind)::value;
+        r.template block<KIND>(issue, n - 2 - i);
+        if constexpr (KIND == 2) asked(i + NS + 1 < n);
+        if (++k == nks || KIND == 0) {                         // the tile ends here for this run: its part leaves
+            float4_t *dst = reinterpret_cast<float4_t *>(p.part + (int64_t)((tile + run) * p.split + part) * (BM * BN));
+#pragma unroll
+            for (int ii = 0; ii < TM; ++ii)
+#pragma unroll
+                for (int j = 0; j < TN; ++j) dst[(ii * TN + j) * 256 + tid] = r.acc[ii][j];
+            r.clear();
+            k = 0;
+            ++tile;
+        }
+    };
+    int i = 0;
+    for (; i + NS < n; ++i) unit(std::integral_constant<int, 2>{}, i);
+    for (; i + 1 < n; ++i) unit(std::integral_constant<int, 1>{}, i);
+    unit(std::integral_constant<int, 0>{}, i);
+#endif
+}
+
+// Its parts: thread for thread the layout of the ring's accumulators; a workgroup per (tile, 16-row blocks i of the wavefront rows).
+template <int BM, int BN, int DT>
+__global__ __launch_bounds__(256) void qkv_ring_finish_kernel(StreamArgs p)
+{
+    typedef typename Elem<DT>::T elem_t;
+    typedef elem_t out_t __attribute__((ext_vector_type(BN / 32)));
+    constexpr int TN = BN / 32;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tile = (int)blockIdx.x / p.split, part = (int)blockIdx.x % p.split, i = blockIdx.y;
+    const int m0 = (wave >> 1) * (BM / 2) + 16 * i + 4 * (lane >> 4);       // first of this thread's 4 rows
+    if (m0 >= p.B) return;                                                  // no barrier in this kernel
+    const int w0 = run_of(tile * p.nks, p.units, p.runs), w1 = run_of(tile * p.nks + p.nks - 1, p.units, p.runs);
+    const float4_t *src = reinterpret_cast<const float4_t *>(p.part + (int64_t)((tile + w0) * p.split + part) * (BM * BN)) + i * TN * 256 + tid;
+    float4_t sum[TN];
+#pragma unroll
+    for (int j = 0; j < TN; ++j) sum[j] = src[256 * j];
+    for (int w = w0 + 1; w <= w1; ++w) {
+        src += p.split * (BM * BN / 4);
+#pragma unroll
+        for (int j = 0; j < TN; ++j) sum[j] += src[256 * j];
+    }
+    const bool is_q = tile < p.q_tiles;
+    const int n = ((is_q ? tile : tile - p.q_tiles) * p.split + part) * BN + (BN / 2) * (wave & 1) + TN * (lane & 15);   // first of TN features
+    const out_t bias = *reinterpret_cast<const out_t *>(static_cast<const elem_t *>(is_q ? p.bq : p.bkv) + n);
+    const int f = n < p.d ? n : n - p.d;
+    const int h = f / p.head_dim, e = f % p.head_dim;
+    const int head_stride = p.pd.block_table ? (p.head_dim << p.pd.blk_log2) : p.L_cap * p.head_dim;
+    elem_t *dst = is_q ? static_cast<elem_t *>(p.q_out) + n
+                       : static_cast<elem_t *>(n < p.d ? p.K_dst : p.V_dst) + (int64_t)h * head_stride + e;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int m = m0 + r;
+        if (m >= p.B) break;
+        int64_t base = -1;                                                  // or the row is not stored
+        if (is_q) {
+            base = (int64_t)m * p.d;
+        } else if (p.pd.block_table) {
+            int32_t entry;
+            int row;
+            paged_slot(p.pd, m, entry, row);
+            if (row >= 0 && entry >= 0 && entry < p.pd.P_kv) base = ((((int64_t)entry * p.n_heads) << p.pd.blk_log2) + row) * p.head_dim;
+        } else {
+            base = ((int64_t)m * p.n_heads * p.L_cap + p.tok_pos) * p.head_dim;
+        }
+        if (base >= 0) {
+            out_t o;
+#pragma unroll
+            for (int j = 0; j < TN; ++j) o[j] = (elem_t)(sum[j][r] + (float)bias[j]);
+            *reinterpret_cast<out_t *>(dst + base) = o;
+        }
+    }
+}
+
 size_t align256(size_t n) { return (n + 255) / 256 * 256; }
 
 int stream_runs(int units, int workgroups)
@@ -473,6 +626,46 @@ hipError_t launch_dt(const QkvArgs &a, int cus, hipStream_t s)
     if ((e = hipGetLastError()) != hipSuccess || FUSED) return e;
     hipLaunchKernelGGL((qkv_finish_kernel<MT, TN, DT>), dim3((unsigned)(SPLIT * tiles), (unsigned)((a.B + 15) / 16)), dim3(256), 0, s, t);
     return hipGetLastError();
+}
+
+template <int BM, int NS, int DT>
+hipError_t launch_ring_dt(const QkvArgs &a, int cus, hipStream_t s)
+{
+    constexpr int BN = 64;
+    typedef typename Elem<DT>::T elem_t;
+    elem_t *xhat = static_cast<elem_t *>(a.scratch);
+    StreamArgs t;
+    t.xhat = xhat; t.Wq = a.Wq; t.Wkv = a.Wkv; t.bq = a.bq; t.bkv = a.bkv;
+    t.part = reinterpret_cast<float *>(static_cast<char *>(a.scratch) + align256((size_t)a.B * a.d * 2));
+    t.arrived = nullptr;
+    t.q_out = a.q_out; t.K_dst = a.K_dst; t.V_dst = a.V_dst; t.pd = paged_dst(a);
+    t.n_heads = a.n_heads; t.head_dim = a.head_dim; t.L_cap = a.L_cap; t.tok_pos = a.tok_pos;
+    t.B = a.B; t.d = a.d; t.q_tiles = a.d / BN; t.nks = a.d / kUnitK; t.split = 1;
+    const int tiles = a.K_dst ? 3 * t.q_tiles : t.q_tiles;
+    t.units = 3 * t.q_tiles * t.nks;
+    t.live = tiles * t.nks;
+    t.runs = stream_runs(t.units, ring_per_cu<BM, BN, NS>() * cus);
+    hipLaunchKernelGGL(qkv_norm_kernel<DT>, dim3((unsigned)a.B), dim3(256), 0, s, static_cast<const elem_t *>(a.x),
+                       static_cast<const elem_t *>(a.ln_w), static_cast<const elem_t *>(a.ln_b), xhat,
+                       static_cast<elem_t *>(a.act_dst), a.act_row_stride, a.d, a.eps, t.pd, t.arrived, 0);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    auto kern = qkv_ring_kernel<BM, BN, NS, DT>;
+    constexpr int lds = ring::lds_bytes<BM, BN, NS>();
+    static_assert(lds <= 160 * 1024, "the workgroup must fit the LDS of a compute unit");
+    static LdsOnce lds_once;
+    e = allow_dynamic_lds(reinterpret_cast<const void *>(kern), lds, lds_once);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(run_of(t.live - 1, t.units, t.runs) + 1)), dim3(256), lds, s, t);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    hipLaunchKernelGGL((qkv_ring_finish_kernel<BM, BN, DT>), dim3((unsigned)tiles, BM / 32), dim3(256), 0, s, t);
+    return hipGetLastError();
+}
+
+template <int BM, int NS>
+hipError_t launch_ring(const QkvArgs &a, int cus, hipStream_t s)
+{
+    return a.dtype == 1 ? launch_ring_dt<BM, NS, 1>(a, cus, s) : launch_ring_dt<BM, NS, 0>(a, cus, s);
 }
 
 template <int MT, int TN, int NA, int NB, int SPLIT, bool FUSED = false>
@@ -549,7 +742,14 @@ hipError_t launch_qkv_stream(const QkvArgs &a, hipStream_t s)
     const hipError_t e = current_device_cus(&dev, &cus);
     if (e != hipSuccess) return e;
     if (cus > kQkvStreamCus) cus = kQkvStreamCus;
-    if (a.d % 128 != 0) return launch_any<1, 1>(a, cus, s);
+    if (a.d % 128 != 0) {
+        switch ((a.B + 31) / 32) {
+        case 1: return launch_ring<32, 6>(a, cus, s);
+        case 2: return launch_ring<64, 5>(a, cus, s);
+        case 3: return launch_ring<96, 4>(a, cus, s);
+        default: return launch_ring<128, 3>(a, cus, s);
+        }
+    }
     // Q alone: two workgroups a run, each with the same units along the reduction of 64 features, so the bits are the same
     return a.K_dst ? launch_any<2, 1>(a, cus, s) : launch_any<1, 2>(a, cus, s);
 }
