@@ -12,9 +12,10 @@
 // of a token: the block table is read with scalar loads, one entry for every 16 tokens of a step (steps are
 // aligned to 64 tokens inside a pair, so that 16 tokens never straddle a block), during the step before.  Where a workgroup
 // per pair keeps the chip as busy (pair_in_one_launch), its wavefronts merge in LDS and there is no second kernel.
-// Measured with the merge (profiles/decode_attention_cached.txt, 16-token blocks in random order; in brackets with ranges
-// that end inside a step, entries fetched when they are needed and a merge that walks the partials one by one): 411 MB of
-// 32 ragged requests 72.8 us (90.5), 7.6 GB 1180 (1212), 33 MB of one request 12.4 (42).
+// Measured, the form taken (profiles/decode_attention_cached.txt, 16-token blocks in random order; in brackets ranges and merge
+// where that is not the form taken, from another session): 411 MB of 32 ragged requests 65.6 us (72.8), 67 MB 10.7 (15.8), 33 MB of one
+// request, ranges, 12.1.  Before, with ranges that ended inside a step, entries fetched when they were needed and a merge that
+// walked the partials one by one: 411 MB 90.5, 7.6 GB 1212, one request 42.
 #include "hk_internal.h"
 #include "elem.h"
 #include "attn_merge.h"
@@ -263,7 +264,8 @@ bool pair_in_one_launch(const PagedAttnArgs &a)
     const int64_t n = (longest + kTile - 1) / kTile * (a.head_dim / 64);
     if (n <= 16) return true;
     const int64_t tokens = a.total_tokens - a.other_tokens, room = longest * a.B;
-    if (pairs >= 448) return n <= 64 && tokens * a.H >= 224 * longest;
+    if (pairs >= 448)
+        return n <= (pairs < 2048 ? 64 : 128) && tokens * a.H >= 224 * longest && (pairs < 3072 || n <= 32 || 10 * tokens <= 9 * room);
     if (pairs < 128 || 2 * tokens < room) return false;
     if (pairs < 180) return n <= 32;
     return pairs <= 256 || n <= 24;
