@@ -444,8 +444,8 @@ __global__ __launch_bounds__(256) void qkv_finish_kernel(StreamArgs p)
 }
 
 // ---- layers that 128 does not divide: units of 64 features, both operands in one ring, two workgroups a compute unit and twice as
-// many runs, so that Q alone, a third of them, fills the chip (d = 9152, B = 64: 47 us; with rings of their own and one workgroup
-// a unit 72, where Q, K and V gain 1 to 3 %).
+// many runs, so that Q alone, a third of them, fills the chip (d = 8128, B = 64: 47 us; with rings of their own and one workgroup
+// a unit 69, where Q, K and V gain 1 to 3 %).
 // Workgroups of a compute unit: two where the LDS of one allows it.
 template <int BM, int BN, int NS>
 constexpr int ring_per_cu() { return ring::lds_bytes<BM, BN, NS>() <= 80 * 1024 ? 2 : 1; }
