@@ -374,6 +374,7 @@ int hk_paged_decode_attn(const hk_shape *shape, const void *q, int32_t B, const 
  *
  *   n_heads <= 128, B <= 65535; otherwise HK_ERR_SHAPE.
  *   workspace    needs hk_absorbed_workspace_bytes(shape, B, L_kv, L_act); scratch only.
+ *                The size does not fall as B, L_kv or L_act grow: scratch for the largest call serves the smaller ones.
  * bfloat16 tensors are converted to fp16 as they are loaded and the step computes as it does for fp16 (the
  * carried query and the weighted row sum keep 11 significant bits); the conversion is exact for magnitudes
  * from 2^-14 to 65504, larger ones are taken as 65504.
@@ -396,7 +397,8 @@ int hk_hybrid_decode_attn_absorbed(const hk_shape *shape,
  * hk_hybrid_decode_attn_absorbed (scores per block, softmax per request over its own number of checkpoint
  * rows, weighted row sum through the block list); the two parts are joined through their softmax maxima and
  * denominators.  A request without tokens gets an all-zero output.  n_heads <= 128, B <= 65535; workspace:
- * hk_paged_absorbed_workspace_bytes (scratch only; the table, seq_len and cu_tokens are not written).
+ * hk_paged_absorbed_workspace_bytes (scratch only; the table, seq_len and cu_tokens are not written; the size does not
+ * fall as total_tokens or n_act_used grow).
  * When n_act_used > 0 every length and every table entry is read on the device at run time and cu_tokens is not
  * read at all; total_tokens (which sizes the launch and the workspace) may then be any upper bound of the sum of
  * seq_len, and n_act_used any upper bound up to P_act of the ACT blocks the table names.  With such bounds one

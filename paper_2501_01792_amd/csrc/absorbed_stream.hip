@@ -880,6 +880,9 @@ hipError_t launch_gather(const GatherArgs &p, hipStream_t s)
 // Rows that do not stay in the last-level cache (256 MB) until the second pass: loads and stores are non-temporal then.
 bool absorbed_streams(int64_t rows, int d) { return rows * d * 2 > (192LL << 20); }
 
+// Blocks of the fewest rows that the rule below takes for a layer.
+int absorbed_finest_rows_log2(int d) { return d <= 2048 ? 6 : 5; }
+
 // Rows of a block of the score pass, as a power of two: 2^5 the slab form, 2^6 and 2^8 the ring form.  Where the lines lie
 // (whole step, no cached tokens, fp16, us with blocks of 32 / 64 / 256 rows):
 //   a workgroup of the ring form walks the whole reduction axis (d / 64 stages, about 0.3 us each), of the slab form a
@@ -891,7 +894,7 @@ bool absorbed_streams(int64_t rows, int d) { return rows * d * 2 > (192LL << 20)
 int absorbed_rows_log2(int64_t rows, int d, int H)
 {
     if (rows >= 65536 && H > 32) return 8;
-    return rows >= 8192 || d <= 2048 ? 6 : 5;
+    return rows >= 8192 ? 6 : absorbed_finest_rows_log2(d);
 }
 
 hipError_t launch_absorbed_stream(const AbsorbedArgs &a, const AbsorbedRows *pr, int64_t rows, hipStream_t s)

@@ -477,10 +477,11 @@ size_t absorbed_proj_floats(const hk_shape *s, int64_t B)
     return (size_t)parts * rows * s->d;
 }
 
-// Blocks of the score pass that a sequence of up to L rows has, `rows` of them in all sequences.
-size_t absorbed_blocks(const hk_shape *s, int64_t L, int64_t rows)
+// The most blocks of the score pass that a sequence of up to L rows can have.  The pass takes coarser blocks the more rows
+// there are in all; scratch that is enough for many rows must be enough for fewer, so it is that of the finest.
+size_t absorbed_blocks(const hk_shape *s, int64_t L)
 {
-    const int log2 = hk::absorbed_rows_log2(rows, s->d, s->n_heads);
+    const int log2 = hk::absorbed_finest_rows_log2(s->d);
     return (size_t)((L + (1 << log2) - 1) >> log2);
 }
 
@@ -508,7 +509,7 @@ int make_absorbed_plan(const hk_shape *s, int64_t B, int64_t L_kv, int64_t L_act
     p->off_u = take(act ? bh * s->d * 2 : 0);
     p->off_c12 = take(act ? bh * sizeof(float2) : 0);
     p->off_w = take(act ? bh * p->Lp * 2 : 0);
-    p->off_part = take(act ? bh * absorbed_blocks(s, L_act, p->M) * sizeof(float4) : 0);
+    p->off_part = take(act ? bh * absorbed_blocks(s, L_act) * sizeof(float4) : 0);
     p->off_sums = take(act ? bh * sizeof(float4) : 0);
     p->off_y = take(act ? bh * s->d * 2 : 0);
     p->off_outc = take(act ? bh * s->head_dim * 2 : 0);
@@ -840,7 +841,7 @@ int make_paged_absorbed_plan(const hk_shape *s, int64_t B, const hk_paged_cache 
     p->off_u = take(act ? bh * s->d * 2 : 0);
     p->off_c12 = take(act ? bh * sizeof(float2) : 0);
     p->off_w = take(act ? bh * p->Lp * 2 : 0);
-    p->off_part = take(act ? bh * absorbed_blocks(s, max_rows, (int64_t)c->n_act_used * c->block_tokens) * sizeof(float4) : 0);
+    p->off_part = take(act ? bh * absorbed_blocks(s, max_rows) * sizeof(float4) : 0);
     p->off_sums = take(act ? bh * sizeof(float4) : 0);
     p->off_y = take(act ? bh * s->d * 2 : 0);
     p->off_outc = take(act ? bh * s->head_dim * 2 : 0);

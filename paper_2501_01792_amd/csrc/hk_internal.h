@@ -174,6 +174,7 @@ constexpr int kAbsorbMaxHeads = 128;   // heads (rows of the small operand of th
 constexpr int kAbsorbMaxBatch = 128;   // sequences one launch of the output projection takes
 int absorbed_row_pitch(int L_act);     // elements between the rows of w
 int absorbed_rows_log2(int64_t rows, int d, int H);   // block of the score pass for `rows` checkpoint rows in all
+int absorbed_finest_rows_log2(int d);                 // the least of them over all numbers of rows
 void absorbed_project_parts(int d, int H, int *parts, int *steps_per_part);   // how the output projection cuts its reduction axis
 bool absorbed_streams(int64_t rows, int d);                  // whether that many rows outgrow the last-level cache
 // Checkpoint rows in blocks of 2^blk_log2 rows scattered over a pool.

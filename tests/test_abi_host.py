@@ -179,6 +179,27 @@ def test_prepare_layer_rejects_bad_arguments():
     assert _regen(ok, lp=hk.hk_layer_params(FAKE, FAKE, FAKE, FAKE, FAKE + 16)) == hk.HK_ERR_ALIGN
 
 
+@pytest.mark.parametrize("d,H", [(768, 12), (2048, 32), (2112, 33), (4096, 32), (9216, 72), (8192, 128)])
+def test_scratch_for_more_checkpoints_is_enough_for_fewer(d, H):
+    """The step without regeneration takes coarser blocks the more checkpoint rows there are (from 8192 and 65536 rows on):
+    what it asks for must not fall there, neither with the context and the batch nor with the blocks in use of a table, so
+    that a buffer sized once for the largest call serves every smaller one."""
+    s = hk.make_shape(d, H)
+    for B in (1, 3, 8, 64, 100):
+        sizes = [hk.hk_absorbed_workspace_bytes(s, B, 64, L) for L in sorted({*range(0, 5000, 61), *range(1000, 1050), *(
+            max(0, rows // B + i) for rows in (8192, 65536) for i in range(-40, 3))})]
+        assert sizes[0] > 0 and sizes == sorted(sizes), B
+    for L in (1, 128, 1024, 4096):
+        sizes = [hk.hk_absorbed_workspace_bytes(s, B, 64, L) for B in range(1, 129)]
+        assert sizes[0] > 0 and sizes == sorted(sizes), L
+    for bt in (16, 1024):
+        sizes = []
+        for used in sorted({*range(1, 8192, 97), *(max(1, rows // bt + i) for rows in (8192, 65536) for i in range(-3, 3))}):
+            c = hk.hk_paged_cache(FAKE, FAKE, FAKE, FAKE, FAKE, FAKE, 64 * 4096, 8192, 8192, used, bt, 4096 // bt)
+            sizes.append(hk.lib().hk_paged_absorbed_workspace_bytes(ctypes.byref(s), 64, ctypes.byref(c)))
+        assert sizes[0] > 0 and sizes == sorted(sizes), bt
+
+
 def test_qkv_current_rejects_bad_arguments():
     """Every check of hk_qkv_current runs on the host before a launch: no GPU is touched here."""
     ok = hk.make_shape(768, 12)
