@@ -190,13 +190,23 @@ def _dev_ptr(t, name, dtype=None):
     return t.data_ptr()
 
 
+_current_stream = None                                       # handle of the current stream, once torch is needed
+
+
 def _stream_ptr(stream):
-    """The hipStream_t of ``stream``, or of the current device's current stream: its handle alone, without the Stream object
-    that torch.cuda.current_stream builds around it on every call."""
+    """The hipStream_t of ``stream``, or of the current device's current stream: where torch has the calls for it, its handle
+    alone, without the Stream object that torch.cuda.current_stream builds around it on every call."""
+    global _current_stream
     if stream is not None:
         return stream.cuda_stream
-    import torch
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    if _current_stream is None:
+        import torch
+        raw, device = (getattr(torch._C, n, None) for n in ("_cuda_getCurrentRawStream", "_cuda_getDevice"))
+        if raw is not None and device is not None:
+            _current_stream = lambda: raw(device())
+        else:
+            _current_stream = lambda: torch.cuda.current_stream().cuda_stream
+    return _current_stream()
 
 
 def _regenerated(workspace, el, offsets, size):
