@@ -226,8 +226,11 @@ def _params(ln_w, ln_b, Wkv, bkv, prepared=None, el=None):
     if el is None:
         import torch
         el = torch.float16
-    return hk_layer_params(_dev_ptr(ln_w, "ln_w", el), _dev_ptr(ln_b, "ln_b", el), _dev_ptr(Wkv, "Wkv", el),
-                           _dev_ptr(bkv, "bkv", el), _dev_ptr(prepared, "prepared"))
+    lp = hk_layer_params(_dev_ptr(ln_w, "ln_w", el), _dev_ptr(ln_b, "ln_b", el), _dev_ptr(Wkv, "Wkv", el),
+                         _dev_ptr(bkv, "bkv", el), _dev_ptr(prepared, "prepared"))
+    if ln_w is None or ln_b is None or Wkv is None or bkv is None:         # also where the call would not read them
+        raise AttributeError("a layer has four tensors: ln_w, ln_b, Wkv, bkv")
+    return lp
 
 
 def hk_prepared_bytes(shape: hk_shape) -> int:

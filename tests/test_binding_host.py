@@ -1,6 +1,7 @@
 """The binding's host side, without a GPU."""
 import types
 
+import pytest
 import torch
 
 from paper_2501_01792_amd import binding
@@ -14,3 +15,9 @@ def test_current_stream_without_torchs_own_shortcut(monkeypatch):
     monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=0x1230))
     assert binding._stream_ptr(None) == 0x1230
     assert binding._stream_ptr(types.SimpleNamespace(cuda_stream=0x4560)) == 0x4560
+
+
+def test_a_layer_without_its_tensors_is_refused():
+    """Before the library is asked: a step over cached tokens alone does not read the layer, and would take null pointers."""
+    with pytest.raises(AttributeError):
+        binding._params(None, None, None, None)
