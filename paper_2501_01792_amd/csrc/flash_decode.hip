@@ -14,7 +14,7 @@
 //     is unique, and makes the partials of one pair a contiguous run.  A second small kernel
 //     merges the run of every pair by log-sum-exp.  Wavefronts of this kernel never talk to each other:
 //     no LDS, no barrier.  (Those of the merge may: attn_merge.h.)
-//   * Where a workgroup per pair keeps the chip as busy (pair_in_one_launch), its wavefronts merge in LDS and there is
+//   * Where a workgroup per pair keeps the chip as busy (attn_pairs.h), its wavefronts merge in LDS and there is
 //     neither a second kernel nor a partial in memory.
 //   * A wavefront consumes 64 tokens at a time (attn_tile.h).  dh/8 lanes cover one row with 16-byte loads, so
 //     every load instruction of a wavefront reads whole, consecutive rows (1 KiB contiguous), and all K and V
@@ -30,6 +30,7 @@
 #include "hk_internal.h"
 #include "elem.h"
 #include "attn_merge.h"
+#include "attn_pairs.h"
 #include "attn_ranges.h"
 #include "attn_tile.h"
 
@@ -103,7 +104,7 @@ __global__ __launch_bounds__(kThreads, 3) void flash_decode_kernel(
 }
 
 // One workgroup per pair: its P wavefronts take the steps of the two segments in turn and merge in LDS, so that one launch
-// does what the ranges and their merge do in two (pair_in_one_launch says when).  Bound by the latency of a step and of a
+// does what the ranges and their merge do in two (attn_pairs.h says when).  Bound by the latency of a step and of a
 // launch for short contexts; for long ones by what one compute unit can ask for, 58 GB/s: 8 wavefronts of a pair were no
 // faster than 4.  1 and 2 wavefronts a pair, several pairs a workgroup, for contexts of as many steps.
 template <int DH, int DT, int P>
@@ -173,27 +174,7 @@ __global__ __launch_bounds__(merge::kThreads) void merge_partials_kernel(const f
     if (lse && (threadIdx.x & 63) == 0) lse[bh] = make_float2(m, l);
 }
 
-int pair_steps(int L0, int L1) { return (L0 + kTile - 1) / kTile + (L1 + kTile - 1) / kTile; }
-
-// One workgroup per pair, or ranges and a merge?  Ranges balance any number of pairs over the chip, at the price of a second
-// launch, partials in memory and ranges that end inside a pair.  n counts 16 KB of K and V, what a step of 64 tokens of
-// head_dim 64 reads.  Measured over 1 to 4608 pairs x 200 to 4096 tokens, both head dimensions and types, one workgroup per pair
-// against ranges (us, replayed from a graph, fp16, head_dim 128 unless said):
-//   * short contexts: 8 pairs of 400 tokens 6.3 / 8.0, 72 of 200 5.2 / 8.7; at 1000 tokens 8 pairs take 11.4 / 8.9 and 32 take
-//     11.9 / 9.7: too few compute units ask for the rows
-//   * from 128 pairs on: 128 of 1000 tokens 15.5 / 17.0, of 4096 52.4 / 49.3
-//   * 180 to 256 pairs, nearly one per compute unit: 200 of 1000 tokens 19.4 / 25.0, of 4096 68.7 / 75.4; 256: 23.8 / 27.9, 86.4 / 92.7
-//   * 257 to 447: some compute units get two: 290 of 700 tokens faster, of 1000 32.1 / 31.8; 352 of 2000 70.7 / 67.4
-//   * from 448 on the workgroups' own order evens that out: 480 of 2000 tokens 81.6 / 86.3, 4608 707 / 731; level from 3000
-//     tokens on (1100 pairs 273 / 269)
-bool pair_in_one_launch(int64_t pairs, int steps, int head_dim)
-{
-    const int n = steps * (head_dim / 64);
-    if (pairs < 128) return n <= 16;
-    if (pairs < 180) return n <= 32;
-    if (pairs <= 256) return true;
-    return n <= (pairs < 448 ? 24 : 64);
-}
+static_assert(pairs::kTile == kTile, "the rules count the kernel's steps");
 
 template <int DH, int DT, int P>
 void launch_merge(const AttnArgs &a, int L, int64_t total, hipStream_t s)
@@ -210,8 +191,8 @@ hipError_t launch_dh(const AttnArgs &a, hipStream_t s)
     const int L = a.L0 + a.L1;
     const int64_t total = (int64_t)a.BH * L;
     const float scale_log2e = a.scale * 1.4426950408889634f;
-    const int steps = pair_steps(a.L0, a.L1);
-    if (!a.ranges_given && pair_in_one_launch(a.BH, steps, DH)) {
+    const int steps = pairs::steps(a.L0, a.L1);
+    if (!a.ranges_given && pairs::contiguous(a.BH, steps, DH)) {
         auto launch = [&](auto kern, int per_block) {
             hipLaunchKernelGGL(kern, dim3((unsigned)((a.BH + per_block - 1) / per_block)), dim3(kThreads), 0, s,
                                static_cast<const elem_t *>(a.q),

@@ -11,7 +11,7 @@
 // (wavefront + pair); a second kernel merges each pair's run of partials.  What differs is the address
 // of a token: the block table is read with scalar loads, one entry for every 16 tokens of a step (steps are
 // aligned to 64 tokens inside a pair, so that 16 tokens never straddle a block), during the step before.  Where a workgroup
-// per pair keeps the chip as busy (pair_in_one_launch), its wavefronts merge in LDS and there is no second kernel.
+// per pair keeps the chip as busy (attn_pairs.h), its wavefronts merge in LDS and there is no second kernel.
 // Measured, the form taken (profiles/decode_attention_cached.txt, 16-token blocks in random order; in brackets ranges and merge
 // where that is not the form taken, from another session): 411 MB of 32 ragged requests 65.6 us (72.8), 67 MB 10.7 (15.8), 33 MB of one
 // request, ranges, 12.1.  Before, with ranges that ended inside a step, entries fetched when they were needed and a merge that
@@ -19,6 +19,7 @@
 #include "hk_internal.h"
 #include "elem.h"
 #include "attn_merge.h"
+#include "attn_pairs.h"
 #include "attn_ranges.h"
 #include "attn_tile.h"
 
@@ -154,7 +155,7 @@ __global__ __launch_bounds__(kThreads, 3) void paged_decode_kernel(
 }
 
 // One workgroup per (request, head): its wavefronts take the steps of the pair in turn and merge in LDS, so that one launch
-// does what the ranges and their merge do in two (pair_in_one_launch says when), and no wavefront looks for its request.
+// does what the ranges and their merge do in two (attn_pairs.h says when), and no wavefront looks for its request.
 template <int DH, int DT>
 __global__ __launch_bounds__(kThreads, 3) void paged_pair_kernel(
     const typename Elem<DT>::T *__restrict__ q,
@@ -251,26 +252,6 @@ void launch_merge(const PagedAttnArgs &a, int64_t total, hipStream_t s)
                        static_cast<typename Elem<DT>::T *>(a.out), a.lse);
 }
 
-// One workgroup per pair, or ranges and a merge?  As in flash_decode.hip (which has the figures of pairs of one length), with
-// the longest length that the table has room for; n counts 16 KB of K and V.  Lengths that differ make the ranges worse (a
-// wavefront searches its requests, and steps over those that end) and leave compute units to the long pairs: half of the
-// requests 16 tokens, half L, 256 pairs, L = 1000: 16.1 us against 27.6; 1024 pairs, L = 2000: 93.5 against 122; lengths L/2 to L, 32
-// requests x 32 heads, L = 1000: 71.7 against 77.0; 2560 pairs, L = 2000: 320 against 326; 864, L = 4000: 232 against 230.
-// What a workgroup per pair cannot balance is a few long requests among many short ones: beyond short contexts the tokens have to
-// be those of 224 pairs of full length, or half of what the table has room for where there are fewer than 448 pairs.
-bool pair_in_one_launch(const PagedAttnArgs &a)
-{
-    const int64_t pairs = (int64_t)a.B * a.H, longest = (int64_t)a.max_blocks * a.block_tokens;
-    const int64_t n = (longest + kTile - 1) / kTile * (a.head_dim / 64);
-    if (n <= 16) return true;
-    const int64_t tokens = a.total_tokens - a.other_tokens, room = longest * a.B;
-    if (pairs >= 448)
-        return n <= (pairs < 2048 ? 64 : 128) && tokens * a.H >= 224 * longest && (pairs < 3072 || n <= 32 || 10 * tokens <= 9 * room);
-    if (pairs < 128 || 2 * tokens < room) return false;
-    if (pairs < 180) return n <= 32;
-    return pairs <= 256 || n <= 24;
-}
-
 template <int DH, int DT>
 hipError_t launch_dh(const PagedAttnArgs &a, hipStream_t s)
 {
@@ -279,7 +260,7 @@ hipError_t launch_dh(const PagedAttnArgs &a, hipStream_t s)
     const float scale_log2e = a.scale * 1.4426950408889634f;
     int blk_log2 = 0;
     while ((1 << blk_log2) < a.block_tokens) ++blk_log2;
-    if (total > 0 && pair_in_one_launch(a)) {
+    if (total > 0 && pairs::paged(a.B, a.H, (int64_t)a.max_blocks * a.block_tokens, a.total_tokens - a.other_tokens, a.head_dim)) {
         hipLaunchKernelGGL((paged_pair_kernel<DH, DT>), dim3((unsigned)(a.B * a.H)), dim3(kThreads), 0, s,
                            static_cast<const elem_t *>(a.q),
                            static_cast<const elem_t *>(a.K_pool), static_cast<const elem_t *>(a.V_pool),
