@@ -142,6 +142,10 @@ __device__ __forceinline__ RowStats row_stats(float s1, float s2, float first, i
 //     rows of one head: D of v_mfma_f32_16x16x32 has row 4 (lane / 16) + r of block i, head lane % 16.
 //   * RW = 2, NW = 8 (256 rows, U read once for them) and RW = 4, NW = 4 were level (388 us; 128 rows: 431), as were 2 and 4
 //     stages of rows and up to 8 of U; fragments of the next half read under the MFMAs of this one: 390.
+//   * From six blocks of heads on the 256-row form keeps 25 to 64 registers in scratch, and is the best all the same: 96 heads, d =
+//     12288, 65536 rows: 721 us the whole step, 742 with 128 rows (RW = 1, NW = 8, no scratch), 792 with 64; 128 heads, d =
+//     16384: 1145 / 1152 / 1397.  Blocks of 16 heads one by one: 81 to 96 heads on the form of 128 took 781 us there, and in bf16
+//     at 16384 rows of d = 6144 178, where six blocks take 163.
 template <int HB, int RW, int NW, int XS, int US>
 constexpr int ring_lds_bytes() { return NW * XS * RW * 2048 + US * HB * 2048 + NW * HB * 16 * 12; }
 
@@ -838,6 +842,8 @@ hipError_t launch_scores_form(const ScoreArgs &p, int rows_log2, int64_t items, 
     case 3: return launch_ring_rows<3, DT, PAGED>(p, rows_log2, items, cus, s);
     case 4: return launch_ring_rows<4, DT, PAGED>(p, rows_log2, items, cus, s);
     case 5: return launch_ring_rows<5, DT, PAGED>(p, rows_log2, items, cus, s);
+    case 6: return launch_ring_rows<6, DT, PAGED>(p, rows_log2, items, cus, s);
+    case 7: return launch_ring_rows<7, DT, PAGED>(p, rows_log2, items, cus, s);
     default: return launch_ring_rows<8, DT, PAGED>(p, rows_log2, items, cus, s);
     }
 }
@@ -871,6 +877,8 @@ hipError_t launch_gather(const GatherArgs &p, hipStream_t s)
     case 3: return launch_gather_as<3, DT, PAGED>(p, s);
     case 4: return launch_gather_as<4, DT, PAGED>(p, s);
     case 5: return launch_gather_as<5, DT, PAGED>(p, s);
+    case 6: return launch_gather_as<6, DT, PAGED>(p, s);
+    case 7: return launch_gather_as<7, DT, PAGED>(p, s);
     default: return launch_gather_as<8, DT, PAGED>(p, s);
     }
 }

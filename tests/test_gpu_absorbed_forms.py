@@ -22,6 +22,8 @@ SIZES = [
     (33, 64, 2, 1100),                                                          # 35 of them: two stretches
     (40, 64, 8, 1025), (33, 64, 100, 83), (50, 64, 5, 1700), (72, 64, 9, 1000), (128, 64, 2, 4099),   # 64-row blocks, wide
     (40, 64, 64, 1025), (33, 64, 2, 33000), (50, 64, 40, 1700), (72, 64, 33, 1990), (100, 64, 11, 6000),   # 256-row blocks
+    (81, 64, 2, 70), (96, 64, 9, 1000), (88, 64, 33, 1990),                     # six and seven blocks of heads, each form
+    (97, 64, 2, 70), (112, 64, 9, 1000), (104, 64, 11, 6000),
 ]
 ids = ["%dx%d-%dx%d" % s for s in SIZES]
 
