@@ -66,9 +66,12 @@ struct Plan {
     int rest_form;
 };
 constexpr double kSecondUs = 5., kSure = 0.2;
-inline Plan plan(int64_t M, int d, int cus)
+// cu_limit > 0: the caller keeps compute units free of the 256 x 256 tiles; rounds over all of them are not what that launch
+// takes then (240 units, d = 4096, 2600 rows, beside the attention: 230 us in two launches, 200 in one).
+inline Plan plan(int64_t M, int d, int cus, int cu_limit)
 {
     const Plan one = {pick(M, d, cus), M, 0};
+    if (cu_limit > 0) return one;
     const TileForm &f = kForms[0];
     const int64_t cols = col_tiles(f, d), tiles = row_tiles(f, M) * cols;
     if (tiles < cus) return one;

@@ -182,7 +182,7 @@ hipError_t launch_kv_gemm_prepared(const KvGemmArgs &a, hipStream_t s)
     int dev = 0, cus = 0;
     const hipError_t e = current_device_cus(&dev, &cus);
     if (e != hipSuccess) return e;
-    const forms::Plan p = forms::plan(a.M, a.d, cus);
+    const forms::Plan p = forms::plan(a.M, a.d, cus, a.cu_limit);
     KvGemmArgs part = a;
     part.M = p.rows;
     const hipError_t first = launch_kv_gemm_form(part, p.form, s);
