@@ -42,6 +42,10 @@ inline bool contiguous(int64_t pairs, int steps, int head_dim)
 // requests x 32 heads, L = 1000: 71.7 against 77.0; 2560 pairs, L = 2000: 320 against 326; 864, L = 4000: 232 against 230.
 // What a workgroup per pair cannot balance is a few long requests among many short ones: beyond short contexts the tokens have to
 // be those of 224 pairs of full length, or half of what the table has room for where there are fewer than 448 pairs.
+// `tokens` may be a bound, up to the room, whatever the lengths are: the lines for n lie where one long request among short ones
+// (16 tokens) is not slower for it either.  256 pairs, L = 1000: 12.5 us against 14.0, L = 2000: 22.2 against 17.6, L = 4096: 41.9
+// against 23.7 (and 81 against 89 where all are that long); 240 pairs of head_dim 64, L = 2000 (n = 32): 10.5 against 14.2, L =
+// 3000: 17.4 against 14.9.
 inline bool paged(int64_t requests, int heads, int64_t longest, int64_t tokens, int head_dim)
 {
     const int64_t pairs = requests * heads;
@@ -52,8 +56,7 @@ inline bool paged(int64_t requests, int heads, int64_t longest, int64_t tokens, 
     if (pairs >= 448)
         return n <= (pairs < 2048 ? 64 : 128) && tokens * heads >= 224 * longest && (pairs < 3072 || n <= 32 || 10 * tokens <= 9 * room);
     if (pairs < 128 || 2 * tokens < room) return false;
-    if (pairs < 180) return n <= 32;
-    return pairs <= 256 || n <= 24;
+    return n <= (pairs <= 256 ? 32 : 24);
 }
 
 }  // namespace pairs

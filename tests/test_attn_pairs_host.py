@@ -14,3 +14,12 @@ def test_more_pairs_than_a_launch_has_threads_for(rule):
     most = (1 << 24) - 1
     assert rule([("p", most, 1, 16, most, 64), ("p", most // 5, 5, 512, 5, 128), ("c", most, 64, 0, 64)]) == [True] * 3
     assert rule([("p", most + 1, 1, 16, most, 64), ("p", 1 << 21, 8, 16, 1 << 21, 128), ("c", most + 1, 64, 0, 64)]) == [False] * 3
+
+
+def test_a_bound_in_the_place_of_the_tokens(rule):
+    """The caller may pass the whole room of the table as the number of tokens.  128 to 256 pairs take a workgroup each then only
+    up to a length at which a few long requests among short ones are no slower for it."""
+    def full(requests, heads, room, dh):
+        return ("p", requests, heads, room, requests * room, dh)
+    assert rule([full(8, 32, 1024, 128), full(5, 32, 1024, 128), full(20, 12, 2048, 64)]) == [True] * 3
+    assert rule([full(8, 32, 1040, 128), full(8, 32, 4096, 128), full(7, 32, 2000, 128), full(20, 12, 3008, 64)]) == [False] * 4
