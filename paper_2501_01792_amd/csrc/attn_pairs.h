@@ -45,7 +45,11 @@ inline bool contiguous(int64_t pairs, int steps, int head_dim)
 // `tokens` may be a bound, up to the room, whatever the lengths are: the lines for n lie where one long request among short ones
 // (16 tokens) is not slower for it either.  256 pairs, L = 1000: 12.5 us against 14.0, L = 2000: 22.2 against 17.6, L = 4096: 41.9
 // against 23.7 (and 81 against 89 where all are that long); 240 pairs of head_dim 64, L = 2000 (n = 32): 10.5 against 14.2, L =
-// 3000: 17.4 against 14.9.
+// 3000: 17.4 against 14.9.  From 448 pairs on, L = 2000 (n = 64): 448 pairs 25.1 against 26.1, 640 26.3 / 25.5, 2048 26.4 / 27.0, 4608
+// 31.2 / 38.6; L = 2500 (n = 80): 448 30.0 / 27.1, 2048 31.4 / 29.7; L = 4096: 2048 46.2 / 35.2, 2880 52.0 / 50.1.
+// From 2560 pairs on lengths that are all alike are level up to n = 48 (9216 pairs, L = 1500: 1096 / 1103) and lose a little beyond
+// (L = 2000, 2304 pairs: 366 / 371; 2880 480 / 473, 4608 758 / 748, 9216 1514 / 1478); lengths L/2 to L gain 1 to 3 % there, an eighth
+// of the requests L and the others 16 tokens a quarter (4608: 108 / 145).
 inline bool paged(int64_t requests, int heads, int64_t longest, int64_t tokens, int head_dim)
 {
     const int64_t pairs = requests * heads;
@@ -54,7 +58,7 @@ inline bool paged(int64_t requests, int heads, int64_t longest, int64_t tokens, 
     if (n <= 16) return true;
     const int64_t room = longest * requests;
     if (pairs >= 448)
-        return n <= (pairs < 2048 ? 64 : 128) && tokens * heads >= 224 * longest && (pairs < 3072 || n <= 32 || 10 * tokens <= 9 * room);
+        return n <= 64 && tokens * heads >= 224 * longest && (pairs < 2560 || n <= 32 || 10 * tokens <= 9 * room);
     if (pairs < 128 || 2 * tokens < room) return false;
     return n <= (pairs <= 256 ? 32 : 24);
 }
