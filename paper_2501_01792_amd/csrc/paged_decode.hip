@@ -132,7 +132,8 @@ __global__ __launch_bounds__(kThreads, 3) void paged_decode_kernel(
         const int t_last = t_end < len ? t_end & ~(kTile - 1) : len;
         const int pair = r * H + h;
         const int32_t *tab = table + (int64_t)r * max_blocks;
-        const int last_block = (t_last - 1) >> blk_log2;           // used only when the range is not empty
+        int last_block = (t_last - 1) >> blk_log2;                 // used only when the range is not empty
+        if (last_block >= max_blocks) last_block = max_blocks - 1;             // a corrupt length cannot leave the table's row
 
         const half8_t qv = *reinterpret_cast<const half8_t *>(q + (int64_t)pair * DH + c * 8);
         tile_t tile;
@@ -174,7 +175,8 @@ __global__ __launch_bounds__(kThreads, 3) void paged_pair_kernel(
     const int g = lane / LPR, c = lane % LPR;
     const int blk = 1 << blk_log2;
     const int64_t blk_elems = (int64_t)H * blk * DH;
-    const int len = seq_len[r];
+    const int64_t room = (int64_t)max_blocks << blk_log2;
+    const int len = seq_len[r] < room ? seq_len[r] : (int)room;            // a corrupt length cannot leave the table's row
     const int last_block = (len - 1) >> blk_log2;              // used only when there are tokens
     const int32_t *tab = table + (int64_t)r * max_blocks;
     const half8_t qv = *reinterpret_cast<const half8_t *>(q + (int64_t)pair * DH + c * 8);

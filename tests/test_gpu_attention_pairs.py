@@ -93,3 +93,32 @@ def test_paged_pairs_against_ranges(hk, H, dh, lens, spare, bt, dtype):
         err = float((out[b:b + 1].double() - ref).norm() / ref.norm())
         print("request %d rel_l2 %.2e" % (b, err), flush=True)
         assert err <= TOL[dtype]
+
+
+@pytest.mark.parametrize("H,room", [(40, 512), (40, 2048)], ids=["pairs", "ranges"])
+def test_a_length_beyond_the_table(hk, H, room):
+    """A request whose length is more than its row of the table holds reads no entry of another row: with a workgroup per pair its
+    context ends with the row; in ranges the tokens beyond are the last block's, again.  (The row that follows it here is one of
+    the same tensor that the call is not given.)"""
+    B, dh, bt = 3, 128, 16
+    gen = torch.Generator(device="cuda").manual_seed(room)
+    cols, over = room // bt, 5 * bt
+    K, V = (torch.empty(4 * cols, H, bt, dh, dtype=torch.float16, device="cuda").normal_(generator=gen) for _ in range(2))
+    q = torch.empty(B, H, dh, dtype=torch.float16, device="cuda").normal_(generator=gen)
+    rows = torch.randperm(4 * cols, generator=gen, device="cuda", dtype=torch.int64).to(torch.int32).view(4, cols)
+    layer = tuple(torch.zeros(8, device="cuda", dtype=torch.float16) for _ in range(4))
+
+    def step(table, lens):
+        cu = torch.tensor([0] + list(np.cumsum(lens)), dtype=torch.int64, device="cuda")
+        return hk.paged_decode_attn(q, K, V, None, table, torch.tensor(lens, dtype=torch.int32, device="cuda"), bt, layer,
+                                    cu_tokens=cu, total_tokens=sum(lens))
+
+    lens = [room - over - 7, 33, room + over]
+    got = step(rows[:B], lens)
+    if room == 512:
+        want = step(rows[:B], lens[:2] + [room])
+        assert torch.equal(got, want)
+    else:
+        longer = torch.cat([rows[:B], rows[:B, -1:].expand(B, over // bt)], 1).contiguous()
+        want = step(longer, lens)
+        assert float((got.double() - want.double()).norm() / want.double().norm()) <= TOL[torch.float16]
