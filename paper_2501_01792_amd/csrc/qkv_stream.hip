@@ -146,7 +146,33 @@ struct StreamArgs {
     PagedDst pd;
 };
 
-// Where the rows of 4 TN consecutive features from feature n of Q (is_q) or of K, V go, and their store, bias added and rounded.
+// Feature n of Q (is_q) or of K, V in the row that a store begins with, and where row m lies from there (-1: it is not stored).
+template <int DT>
+__device__ __forceinline__ typename Elem<DT>::T *feature_dst(const StreamArgs &p, bool is_q, int n)
+{
+    typedef typename Elem<DT>::T elem_t;
+    const int f = n < p.d ? n : n - p.d;
+    const int head_stride = p.pd.block_table ? (p.head_dim << p.pd.blk_log2) : p.L_cap * p.head_dim;
+    return is_q ? static_cast<elem_t *>(p.q_out) + n
+                : static_cast<elem_t *>(n < p.d ? p.K_dst : p.V_dst) + (int64_t)(f / p.head_dim) * head_stride + f % p.head_dim;
+}
+__device__ __forceinline__ int64_t row_offset(const StreamArgs &p, bool is_q, int m)
+{
+    int64_t base = -1;
+    if (is_q) {
+        base = (int64_t)m * p.d;
+    } else if (p.pd.block_table) {
+        int32_t entry;
+        int row;
+        paged_slot(p.pd, m, entry, row);
+        if (row >= 0 && entry >= 0 && entry < p.pd.P_kv) base = ((((int64_t)entry * p.n_heads) << p.pd.blk_log2) + row) * p.head_dim;
+    } else {
+        base = ((int64_t)m * p.n_heads * p.L_cap + p.tok_pos) * p.head_dim;
+    }
+    return base;
+}
+
+// Store of 4 TN consecutive features from feature n of Q (is_q) or of K, V, bias added and rounded.
 template <int TN, int DT>
 struct Output {
     typedef typename Elem<DT>::T elem_t;
@@ -159,25 +185,12 @@ struct Output {
     __device__ __forceinline__ Output(const StreamArgs &args, bool is_q_, int n) : p(args), is_q(is_q_)
     {
         bias = *reinterpret_cast<const out_t *>(static_cast<const elem_t *>(is_q ? p.bq : p.bkv) + n);
-        const int f = n < p.d ? n : n - p.d;
-        const int head_stride = p.pd.block_table ? (p.head_dim << p.pd.blk_log2) : p.L_cap * p.head_dim;
-        dst = is_q ? static_cast<elem_t *>(p.q_out) + n
-                   : static_cast<elem_t *>(n < p.d ? p.K_dst : p.V_dst) + (int64_t)(f / p.head_dim) * head_stride + f % p.head_dim;
+        dst = feature_dst<DT>(p, is_q, n);
     }
     __device__ __forceinline__ void store(int m, const float4_t (&sum)[TN]) const
     {
         if (m >= p.B) return;
-        int64_t base = -1;                                     // or the row is not stored
-        if (is_q) {
-            base = (int64_t)m * p.d;
-        } else if (p.pd.block_table) {
-            int32_t entry;
-            int row;
-            paged_slot(p.pd, m, entry, row);
-            if (row >= 0 && entry >= 0 && entry < p.pd.P_kv) base = ((((int64_t)entry * p.n_heads) << p.pd.blk_log2) + row) * p.head_dim;
-        } else {
-            base = ((int64_t)m * p.n_heads * p.L_cap + p.tok_pos) * p.head_dim;
-        }
+        const int64_t base = row_offset(p, is_q, m);
         if (base < 0) return;
         out_t o;
 #pragma unroll
@@ -556,26 +569,12 @@ __global__ __launch_bounds__(256) void qkv_ring_finish_kernel(StreamArgs p)
     const bool is_q = tile < p.q_tiles;
     const int n = ((is_q ? tile : tile - p.q_tiles) * p.split + part) * BN + (BN / 2) * (wave & 1) + TN * (lane & 15);   // first of TN features
     const out_t bias = *reinterpret_cast<const out_t *>(static_cast<const elem_t *>(is_q ? p.bq : p.bkv) + n);
-    const int f = n < p.d ? n : n - p.d;
-    const int h = f / p.head_dim, e = f % p.head_dim;
-    const int head_stride = p.pd.block_table ? (p.head_dim << p.pd.blk_log2) : p.L_cap * p.head_dim;
-    elem_t *dst = is_q ? static_cast<elem_t *>(p.q_out) + n
-                       : static_cast<elem_t *>(n < p.d ? p.K_dst : p.V_dst) + (int64_t)h * head_stride + e;
+    elem_t *dst = feature_dst<DT>(p, is_q, n);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const int m = m0 + r;
         if (m >= p.B) break;
-        int64_t base = -1;                                                  // or the row is not stored
-        if (is_q) {
-            base = (int64_t)m * p.d;
-        } else if (p.pd.block_table) {
-            int32_t entry;
-            int row;
-            paged_slot(p.pd, m, entry, row);
-            if (row >= 0 && entry >= 0 && entry < p.pd.P_kv) base = ((((int64_t)entry * p.n_heads) << p.pd.blk_log2) + row) * p.head_dim;
-        } else {
-            base = ((int64_t)m * p.n_heads * p.L_cap + p.tok_pos) * p.head_dim;
-        }
+        const int64_t base = row_offset(p, is_q, m);
         if (base >= 0) {
             out_t o;
 #pragma unroll
