@@ -1,7 +1,8 @@
 """The attention with a workgroup per (sequence, head) and the attention cut into ranges, on either side of the rule that
 chooses between them: one, two and more steps of 64 tokens in one or two segments, workgroups that hold several pairs and are
-partly filled, the lengths and numbers of pairs next to the rule's lines.  Against softmax attention in 64 bits; the same call
-with a number of ranges of the caller's own (always cut into ranges) has to agree.
+partly filled, the lengths and numbers of pairs next to the rule's lines (test_attn_pairs_host.py says which form each of these
+sizes takes).  Against softmax attention in 64 bits; the same inputs cut into ranges have to agree: by a number of ranges of the
+caller's own, or, on a block table, by columns behind the requests' blocks that give the table room for longer rows.
 
 Tolerance: the scores and sums are fp32 (errors of order 1e-6 here), so what is left is the output's one rounding, at most
 2^-11 (fp16) or 2^-8 (bf16) of each element, and with it of the norm."""
@@ -59,12 +60,14 @@ def test_pairs_against_ranges(hk, B, H, dh, L_kv, L_act, dtype):
 PAGED = [(3, 128, [513, 0, 1, 512], 0), (3, 128, [512, 64, 65], 0), (40, 128, [1024, 1000, 513], 0), (43, 128, [1024, 1000, 513], 0),
          (43, 128, [1025, 1000, 513], 0), (64, 128, [2100, 1100, 2000, 700], 0), (86, 64, [1500, 1536, 800], 0),
          (86, 64, [1600, 1536, 800], 0), (64, 64, [4096] * 4 + [17, 0, 2000], 0), (64, 64, [4096] * 3 + [17, 0, 300, 2000], 0),
-         (64, 128, [100] * 8, 40), (64, 128, [1000] * 8, 1), (64, 128, [1000] * 8, 200)]
+         (64, 128, [100] * 8, 40), (64, 128, [1000] * 8, 1), (64, 128, [1000] * 8, 200),
+         (39, 128, [1100 - 7 * i for i in range(65)], 0), (40, 128, [1100 - 7 * i for i in range(64)], 0), (40, 128, [1100] * 64, 0)]
 
 
 @pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16], ids=["f16", "bf16"])
 @pytest.mark.parametrize("bt", [16, 128])
-@pytest.mark.parametrize("H,dh,lens,spare", PAGED, ids=["%dx%d-%s-%d" % (h, dh, "_".join(map(str, n)), s) for h, dh, n, s in PAGED])
+@pytest.mark.parametrize("H,dh,lens,spare", PAGED, ids=["%dx%d-%s-%d" % (h, dh, "_".join(map(str, n)) if len(n) < 9 else "%dx%d_to_%d" % (len(n), n[-1], n[0]), s)
+                                               for h, dh, n, s in PAGED])
 def test_paged_pairs_against_ranges(hk, H, dh, lens, spare, bt, dtype):
     B = len(lens)
     gen = torch.Generator(device="cuda").manual_seed(sum(lens) + H)
@@ -75,24 +78,49 @@ def test_paged_pairs_against_ranges(hk, H, dh, lens, spare, bt, dtype):
     counts = [(n + bt - 1) // bt for n in lens]
     rng = np.random.default_rng(sum(lens))
     order = rng.permutation(sum(counts))
-    table = np.full((B, max(counts) + spare), -12345, np.int32)          # what lies behind a request's blocks is never used
+    room_for_ranges = 4097 * 128 // dh                                   # tokens; what lies behind a request's blocks is never used
+    table = np.full((B, max(counts) + spare + room_for_ranges // bt), -12345, np.int32)
     for b, at in enumerate(np.cumsum([0] + counts[:-1])):
         table[b, :counts[b]] = order[at:at + counts[b]]
     K, V = draw(len(order), H, bt, dh, std=1.5), draw(len(order), H, bt, dh)
     q = draw(B, H, dh)
     layer = tuple(torch.zeros(8, device="cuda", dtype=dtype) for _ in range(4))
     cu = torch.tensor(np.concatenate([[0], np.cumsum(lens)]), dtype=torch.int64, device="cuda")
-    out = hk.paged_decode_attn(q, K, V, None, torch.from_numpy(table).cuda(), torch.tensor(lens, dtype=torch.int32, device="cuda"), bt,
-                               layer, cu_tokens=cu, total_tokens=sum(lens))
+    lens_dev = torch.tensor(lens, dtype=torch.int32, device="cuda")
+    chosen, cut = (hk.paged_decode_attn(q, K, V, None, torch.from_numpy(np.ascontiguousarray(t)).cuda(), lens_dev, bt, layer,
+                                        cu_tokens=cu, total_tokens=sum(lens)) for t in (table[:, :max(counts) + spare], table))
     for b, n in enumerate(lens):
         if n == 0:
-            assert not out[b].any()
+            assert not chosen[b].any() and not cut[b].any()
             continue
         rows = [t[torch.from_numpy(table[b, :counts[b]]).long().cuda()].transpose(0, 1).reshape(1, H, -1, dh)[:, :, :n] for t in (K, V)]
         ref = _reference(q[b:b + 1], *rows)
-        err = float((out[b:b + 1].double() - ref).norm() / ref.norm())
-        print("request %d rel_l2 %.2e" % (b, err), flush=True)
-        assert err <= TOL[dtype]
+        for name, out in (("chosen", chosen), ("ranges", cut)):
+            err = float((out[b:b + 1].double() - ref).norm() / ref.norm())
+            print("request %d %s rel_l2 %.2e" % (b, name, err), flush=True)
+            assert err <= TOL[dtype], name
+
+
+@pytest.mark.parametrize("H,room", [(64, 1008), (64, 2064)], ids=["pairs", "ranges"])
+def test_tokens_known_as_a_bound(hk, H, room):
+    """One long request among short ones, and the whole room of the table in the place of the tokens' number."""
+    B, dh, bt = 8, 128, 16
+    lens = [room - 3] + [5, 16, 0, 17, 1, 64, 33]
+    gen = torch.Generator(device="cuda").manual_seed(room)
+    K, V = (torch.empty(B * room // bt, H, bt, dh, dtype=torch.float16, device="cuda").normal_(generator=gen) for _ in range(2))
+    q = torch.empty(B, H, dh, dtype=torch.float16, device="cuda").normal_(generator=gen)
+    table = torch.randperm(len(K), generator=gen, device="cuda", dtype=torch.int64).to(torch.int32).view(B, -1)
+    layer = tuple(torch.zeros(8, device="cuda", dtype=torch.float16) for _ in range(4))
+    cu = torch.tensor([0] + list(np.cumsum(lens)), dtype=torch.int64, device="cuda")
+    out = hk.paged_decode_attn(q, K, V, None, table, torch.tensor(lens, dtype=torch.int32, device="cuda"), bt, layer, cu_tokens=cu,
+                               total_tokens=B * room)
+    for b, n in enumerate(lens):
+        rows = [t[table[b].long()].transpose(0, 1).reshape(1, H, -1, dh)[:, :, :n] for t in (K, V)]
+        if n == 0:
+            assert not out[b].any()
+        else:
+            ref = _reference(q[b:b + 1], *rows)
+            assert float((out[b:b + 1].double() - ref).norm() / ref.norm()) <= TOL[torch.float16], b
 
 
 @pytest.mark.parametrize("H,room", [(40, 512), (40, 2048)], ids=["pairs", "ranges"])
