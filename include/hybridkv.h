@@ -246,8 +246,8 @@ int hk_regen_offsets(const hk_shape *shape, int32_t B, int32_t L_act, size_t *k_
  *   events[0] before the first kernel,      events[1] after the LayerNorm statistics,
  *   events[2] after the K/V projection,     events[3] after the attention streaming kernel,
  *   events[4] after the merge of the attention partials (end of the step).
- * Stages that do not run (L_act == 0) leave their event recorded back to back
- * with the previous one.
+ * Stages that do not run (L_act == 0; the merge, where the attention is a single
+ * launch) leave their event recorded back to back with the previous one.
  */
 int hk_hybrid_decode_attn_marked(const hk_shape *shape,
                                  const void *q,
@@ -394,9 +394,9 @@ int hk_hybrid_decode_attn_absorbed(const hk_shape *shape,
  * result up to rounding as hk_paged_decode_attn (Sec. 4.1, 4.2.1; Eq. 7, 3, 4).  Every request's row of the
  * block table is split on the device into its KV blocks and its checkpoint blocks, each in logical order.  The
  * KV blocks take the block-table attention kernel; the checkpoint blocks take the steps of
- * hk_hybrid_decode_attn_absorbed (scores per block, softmax per request over its own number of checkpoint
- * rows, weighted row sum through the block list); the two parts are joined through their softmax maxima and
- * denominators.  A request without tokens gets an all-zero output.  n_heads <= 128, B <= 65535; workspace:
+ * hk_hybrid_decode_attn_absorbed over the request's own number of checkpoint rows (scores, with the softmax of
+ * every stretch of rows about a reference of its own; weighted row sum through the block list, in which the
+ * stretches meet); the two parts are joined through their softmax references and denominators.  A request without tokens gets an all-zero output.  n_heads <= 128, B <= 65535; workspace:
  * hk_paged_absorbed_workspace_bytes (scratch only; the table, seq_len and cu_tokens are not written; the size does not
  * fall as total_tokens or n_act_used grow).
  * When n_act_used > 0 every length and every table entry is read on the device at run time and cu_tokens is not

@@ -714,7 +714,8 @@ hipError_t launch_any(const QkvArgs &a, int cus, hipStream_t s)
 // Wider layers than 9216 stay with one launch.  A build without the limit gained on Q + K + V (10240: 0.81 to 1.10 of the
 // one-launch kernel's time; 11264 and 12288, where that kernel's workgroups need a second round: 0.47 to 0.87; 16384: 0.60 to
 // 0.97), but lost on Q alone from 11264 on (up to 1.07 there, 1.14 at 12288, 1.27 at 14336), and q must come from the same
-// form in both: a rule for them needs the cut of Q alone to fill the chip first.
+// form in both.  That was with a third of the workgroups for Q alone; they fill the chip since two share a run, and the
+// widths beyond 9216 have not been measured again.
 bool qkv_stream_takes(int B, int d, int dtype)
 {
     if (B <= 0 || B > kQkvMaxRows || d % kUnitK != 0 || d > kMaxD) return false;

@@ -28,7 +28,7 @@ SCRATCH = os.path.join("gpurun_out", "prof")      # raw profiler output, relativ
 
 KERNELS = ("column_product|paged_index|paged_prefix|paged_append|absorbed_scores_ring|absorbed_scores_slab|absorbed_gather|"
            "absorbed_project_block|absorbed_project|absorbed_join|"
-           "qkv_fused|qkv_norm|qkv_stream|qkv_finish|paged_decode|paged_pair|paged_merge|kv_gemm_fold|kv_gemm_tile|kv_gemm|prepare_layer|"
+           "qkv_fused|qkv_norm|qkv_stream|qkv_ring_finish|qkv_ring|qkv_finish|paged_decode|paged_pair|paged_merge|kv_gemm_fold|kv_gemm_tile|kv_gemm|prepare_layer|"
            "flash_decode|flash_pair|merge_partials|segment_join|mfma_rate|ln_stats[a-z_]*")
 
 # counter groups, each within what one pass can hold (8 SQ, 4 TCC, 2 GRBM)
