@@ -22,8 +22,9 @@
 //     us; 134 MB, which stay: 25 against 22.5), and the results leave with non-temporal stores then: dirty lines that are
 //     written back under a stream of reads cost it far more than their bytes (gather of 2.4 GB, 85 MB of results: 452
 //     against 385 us).
-// Measured on 64 x 2048 rows of d = 9216 (72 heads), before -> now: scores and softmax 471 + 28 -> 381 us (6.3
-// TB/s), gather 465 -> 390; 32 x 512 rows of d = 4096 (32 heads): 28.5 + 6.6 -> 25.5, gather 31 -> 23.5.  Error against 64 bits as
+// Measured on 64 x 2048 rows of d = 9216 (72 heads), before -> now (profiles/absorbed_step_opt66b_ratio0.5.txt, 42 calls on
+// average, in brackets the least): scores and softmax 471 + 28 -> 385 us (376; 6.3 TB/s), gather 465 -> 412 (383); 32 x 512 rows of d =
+// 4096 (32 heads, profiles/absorbed_step_opt6.7b.txt): 28.5 + 6.6 -> 27.0 (25.2), gather 31 -> 23.7 (23.1).  Error against 64 bits as
 // before: 0.90 to 1.11 of it over 13 shapes, 0.99 in the middle (fp16 and bf16).
 #include "hk_internal.h"
 #include "kv_gemm_common.h"

@@ -24,8 +24,8 @@
 //   * Small problems that are cut into ranges have ranges of one step each, aligned to the pairs, so that they too fill the
 //     chip and pay one latency (with at least 128 tokens per range, 64,000 positions ran on 125 of 256 compute units).
 // Measured, the form taken (profiles/decode_attention_cached.txt; in brackets ranges and merge where that is not the form taken,
-// from another session): 4.8 GB fp16 684 us, 7.06 TB/s (727), bf16 711 (747); 268 MB 40.0 (43.9); 67 MB 9.9 (15.0); 33 MB of one
-// request, ranges, 9.8.  Before, with V asked for behind K, at least 128 tokens a range and a merge that walked the partials one
+// from another session): 4.8 GB fp16 686 us, 7.04 TB/s (727), bf16 712 (747); 268 MB 39.5 (43.9); 67 MB 9.9 (15.0); 33 MB of one
+// request, ranges, 9.7.  Before, with V asked for behind K, at least 128 tokens a range and a merge that walked the partials one
 // by one: 4.8 GB fp16 737, bf16 771; 268 MB 47.5; one request 36.4.
 #include "hk_internal.h"
 #include "elem.h"

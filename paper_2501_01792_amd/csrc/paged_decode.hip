@@ -13,7 +13,7 @@
 // aligned to 64 tokens inside a pair, so that 16 tokens never straddle a block), during the step before.  Where a workgroup
 // per pair keeps the chip as busy (attn_pairs.h), its wavefronts merge in LDS and there is no second kernel.
 // Measured, the form taken (profiles/decode_attention_cached.txt, 16-token blocks in random order; in brackets ranges and merge
-// where that is not the form taken, from another session): 411 MB of 32 ragged requests 65.6 us (72.8), 67 MB 10.7 (15.8), 33 MB of one
+// where that is not the form taken, from another session): 411 MB of 32 ragged requests 64.8 us (72.8), 67 MB 10.5 (15.8), 33 MB of one
 // request, ranges, 12.1.  Before, with ranges that ended inside a step, entries fetched when they were needed and a merge that
 // walked the partials one by one: 411 MB 90.5, 7.6 GB 1212, one request 42.
 #include "hk_internal.h"

@@ -30,8 +30,8 @@
 //     (d = 4096, B = 128: 37.4 -> 40.4; 7168, B = 32: 61.6 -> 63.4).
 //   * Non-temporal stores of the parts were slower (B = 64, d = 7168: 74 us against 72): the finishing kernel finds them in cache.
 // Measured, fp16, Q + K + V, new weights in every call, in brackets the one-launch kernel
-// (profiles/qkv_single_kernel_vs_three_launches.txt): d = 7168, B = 32 / 64 / 128: 62 / 70 / 84 us (83 / 113 / 120; 308 MB of
-// weights); d = 4096, B = 128: 37 (69); d = 9216, B = 128: 125 (148 to 169, two sessions).  Error against 64 bits
+// (profiles/qkv_single_kernel_vs_three_launches.txt): d = 7168, B = 32 / 64 / 128: 63 / 71 / 84 us (83 / 111 / 120; 308 MB of
+// weights); d = 4096, B = 128: 38 (70); d = 9216, B = 128: 128 (157).  Error against 64 bits
 // 2.9e-4 (3.6e-4: two roundings on the way into the product); bf16 2.35e-3 (2.8e-3).
 #include "hk_internal.h"
 #include "elem.h"
@@ -695,22 +695,23 @@ hipError_t launch_any(const QkvArgs &a, int cus, hipStream_t s)
 
 }  // namespace
 
-// Where the lines lie (measured, new weights in every call, replayed from a graph, us a call, one-launch kernel against
-// this one, fp16 / bf16 where they differ; next to the lines at 8192 and 8448 with rings that both operands shared, 0 to 3 %
-// slower than now).  Three launches cost 12 to 14 us however small the layer, so many rows and wide
+// Where the lines lie (new weights in every call, replayed from a graph, us a call, one-launch kernel against this one, fp16 /
+// bf16 where they differ).  The sizes that come here: profiles/qkv_single_kernel_vs_three_launches.txt, 306 of them, none slower
+// than 0.96 of the one-launch kernel.  The sizes that stay there (marked *) were measured with rings that both operands shared, 0
+// to 3 % slower than now, and not since.  Three launches cost 12 to 14 us however small the layer, so many rows and wide
 // layers come here.
-//   97 rows and more: every layer from d = 768 on: 25.0 / 28.1 against 13.4 (B = 128); 4096: 69 / 84 against 37; 7168:
-//     116 / 141 against 84; 9216: 148 / 179 against 125; 9152 (units of 64 features): 148 against 149 / 181 against 150
-//   65 to 96 rows: from d = 768 on: 18.8 / 20.9 against 12.3 (B = 65).  fp16 below 8448: 8192, B = 96: 118 against 108;
-//     8256, B = 65: 114 against 107; 8448, B = 96: 111.7 against 116.6; 9216, B = 96: 118 against 127; 9152: 118 against
-//     137.  bf16 everywhere: 9216, B = 96: 145 against 128
-//   33 to 64 rows: from d = 2048 on: 20.6 / 23.7 against 17.6 (B = 33).  fp16 below 8192, where the one-launch kernel
-//     changes to workgroups of 128 features: 8128, B = 64: 132 against 97; 8192, B = 33: 91 against 95 and 101 against 98
-//     (two sessions); 8704: level.  bf16 below 8448: 8256, B = 64: 111 against 104; 8448: 101 against 103; 9152: 109
-//     against 123; 9216: level
+//   97 rows and more: every layer from d = 768 on: 25.1 / 28.0 against 13.9 / 13.7 (B = 128); 4096: 70 / 84 against 38; 7168:
+//     120 / 143 against 84; 9216: 157 / 194 against 128; 9152 (units of 64 features): 160 / 194 against 150
+//   65 to 96 rows: from d = 768 on: 18.7 / 20.8 against 12.5 (B = 65).  fp16 below 8448: 8192, B = 96: 118 against 104;
+//     8256, B = 65: 118 against 110; 8448, B = 96: 111.7 against 116.6*; 9216, B = 96: 118 against 127*; 9152: 118 against
+//     137*.  bf16 everywhere: 9216, B = 96: 154 against 121
+//   33 to 64 rows: from d = 2048 on: 21.2 / 24.2 against 17.8 (B = 33).  fp16 below 8192, where the one-launch kernel
+//     changes to workgroups of 128 features: 8128, B = 64: 135 against 96; 8192, B = 33: 91 against 95 and 101 against 98
+//     (two sessions)*; 8704: level*.  bf16 below 8448: 8256, B = 64: 111 against 103; 8448: 101 against 103*; 9152: 109
+//     against 123*; 9216: level*
 //   up to 32 rows: while the one-launch kernel's workgroups (64 features) fit 256 units at once it is level within 8 % or
-//     faster: 4096, B = 32: 29.7 against 27.4; from 5504 on 60 against 39 (B = 1); 9216: 98 against 93 (B = 1), 105
-//     against 94 (B = 32)
+//     faster: 4096, B = 32: 29.7 against 27.4*; from 5504 on 60 against 41 (B = 1); 9216: 99 against 94 (B = 1), 111
+//     against 97 (B = 32)
 // Wider layers than 9216 stay with one launch.  A build without the limit gained on Q + K + V (10240: 0.81 to 1.10 of the
 // one-launch kernel's time; 11264 and 12288, where that kernel's workgroups need a second round: 0.47 to 0.87; 16384: 0.60 to
 // 0.97), but lost on Q alone from 11264 on (up to 1.07 there, 1.14 at 12288, 1.27 at 14336), and q must come from the same
