@@ -36,10 +36,10 @@ inline bool contiguous(int64_t pairs, int steps, int head_dim)
 }
 
 // With the longest length that the table has room for, and the tokens of all requests as far as the host knows.  Lengths that
-// differ make the ranges worse (a
-// wavefront searches its requests, and steps over those that end) and leave compute units to the long pairs: half of the
-// requests 16 tokens, half L, 256 pairs, L = 1000: 16.1 us against 27.6; 1024 pairs, L = 2000: 93.5 against 122; lengths L/2 to L, 32
-// requests x 32 heads, L = 1000: 71.7 against 77.0; 2560 pairs, L = 2000: 320 against 326; 864, L = 4000: 232 against 230.
+// differ make the ranges worse (a wavefront searches its requests, and steps over those that end) and leave compute units to the
+// long pairs: half of the requests 16 tokens, half L, 256 pairs, L = 1000: 16.1 us against 27.6; 1024 pairs, L = 2000: 93.5 against
+// 122; lengths L/2 to L, 32 requests x 32 heads, L = 1000: 71.7 against 77.0; 2560 pairs, L = 2000: 320 against 326; 864, L = 4000:
+// 232 against 230.
 // What a workgroup per pair cannot balance is a few long requests among many short ones: beyond short contexts the tokens have to
 // be those of 224 pairs of full length, or half of what the table has room for where there are fewer than 448 pairs.
 // `tokens` may be a bound, up to the room, whatever the lengths are: the lines for n lie where one long request among short ones
